@@ -567,15 +567,6 @@ struct Tail2Args {
     int ou[kTail2Levels], ob[kTail2Levels], ow[kTail2Levels], orr[kTail2Levels];
 };
 
-// One wavefront's LDS accesses run in order; this keeps the compiler from
-// moving them across the phase boundary.
-__device__ __forceinline__ void wave_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // q / d for q (d - 1) < 65536 with m = ceil(65536 / d): the integer division
 // by a variable takes ~35 instructions, on the critical path of each phase.
 __device__ __forceinline__ int div16(int q, unsigned m) { return int((unsigned(q) * m) >> 16); }
@@ -618,7 +609,7 @@ __global__ __launch_bounds__(kTail2Threads) void k2_tail(Tail2Args A)
     };
     auto sync = [](bool one) {
         if (one)
-            wave_order();
+            mafas::lds_wave_order();
         else
             mafas::lds_barrier();
     };

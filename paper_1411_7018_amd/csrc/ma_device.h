@@ -240,31 +240,43 @@ __device__ __noinline__ double gershgorin_start(Hess g, double F)
 // nonconvex is set when F <= 0, when Newton does not settle within 64
 // steps, or when the result is not finite; such nodes take the general
 // closed form.
-__device__ __forceinline__ double smallest_root(const Hess &g, double F, bool &nonconvex)
-{
-    const double mab = g.xx * g.yy - g.xy * g.xy;
-    const double I1 = g.xx + g.yy + g.zz;
-    const double I2 = mab + (g.xx * g.zz - g.xz * g.xz) + (g.yy * g.zz - g.yz * g.yz);
-    const double I3 = det3(g);
-    const double c0 = I3 - F;
-    const bool spd = g.xx > 0.0 && mab > 0.0 && I3 > 0.0;
+// root_start takes the two steps every lane takes and says whether they
+// settled the node; root_finish is the rule for the others.  A caller whose
+// next step waits on the result (a dependent phase) can store it between the
+// two, ahead of the test.
+struct RootState {
+    double I1, I2, c0, sig, thr, dprev, ad;
+    bool spd, settled;
+
     // one Newton step; returns |step|
-    double sig = 0.0;
-    auto newton = [&]() {
+    __device__ __forceinline__ double newton()
+    {
         const double q = ((I1 - sig) * sig - I2) * sig + c0;
         const double dq = (2.0 * I1 - 3.0 * sig) * sig - I2;
         const double d = q * __builtin_amdgcn_rcp(dq);
         sig -= d;
         return fabs(d);
-    };
+    }
     // a first step already below the threshold settles the node as it
     // would have alone (the second is then round-off, as large as the first
     // may be, and the ratio test says nothing)
     // (bitwise operators: all three comparisons are cheap, and a
     // short-circuit would cost a divergent branch)
-    auto test = [](double ad, double dprev, double thr) {
+    __device__ __forceinline__ bool test() const
+    {
         return bool(!(ad > thr) & (!(ad > 1e-3 * dprev) | !(dprev > thr)));
-    };
+    }
+};
+
+// true: R.sig is the root
+__device__ __forceinline__ bool root_start(const Hess &g, double F, RootState &R)
+{
+    const double mab = g.xx * g.yy - g.xy * g.xy;
+    R.I1 = g.xx + g.yy + g.zz;
+    R.I2 = mab + (g.xx * g.zz - g.xz * g.xz) + (g.yy * g.zz - g.yz * g.yz);
+    const double I3 = det3(g);
+    R.c0 = I3 - F;
+    R.spd = g.xx > 0.0 && mab > 0.0 && I3 > 0.0;
     // Every lane takes the two steps from the SPD start sig = 0; one branch
     // then sends the rest (a non-SPD Hessian, no settling yet, a non-finite
     // iterate, F <= 0) down the full rule, which redoes the start where it
@@ -273,42 +285,51 @@ __device__ __forceinline__ double smallest_root(const Hess &g, double F, bool &n
     // general expressions give exactly these for finite invariants; a
     // non-finite one makes the second step non-finite and takes the full
     // rule), and the threshold is 1e-9 |I1|.
-    double thr = 1e-9 * fabs(I1);
-    double dprev;
-    {
-        const double d = c0 * __builtin_amdgcn_rcp(-I2);
-        sig = -d;
-        dprev = fabs(d);
-    }
-    double ad = newton();
-    bool settled = test(ad, dprev, thr);
-    if (!((F > 0.0) & spd & settled & bool(isfinite(sig)))) {
-        if (F > 0.0) {
-            if (!spd) {
-                sig = gershgorin_start(g, F);
-                thr = 1e-9 * (fabs(I1) + fabs(sig));
-                dprev = newton();
-                ad = newton();
-                settled = test(ad, dprev, thr);
-            }
-            if (!settled) {
-                dprev = ad;
-                for (int it = 2; it < 64; ++it) {
-                    ad = newton();
-                    if (!(ad > thr) && !(ad > 1e-3 * dprev)) {
-                        settled = true;
-                        break;
-                    }
-                    dprev = ad;
+    R.thr = 1e-9 * fabs(R.I1);
+    const double d = R.c0 * __builtin_amdgcn_rcp(-R.I2);
+    R.sig = -d;
+    R.dprev = fabs(d);
+    R.ad = R.newton();
+    R.settled = R.test();
+    return bool((F > 0.0) & R.spd & R.settled & bool(isfinite(R.sig)));
+}
+
+__device__ __forceinline__ double root_finish(const Hess &g, double F, RootState &R,
+                                              bool &nonconvex)
+{
+    if (F > 0.0) {
+        if (!R.spd) {
+            R.sig = gershgorin_start(g, F);
+            R.thr = 1e-9 * (fabs(R.I1) + fabs(R.sig));
+            R.dprev = R.newton();
+            R.ad = R.newton();
+            R.settled = R.test();
+        }
+        if (!R.settled) {
+            R.dprev = R.ad;
+            for (int it = 2; it < 64; ++it) {
+                R.ad = R.newton();
+                if (!(R.ad > R.thr) && !(R.ad > 1e-3 * R.dprev)) {
+                    R.settled = true;
+                    break;
                 }
+                R.dprev = R.ad;
             }
         }
-        if (!(F > 0.0) || !settled || !isfinite(sig)) {
-            nonconvex = true;
-            sig = smallest_root_general(g, F);
-        }
     }
-    return sig;
+    if (!(F > 0.0) || !R.settled || !isfinite(R.sig)) {
+        nonconvex = true;
+        R.sig = smallest_root_general(g, F);
+    }
+    return R.sig;
+}
+
+__device__ __forceinline__ double smallest_root(const Hess &g, double F, bool &nonconvex)
+{
+    RootState R;
+    if (root_start(g, F, R))
+        return R.sig;
+    return root_finish(g, F, R, nonconvex);
 }
 
 // New centre value of one nonlinear Gauss-Seidel update (eq. 2.9 in the

@@ -32,7 +32,8 @@ constexpr int kDefaultMaxBlocks = 16384;
 constexpr int kTailThreads = 512;      // threads of the coarse-level kernel
 constexpr int kMaxTail = 6;            // levels per solve inside that kernel
 constexpr int kTailLdsThreads = 1024;  // threads of its LDS form
-constexpr int kTailLdsDoubles = 18432; // LDS of that form (144 KiB): levels 16, 8, 4, 2
+constexpr int kTailFastN = 16;         // largest level of its 4-colour kernel
+constexpr int kTailLdsDoubles = 19456; // LDS of that form (152 KiB): levels 16, 8, 4, 2
 
 // One grid of one solve inside a batched launch.  Every work item is one
 // wavefront handling 64 nodes of one x-row (bx, by, bz) of a gx x gy x gz
@@ -104,8 +105,10 @@ static_assert(offsetof(RrList, g) == 16, "list header is 16 bytes");
 // LDS form: offsets (in doubles) of each level's u, b, w, r in LDS, -1
 // where the level has no such array (w above the first level, r on the
 // coarsest).
+// md: the factor that divides by n + 1 (div18 in ma_engine.hip).
 struct TailLds {
     int u[kMaxTail], b[kMaxTail], w[kMaxTail], r[kMaxTail];
+    unsigned md[kMaxTail];
 };
 struct TailEntry {
     int nlev;
@@ -193,9 +196,10 @@ hipError_t launch_tail(hipStream_t st, int mode, int order, int rmode, const Tai
                        unsigned long long *nfall);
 // fused residual + restriction (op: OP_MA / OP_LAP), one block per tile
 hipError_t launch_rrestrict(hipStream_t st, int op, int rmode, const RrList *L, int blocks);
-// the LDS form (MODE_MA, MODE_LAP; every entry with lds = 1)
-hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, const TailList *T,
-                           int blocks, int nu1, int nu2, int nu0, unsigned long long *ncount);
+// the LDS form (MODE_MA, MODE_LAP; every entry with lds = 1); fast: every
+// entry's levels have at most kTailFastN intervals
+hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
+                           const TailList *T, int blocks, int nu1, int nu2, int nu0, unsigned long long *ncount);
 
 struct SolveRef {
     ma_solver *s = nullptr;
@@ -321,6 +325,7 @@ class Engine {
     size_t toff_ = 0;                      // byte offset of the tail table
     int tail_blocks_ = 0;                  // blocks of the tail launch (0: no tail)
     bool tail_lds_ = false;                // the tail launch is the LDS form
+    bool tail_fast_ = false;               // and its levels have at most kTailFastN intervals
     char *dl_ = nullptr;                   // device lists
     size_t dl_cap_ = 0;
     char *hstage_ = nullptr;               // pinned staging for uploads

@@ -23,6 +23,7 @@
 #include <cstdint>
 #include <cstring>
 #include <limits>
+#include <type_traits>
 
 namespace mafas {
 
@@ -1086,15 +1087,436 @@ __global__ __launch_bounds__(kTailLdsThreads) void k_tail_lds(
     }
 }
 
-template <int OP, int ORDER>
-hipError_t launch_tail_lds_t(hipStream_t st, int rmode, const TailList *T, int blocks, int nu1,
-                             int nu2, int nu0, unsigned long long *nc)
+
+// q / d for q (d - 1) < 2^18 with m = ceil(2^18 / d).
+__device__ __forceinline__ int div18(int q, unsigned m) { return int((unsigned(q) * m) >> 18); }
+
+// The same for the 4-colour ordering and n <= kTailFastN, the common case.
+// One compute unit runs ~60 dependent phases.  At n = 16 a phase (840 updates
+// on 15 wavefronts) is bound by the instructions it issues; below, a wavefront
+// issues one instruction every four clocks or slower, so a phase lasts as long
+// as its instruction count says.  Hence every level size is a template
+// parameter, and what a phase does besides its update is worked out once per
+// visit of a level:
+//   - LDS strides are constants: the 19 values of a node come from two base
+//     offsets and the reads' immediate offsets (they took ~35 address
+//     instructions of ~200 a phase);
+//   - a thread keeps one position of the colour classes: its node of each
+//     colour is a fixed offset away and the nodes of all colours are the
+//     level's interior, so the residual takes the same positions; the
+//     correction takes blocks of 2 x 2 x 2 nodes, which share eight coarse
+//     values without a branch on the node's parities;
+//   - rows hold the even columns, then (from H on) the odd ones, so the nodes
+//     of a colour are contiguous, and u's rows are P = 4 mod 16 doubles apart
+//     from n = 9 on, which spreads the 8 columns x 4 rows of a half wavefront
+//     over all banks;
+//   - levels whose colours fit a wavefront (n <= 7) run on the first wavefront
+//     alone, down and up again, without barriers;
+//   - the Dirichlet data of every level is injected once, at entry.
+// The expressions of a node are those of k_tail, so results are bitwise the
+// same.  A V-cycle from n = 16 takes 41-47 us (55-59 before), a linear one 24 us
+// (32).
+__host__ __device__ constexpr int tail_pitch(int n) { return n < 9 ? n + 1 : n + 1 + (36 - (n + 1)) % 16; }
+
+// One level in LDS (u and w rows of tail_pitch(n), b and r rows of n + 1).
+struct TailLev {
+    double *u, *b, *w, *r;
+};
+
+// What every thread carries through the levels.  base: the LDS offset of the
+// current level, whose arrays follow each other in the order u, b, w, r (the
+// layout rebuild() makes: no w on the top level), so no level reads a table.
+struct TailCtx {
+    double *S;
+    int tid, nu1, nu2, nu0, bad, base;
+};
+
+// The phases of level size N; ONE: the first wavefront runs them alone.
+template <int OP, int RMODE, int N>
+struct TailSize {
+    static constexpr int HN = N / 2, H = N / 2 + 1, P = tail_pitch(N), Q = N + 1;
+    static constexpr int PZ = (N + 1) * P, QZ = (N + 1) * Q;
+    static constexpr int NU = (N + 1) * (N + 1) * P, NB = (N + 1) * (N + 1) * Q;
+    static constexpr int CNT = HN * HN * (N - 1);   // positions of a colour class
+    // as the host computes them for the row kernels
+    static constexpr double s = double(N) * double(N);
+    static constexpr double hk = OP == OP_MA ? 0.5 / s : 1.0 / (6.0 * s);
+    static constexpr bool ONE = CNT <= 64, COARSER = N % 2 == 0 && N >= 4;
+    static constexpr int NT = ONE ? 64 : kTailLdsThreads;
+    static_assert(CNT <= kTailLdsThreads, "a thread has at most one position");
+    // the next level
+    static constexpr int CN = N / 2, CH = CN / 2 + 1, CP = CN + 1, CZ = (CN + 1) * CP;
+    static_assert(!COARSER || tail_pitch(CN) == CP, "coarser levels are not padded");
+
+    static __device__ __forceinline__ void sync()
+    {
+        if (ONE)
+            lds_wave_order();
+        else
+            lds_barrier();
+    }
+
+    // offsets of this thread's node of each colour in u (o; l: its x - 1
+    // neighbour, whose next double is the x + 1 neighbour) and in b / r
+    struct Nodes {
+        int o[4], l[4], ob[4];
+        bool in[4];
+    };
+    static __device__ __forceinline__ Nodes nodes(int tid)
+    {
+        Nodes M;
+        const int ii = tid % HN, jj = tid / HN % HN, k = 1 + tid / (HN * HN);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int jp = (c ^ (c >> 1) ^ k) & 1, ip = (c ^ jp) & 1;   // 1: odd
+            const int i = 2 * ii + 2 - ip, j = 2 * jj + 2 - jp;
+            const int row = k * (N + 1) + j, x = ip ? H + ii : ii + 1;
+            M.o[c] = row * P + x;
+            M.l[c] = row * P + (ip ? ii : H + ii);
+            M.ob[c] = row * Q + x;
+            M.in[c] = bool((tid < CNT) & (i <= N - 1) & (j <= N - 1));
+        }
+        return M;
+    }
+
+    // the 19 (7) values around the node at o with x neighbours at l and l + 1
+    static __device__ __forceinline__ Hess hess(const double *u, int o, int l)
+    {
+        const double *C = u + o, *X = u + l;
+        constexpr double s4 = 0.25 * s;
+        const double c = C[0];
+        const double w = X[0], e = X[1], a = C[-P], b = C[P], d = C[-PZ], t = C[PZ];
+        const double wa = X[-P], ea = X[1 - P], wb = X[P], eb = X[1 + P];
+        const double wd = X[-PZ], ed = X[1 - PZ], wt = X[PZ], et = X[1 + PZ];
+        const double ad = C[-PZ - P], bd = C[P - PZ], at = C[PZ - P], bt = C[PZ + P];
+        // every read is issued before the first value is used (the compiler
+        // takes them in three batches and waits for each)
+        __builtin_amdgcn_sched_barrier(0);
+        Hess g;
+        g.xx = ((e - c) - (c - w)) * s;
+        g.yy = ((b - c) - (c - a)) * s;
+        g.zz = ((t - c) - (c - d)) * s;
+        g.xy = ((eb - wb) - (ea - wa)) * s4;
+        g.xz = ((et - wt) - (ed - wd)) * s4;
+        g.yz = ((bt - at) - (bd - ad)) * s4;
+        return g;
+    }
+    static __device__ __forceinline__ double lap(const double *u, int o, int l)
+    {
+        const double *C = u + o, *X = u + l;
+        const double c = C[0];
+        return (((X[1] - c) - (c - X[0])) + ((C[P] - c) - (c - C[-P])) +
+                ((C[PZ] - c) - (c - C[-PZ]))) * s;
+    }
+
+    static __device__ __forceinline__ void sweeps(TailCtx &X, const TailLev &V, const Nodes &M,
+                                                  int count)
+    {
+        double F[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            F[c] = V.b[M.in[c] ? M.ob[c] : 0];
+#pragma unroll 1
+        for (int k = 0; k < count; ++k)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (M.in[c]) {
+                    const double v = V.u[M.o[c]];
+                    if (OP == OP_MA) {
+                        // the two-step root is stored ahead of its test, off
+                        // the chain to the next phase
+                        RootState R;
+                        const Hess g = hess(V.u, M.o[c], M.l[c]);
+                        const bool ok = root_start(g, F[c], R);
+                        V.u[M.o[c]] = v + R.sig * hk;
+                        if (!ok) {
+                            bool nc = false;
+                            V.u[M.o[c]] = v + root_finish(g, F[c], R, nc) * hk;
+                            X.bad += nc ? 1 : 0;
+                        }
+                    } else {
+                        V.u[M.o[c]] = lap_point_update(lap(V.u, M.o[c], M.l[c]), v, F[c], hk);
+                    }
+                }
+                sync();
+            }
+    }
+
+    // residual of V, then b, w and u of the next level's interior
+    static __device__ __forceinline__ void restrict_to(int tid, const TailLev &V, const Nodes &M,
+                                                       const TailLev &C)
+    {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (M.in[c]) {
+                const double F = V.b[M.ob[c]];
+                if (OP == OP_MA)
+                    V.r[M.ob[c]] = F - det3(hess(V.u, M.o[c], M.l[c]));
+                else
+                    V.r[M.ob[c]] = F - lap(V.u, M.o[c], M.l[c]);
+            }
+        sync();
+        constexpr int m = CN - 1;
+        constexpr double sc = double(CN) * double(CN);
+        for (int q = tid; q < m * m * m; q += NT) {
+            const int I = 1 + q % m, J = 1 + q / m % m, K = 1 + q / (m * m);
+            const int row = 2 * K * (N + 1) + 2 * J;
+            const double *U = V.u + row * P + I, *R = V.r + row * Q + I;
+            const int crow = K * (CN + 1) + J, cx = (I & 1) * CH + (I >> 1);
+            const int c = crow * CP + cx;
+            const double v = U[0];
+            C.w[c] = v;
+            C.u[c] = v;
+            double rh;
+            if (RMODE == 0) {
+                const double w[3] = {0.25, 0.5, 0.25};
+                rh = 0.0;
+#pragma unroll
+                for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+                    for (int dy = -1; dy <= 1; ++dy) {
+                        const double *T = R + Q * dy + QZ * dz;
+                        const double wz = w[dz + 1] * w[dy + 1];
+                        rh += (wz * w[0]) * T[H - 1];
+                        rh += (wz * w[1]) * T[0];
+                        rh += (wz * w[2]) * T[H];
+                    }
+            } else {
+                rh = (6.0 * R[0] + (R[H - 1] + R[H]) + (R[-Q] + R[Q]) + (R[-QZ] + R[QZ])) / 12.0;
+            }
+            double sh;
+            if (OP == OP_MA)
+                sh = det3(hessian3(U - 2 * PZ, U, U + 2 * PZ, 1, -1, 2 * P, sc, 0.25 * sc));
+            else
+                sh = laplacian3(U - 2 * PZ, U, U + 2 * PZ, 1, -1, 2 * P, sc);
+            C.b[c] = sh + rh;
+        }
+        sync();
+    }
+
+    // Trilinear correction of the nodes (2 a + 1 | 2, 2 b + 1 | 2, 2 c + 1 | 2)
+    // of block (a, b, c) from the coarse nodes a, a + 1 x b, b + 1 x c, c + 1:
+    // the sums of prolong_node (over z, then y, then x, from d = 0).
+    static __device__ __forceinline__ void correct(int tid, const TailLev &V, const TailLev &C)
+    {
+        for (int q = tid; q < HN * HN * HN; q += NT) {
+            const int a = q % HN, b = q / HN % HN, c = q / (HN * HN);
+            const int x[2] = {(a & 1) * CH + (a >> 1), ((a + 1) & 1) * CH + ((a + 1) >> 1)};
+            double e[2][2][2];
+#pragma unroll
+            for (int z = 0; z < 2; ++z)
+#pragma unroll
+                for (int y = 0; y < 2; ++y)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const int o = CP * (b + y) + CZ * (c + z) + x[t];
+                        e[z][y][t] = C.u[o] - C.w[o];
+                    }
+            // node (da, db, dc): 0 odd (two coarse nodes along the axis), 1 even
+            // (the upper one)
+#pragma unroll
+            for (int m = 0; m < 8; ++m) {
+                const int da = m & 1, db = (m >> 1) & 1, dc = m >> 2;
+                const double w = (da ? 1.0 : 0.5) * (db ? 1.0 : 0.5) * (dc ? 1.0 : 0.5);
+                double d = 0.0;
+#pragma unroll
+                for (int z = dc; z < 2; ++z)
+#pragma unroll
+                    for (int y = db; y < 2; ++y)
+#pragma unroll
+                        for (int t = da; t < 2; ++t)
+                            d += w * e[z][y][t];
+                if (2 * a + 1 + da <= N - 1 && 2 * b + 1 + db <= N - 1 && 2 * c + 1 + dc <= N - 1)
+                    V.u[((2 * c + 1 + dc) * (N + 1) + 2 * b + 1 + db) * P + (da ? a + 1 : H + a)] +=
+                        d;
+            }
+        }
+        sync();
+    }
+
+    // One visit of the level: on the way down (the coarsest level included)
+    // sweeps, then residual and restriction; on the way up the correction,
+    // then sweeps.
+    static __device__ __forceinline__ void visit(TailCtx &X, bool top, bool down)
+    {
+        // opaque, or the offsets of every level size are computed ahead of the
+        // loop over the visits and spilled
+        int tid = X.tid;
+        asm volatile("" : "+v"(tid));
+        const Nodes M = nodes(tid);
+        const int size = NU + NB + (top ? 0 : NU) + NB;   // of a level with a coarser one
+        if (!down)
+            X.base -= size;
+        TailLev V, C;
+        V.u = X.S + X.base;
+        V.b = V.u + NU;
+        V.w = V.b + NB;
+        V.r = V.b + NB + (top ? 0 : NU);
+        if (!COARSER) {
+            sweeps(X, V, M, X.nu0);
+            return;
+        }
+        constexpr int CU = (CN + 1) * CZ;   // all four arrays of the coarser level
+        C.u = V.u + size;
+        C.b = C.u + CU;
+        C.w = C.b + CU;
+        C.r = C.w + CU;
+        if (!down)
+            correct(tid, V, C);
+        sweeps(X, V, M, down ? int(X.nu1) : int(X.nu2));
+        if (down) {
+            restrict_to(tid, V, M, C);
+            X.base += size;
+        }
+    }
+};
+
+template <int OP, int RMODE>
+__global__ __launch_bounds__(kTailLdsThreads) void k_tail_lds4(
+    const TailList *__restrict__ T, int nu1, int nu2, int nu0,
+    unsigned long long *__restrict__ ncount)
+{
+    __shared__ double S[kTailLdsDoubles];
+    if (int(blockIdx.x) >= T->nsolves)
+        return;
+    const TailEntry &E = T->e[blockIdx.x];
+    const int slot = E.lv[0].sw.slot;
+    if ((T->stopped >> slot) & 1ull)
+        return;
+    TailCtx X;
+    X.S = S;
+    X.tid = int(threadIdx.x);
+    X.nu1 = nu1;
+    X.nu2 = nu2;
+    X.nu0 = nu0;
+    X.bad = 0;
+    X.base = 0;
+    const int L = E.nlev, tid = X.tid;
+    constexpr int NT = kTailLdsThreads;
+
+    // ---- load the top level, five nodes a thread in flight together
+    const int n0 = E.lv[0].sw.n, m0 = n0 + 1, N0 = m0 * m0 * m0;
+    const int P0 = tail_pitch(n0), H0 = n0 / 2 + 1;
+    double *u0 = S;
+    {
+        const auto gu = gptr<const double>(E.lv[0].sw.p[0]);
+        const auto gb = gptr<const double>(E.lv[0].sw.p[1]);
+        const unsigned md = E.L.md[0];
+        double *b0 = S + m0 * m0 * P0;
+        constexpr int KQ = ((kTailFastN + 1) * (kTailFastN + 1) * (kTailFastN + 1) + NT - 1) / NT;
+        double vu[KQ], vb[KQ];
+#pragma unroll
+        for (int e = 0; e < KQ; ++e) {
+            const int q = tid + e * NT;
+            vu[e] = gu[q < N0 ? q : 0];
+            vb[e] = gb[q < N0 ? q : 0];
+        }
+#pragma unroll
+        for (int e = 0; e < KQ; ++e) {
+            const int q = tid + e * NT, row = div18(q, md), i = q - row * m0;
+            const int x = (i & 1) * H0 + (i >> 1);
+            if (q < N0) {
+                u0[row * P0 + x] = vu[e];
+                b0[row * m0 + x] = vb[e];
+            }
+        }
+    }
+    lds_barrier();
+    // the Dirichlet data of the coarser levels' u and w (whole grids: the
+    // interior is overwritten by the restriction)
+    for (int l = 1; l < L; ++l) {
+        const int m = (n0 >> l) + 1;
+        const unsigned md = E.L.md[l];
+        double *u = S + E.L.u[l], *w = S + E.L.w[l];
+        for (int q = tid; q < m * m * m; q += NT) {
+            const int row = div18(q, md), K = div18(row, md);
+            const int I = q - row * m, J = row - K * m, i = I << l;
+            const double v = u0[((K << l) * m0 + (J << l)) * P0 + (i & 1) * H0 + (i >> 1)];
+            const int c = row * m + (I & 1) * (m / 2 + m % 2) + (I >> 1);
+            u[c] = v;
+            w[c] = v;
+        }
+    }
+    lds_barrier();
+
+    // ---- V-cycle: the larger levels on the whole workgroup, the others, down
+    // and up again, on the first wavefront
+    auto visit = [&](auto ONE, int l, bool down) {
+        switch (n0 >> l) {
+#define MA_TAIL_CASE(N)                                                                          \
+    case N:                                                                                      \
+        if (TailSize<OP, RMODE, N>::ONE == decltype(ONE)::value)                                 \
+            TailSize<OP, RMODE, N>::visit(X, l == 0, down);                                      \
+        break;
+            MA_TAIL_CASE(2)
+            MA_TAIL_CASE(3)
+            MA_TAIL_CASE(4)
+            MA_TAIL_CASE(5)
+            MA_TAIL_CASE(6)
+            MA_TAIL_CASE(7)
+            MA_TAIL_CASE(8)
+            MA_TAIL_CASE(9)
+            MA_TAIL_CASE(10)
+            MA_TAIL_CASE(11)
+            MA_TAIL_CASE(12)
+            MA_TAIL_CASE(13)
+            MA_TAIL_CASE(14)
+            MA_TAIL_CASE(15)
+            MA_TAIL_CASE(16)
+#undef MA_TAIL_CASE
+        default:
+            break;
+        }
+    };
+    static_assert(kTailFastN == 16, "one case per level size");
+    int many = 0;   // levels of more than a wavefront's positions
+    while (many < L && colour_count<0>(n0 >> many) > 64)
+        ++many;
+#pragma unroll 1
+    for (int k = 0; k <= 2 * many; ++k) {
+        if (k == many) {
+            const int m = L - many;
+            if (tid < 64) {
+#pragma unroll 1
+                for (int q = 0; q < 2 * m - 1; ++q)
+                    visit(std::true_type{}, many + (q < m ? q : 2 * m - 2 - q), q < m);
+            }
+            lds_barrier();
+        } else {
+            const int l = k < many ? k : 2 * many - k;
+            if (k < many || l < L - 1)   // the coarsest has no way up
+                visit(std::false_type{}, l, k < many);
+        }
+    }
+
+    if (OP == OP_MA && __builtin_amdgcn_ballot_w64(X.bad > 0)) {
+        int bad = X.bad;
+        for (int off = 32; off > 0; off >>= 1)
+            bad += __shfl_down(bad, off, 64);
+        if ((tid & 63) == 0)
+            atomicAdd(ncount + slot, (unsigned long long)bad);
+    }
+    {
+        const auto gu = gptr<double>(E.lv[0].sw.p[0]);
+        const unsigned md = E.L.md[0];
+        for (int q = tid; q < N0; q += NT) {
+            const int row = div18(q, md), i = q - row * m0;
+            gu[q] = u0[row * P0 + (i & 1) * H0 + (i >> 1)];
+        }
+    }
+}
+
+template <int OP, int RMODE>
+hipError_t launch_tail_lds_t(hipStream_t st, int order, bool fast, const TailList *T, int blocks,
+                             int nu1, int nu2, int nu0, unsigned long long *nc)
 {
     const dim3 grid(blocks), block(kTailLdsThreads);
-    if (rmode == 0)
-        hipLaunchKernelGGL((k_tail_lds<OP, ORDER, 0>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
+    if (order == 1)
+        hipLaunchKernelGGL((k_tail_lds<OP, 1, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
+    else if (fast)
+        hipLaunchKernelGGL((k_tail_lds4<OP, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
     else
-        hipLaunchKernelGGL((k_tail_lds<OP, ORDER, 1>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
+        hipLaunchKernelGGL((k_tail_lds<OP, 0, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
     return hipGetLastError();
 }
 
@@ -1287,19 +1709,19 @@ hipError_t launch_rrestrict(hipStream_t st, int op, int rmode, const RrList *L, 
     return rmode == 0 ? launch_rr_t<OP_LAP, 0>(st, L, blocks) : launch_rr_t<OP_LAP, 1>(st, L, blocks);
 }
 
-hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, const TailList *T,
-                           int blocks, int nu1, int nu2, int nu0, unsigned long long *nc)
+hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
+                           const TailList *T, int blocks, int nu1, int nu2, int nu0, unsigned long long *nc)
 {
     if (blocks <= 0 || blocks > kMaxGrids)
         return hipErrorInvalidValue;
     if (mode != Engine::MODE_MA && mode != Engine::MODE_LAP)
         return hipErrorInvalidValue;
     const bool ma = mode == Engine::MODE_MA;
-    if (order == 0)
-        return ma ? launch_tail_lds_t<OP_MA, 0>(st, rmode, T, blocks, nu1, nu2, nu0, nc)
-                  : launch_tail_lds_t<OP_LAP, 0>(st, rmode, T, blocks, nu1, nu2, nu0, nc);
-    return ma ? launch_tail_lds_t<OP_MA, 1>(st, rmode, T, blocks, nu1, nu2, nu0, nc)
-              : launch_tail_lds_t<OP_LAP, 1>(st, rmode, T, blocks, nu1, nu2, nu0, nc);
+    if (rmode == 0)
+        return ma ? launch_tail_lds_t<OP_MA, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc)
+                  : launch_tail_lds_t<OP_LAP, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc);
+    return ma ? launch_tail_lds_t<OP_MA, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc)
+              : launch_tail_lds_t<OP_LAP, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc);
 }
 
 // ---------------------------------------------------------------------------
@@ -1807,14 +2229,16 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             Ld.u[l] = Ld.b[l] = Ld.w[l] = Ld.r[l] = -1;
             if (l >= L - m)
                 continue;
-            const int N = int(npts(solves_[i].s->lv[m + l].n));
+            const int n = solves_[i].s->lv[m + l].n, N = int(npts(n));
+            const int U = (n + 1) * (n + 1) * tail_pitch(n);
+            Ld.md[l] = ((1u << 18) + n) / (n + 1);
             Ld.u[l] = off;
-            off += N;
+            off += U;
             Ld.b[l] = off;
             off += N;
             if (l > 0) {
                 Ld.w[l] = off;
-                off += N;
+                off += U;
             }
             if (l < L - m - 1) {
                 Ld.r[l] = off;
@@ -1824,11 +2248,13 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
         return off <= kTailLdsDoubles;
     };
     tail_lds_ = !mixed;
+    tail_fast_ = true;
     for (int i = 0; i < S && tail_lds_; ++i) {
         if (!solves_[i].s || levels(i) - multiblock_levels(i) <= 0)
             continue;
         TailLds Ld;
         tail_lds_ = levels(i) - multiblock_levels(i) <= kMaxTail && lds_layout(i, Ld);
+        tail_fast_ &= solves_[i].s->lv[multiblock_levels(i)].n <= kTailFastN;
     }
     toff_ = hbuf_.size();
     hbuf_.resize(toff_ + tail_bytes(S), 0);
@@ -2171,7 +2597,7 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
             }
         }
         if (tail_blocks_ > 0 && tail_lds_)
-            E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_,
+            E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_, tail_fast_,
                                   reinterpret_cast<const TailList *>(dl_ + toff_), tail_blocks_,
                                   nu1_, nu2_, nu0_, dcount_));
         else if (tail_blocks_ > 0)
@@ -2221,7 +2647,7 @@ std::vector<int> Engine::shape() const
     s.push_back(int(stride_));
     s.push_back(int(toff_));
     s.push_back(tail_blocks_);
-    s.push_back(tail_lds_ ? 1 : 0);
+    s.push_back((tail_lds_ ? 1 : 0) + (tail_fast_ ? 2 : 0));
     s.push_back(strip_rows_);
     s.push_back(int(loff_.size()));
     s.insert(s.end(), lgrid_.begin(), lgrid_.end());

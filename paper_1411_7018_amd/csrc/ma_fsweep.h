@@ -94,6 +94,15 @@ __device__ __forceinline__ void lds_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The same for accesses of one wavefront alone: its LDS accesses run in order,
+// so this only keeps the compiler from moving them across.
+__device__ __forceinline__ void lds_wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Block `tile` of grid G by a workgroup of NT threads; su: LDS.  Global
 // offsets are 32-bit: grids up to n = 1289.
 template <int OP, int TX, int TY, int TZ, int NT>
