@@ -64,9 +64,9 @@ typedef enum { MA_RESTRICT_FULL = 0, MA_RESTRICT_HALF = 1 } ma_restriction;
  * (pairs of sweeps go u -> t -> u; an odd last sweep runs per colour).  It
  * applies to the 4-colour ordering in MA_FP64 only. */
 typedef enum {
-    MA_SMOOTHER_AUTO = 0,      /* block sweeps on levels with n <= block_n that
-                                  have more than coarse_n intervals, one
-                                  launch per colour phase elsewhere           */
+    MA_SMOOTHER_AUTO = 0,      /* block sweeps on levels with n <= block_n,
+                                  z-stream sweeps from zsweep_n on, one launch
+                                  per colour phase elsewhere                  */
     MA_SMOOTHER_COLOR = 1,     /* one in-place launch per colour phase          */
     MA_SMOOTHER_FUSED = 2      /* block sweeps on every level                    */
 } ma_smoother;
@@ -105,7 +105,8 @@ typedef struct {
                               z-stream levels 0 picks 32x26 or 32x24 by a
                               model of the chunks' rounds                     */
     int block_n;           /* MA_SMOOTHER_AUTO: block sweeps on levels with
-                              n <= block_n; 0 automatic (64), -1 never          */
+                              n <= block_n; 0 automatic (64 with 4 colours, 88
+                              with 8), -1 never                                  */
     int graphs;            /* 1: replay each cycle from a captured hipGraph      */
     int coarse_n;          /* levels with n <= coarse_n (0..32) run inside one
                               single-workgroup kernel per solve; 0: off         */

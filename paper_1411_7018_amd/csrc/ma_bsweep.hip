@@ -33,6 +33,12 @@ constexpr BCfg kCfg[] = {{8, 8, 8, 256, 0},   {8, 8, 8, 512, 0},  {8, 8, 8, 1024
                          {32, 26, 0, 1024, 1536}, {40, 20, 0, 1024, -1},
                          {32, 24, 0, 1024, -1}};
 constexpr int kZsPureConfig = 11;
+// 8-colour block sweeps: enough threads for the first phase (its block grows
+// by 5, 3, 1 nodes) in one round.
+constexpr BCfg kCfg8[] = {{8, 8, 4, 256, 0}, {8, 8, 8, 320, 0}, {16, 8, 8, 512, 0}};
+constexpr int kNumCfg8 = int(sizeof(kCfg8) / sizeof(kCfg8[0]));
+
+const BCfg &shape_of(int order, int cfg) { return order == 0 ? kCfg[cfg] : kCfg8[cfg]; }
 
 // Compute units of the current device (one z-stream workgroup each at a time).
 int device_cus()
@@ -107,19 +113,58 @@ hipError_t zgo_one(hipStream_t st, const FsGrid &G, unsigned long long *nc)
     return hipGetLastError();
 }
 
-template <int OP, int TX, int TY, int TZ, int NT>
+template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0>
 hipError_t go_list(hipStream_t st, const FsList *L, int blocks, unsigned long long *nc)
 {
-    hipLaunchKernelGGL((k_bsweep<OP, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, L, nc);
+    hipLaunchKernelGGL((k_bsweep<OP, ORDER, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, L, nc);
     return hipGetLastError();
 }
 
-template <int OP, int TX, int TY, int TZ, int NT>
+template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0>
 hipError_t go_one(hipStream_t st, const FsGrid &G, unsigned long long *nc)
 {
     const int blocks = G.tiles_x * G.tiles_y * G.tiles_z;
-    hipLaunchKernelGGL((k_bsweep1<OP, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, G, nc);
+    hipLaunchKernelGGL((k_bsweep1<OP, ORDER, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, G, nc);
     return hipGetLastError();
+}
+
+template <int OP>
+hipError_t list_op8(int cfg, hipStream_t st, const FsList *L, int blocks, unsigned long long *nc)
+{
+    switch (cfg) {
+    case 0:
+        return go_list<OP, 8, 8, 4, 256, 1>(st, L, blocks, nc);
+    case 1:
+        return go_list<OP, 8, 8, 8, 320, 1>(st, L, blocks, nc);
+    case 2:
+        return go_list<OP, 16, 8, 8, 512, 1>(st, L, blocks, nc);
+    default:
+        return hipErrorInvalidValue;
+    }
+}
+
+template <int OP>
+hipError_t one_op8(int cfg, hipStream_t st, const FsGrid &G, unsigned long long *nc)
+{
+    switch (cfg) {
+    case 0:
+        return go_one<OP, 8, 8, 4, 256, 1>(st, G, nc);
+    case 1:
+        return go_one<OP, 8, 8, 8, 320, 1>(st, G, nc);
+    case 2:
+        return go_one<OP, 16, 8, 8, 512, 1>(st, G, nc);
+    default:
+        return hipErrorInvalidValue;
+    }
+}
+
+// Blocks of the Gauss-Seidel iteration: small ones while they give few
+// workgroups.
+const BCfg &gs_shape(int order, int n)
+{
+    if (order == 0)
+        return n <= 40 ? kCfg[5] : kCfg[0];
+    return n <= 40 ? kCfg8[0] : kCfg8[1];
 }
 
 template <int OP>
@@ -201,8 +246,10 @@ int bsweep_num_configs() { return kNumCfg; }
 // the blocks, each with fewer rounds of updates per phase, for more halo
 // recomputation (measured on the level-32 sweeps of one 129^3 solve: 1.7%
 // of the solve faster).
-int bsweep_pick(int n, long tiles8)
+int bsweep_pick(int order, int n, long tiles8)
 {
+    if (order == 1)
+        return n <= 32 && tiles8 < 256 ? 0 : n <= 64 ? 1 : 2;
     if (n <= 16)
         return 2;
     if (n <= 32)
@@ -219,10 +266,10 @@ int bsweep_zs_pick(int n)
     return zs_model_cost100(n, kZsPureConfig) <= zs_model_cost100(n, 7) ? kZsPureConfig : 7;
 }
 
-void bsweep_grid(int cfg, int n, const double *uin, double *uout, const double *F, int op,
-                 int slot, FsGrid *G)
+void bsweep_grid(int order, int cfg, int n, const double *uin, double *uout, const double *F,
+                 int op, int slot, FsGrid *G)
 {
-    const BCfg &b = kCfg[cfg];
+    const BCfg &b = shape_of(order, cfg);
     G->uin = uin;
     G->uout = uout;
     G->F = F;
@@ -248,30 +295,77 @@ void bsweep_grid(int cfg, int n, const double *uin, double *uout, const double *
     G->cu = G->cw = nullptr;
 }
 
-bool bsweep_is_zstream(int cfg) { return cfg >= 0 && cfg < kNumCfg && kCfg[cfg].zwg != 0; }
+bool bsweep_is_zstream(int order, int cfg)
+{
+    return order == 0 && cfg >= 0 && cfg < kNumCfg && kCfg[cfg].zwg != 0;
+}
 
-hipError_t launch_bsweep(hipStream_t st, int op, int cfg, const FsList *L, int blocks,
+hipError_t launch_bsweep(hipStream_t st, int op, int order, int cfg, const FsList *L, int blocks,
                          unsigned long long *nonconvex, bool prolong)
 {
-    if (cfg < 0 || cfg >= kNumCfg || blocks <= 0)
+    if (cfg < 0 || cfg >= (order == 0 ? kNumCfg : kNumCfg8) || blocks <= 0)
         return hipErrorInvalidValue;
+    if (order == 1) {
+        if (prolong)
+            return hipErrorInvalidValue;
+        return op == OP_MA ? list_op8<OP_MA>(cfg, st, L, blocks, nonconvex)
+                           : list_op8<OP_LAP>(cfg, st, L, blocks, nonconvex);
+    }
     if (op == OP_MA)
         return list_op<OP_MA>(cfg, st, L, blocks, nonconvex, prolong);
     return list_op<OP_LAP>(cfg, st, L, blocks, nonconvex, prolong);
 }
 
-hipError_t launch_bsweep_one(hipStream_t st, int op, int cfg, int n, const double *u_in,
-                             double *u_out, const double *F, unsigned long long *nonconvex)
+hipError_t launch_bsweep_one(hipStream_t st, int op, int order, int cfg, int n,
+                             const double *u_in, double *u_out, const double *F,
+                             unsigned long long *nonconvex)
 {
     if (n < 2)
         return hipErrorInvalidValue;
-    if (cfg < 0 || cfg >= kNumCfg)
-        cfg = bsweep_pick(n, long((n - 1 + 7) / 8) * ((n - 1 + 7) / 8) * ((n - 1 + 7) / 8));
+    if (cfg < 0 || cfg >= (order == 0 ? kNumCfg : kNumCfg8))
+        cfg = bsweep_pick(order, n, long((n - 1 + 7) / 8) * ((n - 1 + 7) / 8) * ((n - 1 + 7) / 8));
     FsGrid G;
-    bsweep_grid(cfg, n, u_in, u_out, F, op, 0, &G);
+    bsweep_grid(order, cfg, n, u_in, u_out, F, op, 0, &G);
+    if (order == 1)
+        return op == OP_MA ? one_op8<OP_MA>(cfg, st, G, nonconvex)
+                           : one_op8<OP_LAP>(cfg, st, G, nonconvex);
     if (op == OP_MA)
         return one_op<OP_MA>(cfg, st, G, nonconvex);
     return one_op<OP_LAP>(cfg, st, G, nonconvex);
+}
+
+int gs_blocks(int order, int n)
+{
+    const BCfg &b = gs_shape(order, n);
+    return ((n - 1 + b.tx - 1) / b.tx) * ((n - 1 + b.ty - 1) / b.ty) * ((n - 1 + b.tz - 1) / b.tz);
+}
+
+hipError_t launch_gs_step(hipStream_t st, int order, int n, const double *u_in, double *u_out,
+                          const double *F, const double *part_in, double *part_out, double *sum,
+                          unsigned long long *count, int *stop, int q, double thr)
+{
+    const BCfg &b = gs_shape(order, n);
+    FsGrid G;
+    GsStep A;
+    bsweep_grid(order, order == 0 ? int(&b - kCfg) : int(&b - kCfg8), n, u_in, u_out, F, OP_MA, 0,
+                &G);
+    A.part_in = part_in;
+    A.part_out = part_out;
+    A.sum = sum;
+    A.count = count;
+    A.stop = stop;
+    A.q = q;
+    A.thr = thr;
+    const dim3 grid(gs_blocks(order, n)), block(b.nt);
+    if (&b == &kCfg[5])
+        hipLaunchKernelGGL((k_gs_step<0, 8, 8, 4, 512>), grid, block, 0, st, G, A);
+    else if (&b == &kCfg[0])
+        hipLaunchKernelGGL((k_gs_step<0, 8, 8, 8, 256>), grid, block, 0, st, G, A);
+    else if (&b == &kCfg8[0])
+        hipLaunchKernelGGL((k_gs_step<1, 8, 8, 4, 256>), grid, block, 0, st, G, A);
+    else
+        hipLaunchKernelGGL((k_gs_step<1, 8, 8, 8, 320>), grid, block, 0, st, G, A);
+    return hipGetLastError();
 }
 
 } // namespace mafas

@@ -184,12 +184,12 @@ hipError_t launch_fsplit(hipStream_t st, int n, const double *F, double *fs, lon
 // block sweeps of an FsList (ma_fsweep.h): cfg block shape, blocks >= tiles;
 // prolong: a z-stream shape whose grids carry the coarse u and w (cu, cw)
 // and add the interpolated coarse correction to u_in as they read it
-hipError_t launch_bsweep(hipStream_t st, int op, int cfg, const FsList *L, int blocks,
+hipError_t launch_bsweep(hipStream_t st, int op, int order, int cfg, const FsList *L, int blocks,
                          unsigned long long *nonconvex, bool prolong = false);
-// whether block shape cfg is a z-stream shape
-bool bsweep_is_zstream(int cfg);
-void bsweep_grid(int cfg, int n, const double *uin, double *uout, const double *F, int op,
-                 int slot, FsGrid *G);
+// whether shape cfg of an ordering is a z-stream shape
+bool bsweep_is_zstream(int order, int cfg);
+void bsweep_grid(int order, int cfg, int n, const double *uin, double *uout, const double *F,
+                 int op, int slot, FsGrid *G);
 // one workgroup per TailList entry (blocks >= entries); mode: Engine::Mode
 hipError_t launch_tail(hipStream_t st, int mode, int order, int rmode, const TailList *T,
                        int blocks, int nu1, int nu2, int nu0, unsigned long long *ncount,

@@ -801,24 +801,11 @@ struct RrShape {
 };
 
 template <int OP, int RMODE, int TC, int NT>
-__global__ __launch_bounds__(NT) void k_rrestrict(const RrList *__restrict__ Lst)
+__device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double *__restrict__ su,
+                                               double *__restrict__ sr)
 {
     using R = RrShape<TC>;
     constexpr int RU = R::RU, RR = R::RR, UX = R::UX, RX = R::RX;
-    __shared__ double su[R::SU];
-    __shared__ double sr[R::SR];
-    const int total = Lst->total;
-    const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
-    if (t >= total)
-        return;
-    const int ng = Lst->ngrids;
-    int g = 0;
-    while (g + 1 < ng && Lst->g[g + 1].start <= t)
-        ++g;
-    const RrGrid G = Lst->g[g];   // the whole descriptor in one set of loads
-    if ((Lst->stopped >> G.slot) & 1ull)
-        return;
-    const int tile = t - G.start;
     const int nf = G.n, nc = nf / 2;
     const int tx = tile % G.tiles_x, rest = tile / G.tiles_x;
     const int ty = rest % G.tiles_y, tz = rest / G.tiles_y;
@@ -930,6 +917,48 @@ __global__ __launch_bounds__(NT) void k_rrestrict(const RrList *__restrict__ Lst
     }
 }
 
+template <int OP, int RMODE, int TC, int NT>
+__global__ __launch_bounds__(NT) void k_rrestrict(const RrList *__restrict__ Lst)
+{
+    __shared__ double su[RrShape<TC>::SU];
+    __shared__ double sr[RrShape<TC>::SR];
+    const int total = Lst->total;
+    const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
+    if (t >= total)
+        return;
+    const int ng = Lst->ngrids;
+    int g = 0;
+    while (g + 1 < ng && Lst->g[g + 1].start <= t)
+        ++g;
+    const RrGrid G = Lst->g[g];   // the whole descriptor in one set of loads
+    if ((Lst->stopped >> G.slot) & 1ull)
+        return;
+    rrestrict_tile<OP, RMODE, TC, NT>(G, t - G.start, su, sr);
+}
+
+// The same for one grid passed by value (gridDim.x = its tile count).
+template <int OP, int RMODE, int TC, int NT>
+__global__ __launch_bounds__(NT) void k_rrestrict1(RrGrid G)
+{
+    __shared__ double su[RrShape<TC>::SU];
+    __shared__ double sr[RrShape<TC>::SR];
+    rrestrict_tile<OP, RMODE, TC, NT>(G, tile_of_block(int(blockIdx.x), int(gridDim.x)), su, sr);
+}
+
+// Prolongation of one grid passed by value, one wavefront per work item (rows
+// in y-strips walked along z, as in a batched launch).
+__global__ __launch_bounds__(64) void k_prolong1(GridItem G)
+{
+    const int it = tile_of_block(int(blockIdx.x), int(gridDim.x));
+    const int bx = it % G.gx;
+    int rest = it / G.gx;
+    const int jj = rest % G.w;
+    rest /= G.w;
+    const int bz = rest % G.gz, by = (rest / G.gz) * G.w + jj;
+    if (by < G.gy)
+        prolong_row<double>(G, bx, int(threadIdx.x), 1 + by, 1 + bz);
+}
+
 // Threads per tile: 256 when the launch has many tiles (throughput), 512
 // when it has few (one tile's residual rounds are the latency).
 constexpr int kRrManyTiles = 2048;
@@ -941,6 +970,18 @@ hipError_t launch_rr_t(hipStream_t st, const RrList *L, int blocks)
         hipLaunchKernelGGL((k_rrestrict<OP, RMODE, kRrTile, 256>), dim3(blocks), dim3(256), 0, st, L);
     else
         hipLaunchKernelGGL((k_rrestrict<OP, RMODE, kRrTile, 512>), dim3(blocks), dim3(512), 0, st, L);
+    return hipGetLastError();
+}
+
+template <int RMODE>
+hipError_t launch_rr1_t(hipStream_t st, const RrGrid &G, int blocks)
+{
+    if (blocks >= kRrManyTiles)
+        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, kRrTile, 256>), dim3(blocks), dim3(256), 0,
+                           st, G);
+    else
+        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, kRrTile, 512>), dim3(blocks), dim3(512), 0,
+                           st, G);
     return hipGetLastError();
 }
 
@@ -1709,6 +1750,47 @@ hipError_t launch_rrestrict(hipStream_t st, int op, int rmode, const RrList *L, 
     return rmode == 0 ? launch_rr_t<OP_LAP, 0>(st, L, blocks) : launch_rr_t<OP_LAP, 1>(st, L, blocks);
 }
 
+// Tiles of an nf grid; *G its descriptor.
+static int rr_grid(int nf, const double *uf, const double *F, double *wc, double *uc, double *bc,
+                   int slot, RrGrid *G)
+{
+    std::memset(G, 0, sizeof(*G));
+    G->uf = uf;
+    G->F = F;
+    G->wc = wc;
+    G->uc = uc;
+    G->bc = bc;
+    G->n = nf;
+    G->slot = slot;
+    G->tiles_x = G->tiles_y = G->tiles_z = (nf / 2 + 1 + kRrTile - 1) / kRrTile;
+    G->s = double(nf) * double(nf);
+    return G->tiles_x * G->tiles_y * G->tiles_z;
+}
+
+hipError_t launch_restrict(hipStream_t st, int rmode, int nf, const double *uf, const double *F,
+                           double *wc, double *uc, double *bc)
+{
+    RrGrid G;
+    const int blocks = rr_grid(nf, uf, F, wc, uc, bc, 0, &G);
+    if (rmode == 0)
+        return launch_rr1_t<0>(st, G, blocks);
+    return launch_rr1_t<1>(st, G, blocks);
+}
+
+hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc, const double *wc)
+{
+    GridItem G;
+    std::memset(&G, 0, sizeof(G));
+    G.n = nf;
+    item_dims(LK_PROLONG, 0, nf, &G.gx, &G.gy, &G.gz);
+    G.w = std::min(32, G.gy);
+    G.p[0] = uf;
+    G.p[1] = const_cast<double *>(uc);
+    G.p[2] = const_cast<double *>(wc);
+    hipLaunchKernelGGL(k_prolong1, dim3(padded_items(G.gx, G.gy, G.gz, G.w)), dim3(64), 0, st, G);
+    return hipGetLastError();
+}
+
 hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
                            const TailList *T, int blocks, int nu1, int nu2, int nu0, unsigned long long *nc)
 {
@@ -1968,16 +2050,15 @@ int Engine::strip_width(int gy) const
     return std::max(1, std::min(w, gy));
 }
 
-// Block sweeps for a multi-block level of n intervals (4-colour FP64 only;
-// the caller excludes MODE_MIXED).
+// Block sweeps for a multi-block level of n intervals (FP64 only; the caller
+// excludes MODE_MIXED).
 bool Engine::block_level(int n, Mode mode) const
 {
-    if (order_ != MA_COLOR4 || smoother_ == MA_SMOOTHER_COLOR)
+    if (smoother_ == MA_SMOOTHER_COLOR)
         return false;
-    if (smoother_ == MA_SMOOTHER_FUSED || zs_level(n, mode))
+    if ((smoother_ == MA_SMOOTHER_FUSED && n <= kBlockMaxN) || zs_level(n, mode))
         return true;
-    const int lim = block_n_ == 0 ? 64 : block_n_;
-    return n <= lim;
+    return n <= block_limit(order_, block_n_);
 }
 
 // Automatic choice (zsweep_n = 0), from whole-solve timings on MI355X: the
@@ -2325,12 +2406,14 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             const bool zs = zs_level(nmax, mode) ||
                             (smoother_ == MA_SMOOTHER_FUSED && tile_config_ > kZsFirstConfig);
             int cfg;
-            if (zs)
+            if (order_ != MA_COLOR4)   // tile_config names 4-colour shapes
+                cfg = bsweep_pick(order_, nmax, tiles8);
+            else if (zs)
                 cfg = tile_config_ >= kZsFirstConfig + 1 ? tile_config_ - 1 : bsweep_zs_pick(nmax);
             else if (tile_config_ > 0 && tile_config_ <= kZsFirstConfig)
                 cfg = tile_config_ - 1;
             else
-                cfg = bsweep_pick(nmax, tiles8);
+                cfg = bsweep_pick(order_, nmax, tiles8);
             auto has = [&](int i) { return solves_[i].s && multiblock_levels(i) > d; };
             // up: the post-smoothing pairs, whose first z-stream sweep also
             // applies the coarse-grid correction (the solves in it are those
@@ -2346,7 +2429,7 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                             same = (count(i) > k) == (count(i) > k + 1);
                     if (!same)
                         continue;
-                    const bool pro = up && k == 0 && fuse_prolong_ && bsweep_is_zstream(cfg);
+                    const bool pro = up && k == 0 && fuse_prolong_ && bsweep_is_zstream(order_, cfg);
                     if (pro)
                         pro_fused_[d] = 1;
                     out[k] = int(fsoff_.size());
@@ -2363,7 +2446,7 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                             double *u = const_cast<double *>(level_u(i, d, mode));
                             double *t = sv->lv[d].t;
                             FsGrid G;
-                            bsweep_grid(cfg, sv->lv[d].n, half ? t : u, half ? u : t,
+                            bsweep_grid(order_, cfg, sv->lv[d].n, half ? t : u, half ? u : t,
                                         level_F(i, d, mode), op, i, &G);
                             if (pro && half == 0) {
                                 G.cu = sv->lv[d + 1].u;
@@ -2414,22 +2497,14 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                     continue;
                 const ma_solver *sv = solves_[i].s;
                 RrGrid G;
-                std::memset(&G, 0, sizeof(G));
-                G.uf = level_u(i, d, mode);
-                G.F = level_F(i, d, mode);
-                G.wc = sv->lv[d + 1].w;
-                G.uc = sv->lv[d + 1].u;
-                G.bc = sv->lv[d + 1].b;
-                G.n = sv->lv[d].n;
-                G.slot = i;
-                const int tc = (G.n / 2 + 1 + kRrTile - 1) / kRrTile;
-                G.tiles_x = G.tiles_y = G.tiles_z = tc;
-                G.s = double(G.n) * double(G.n);
-                bound += long(tc) * tc * tc;
+                const int tiles = rr_grid(sv->lv[d].n, level_u(i, d, mode), level_F(i, d, mode),
+                                          sv->lv[d + 1].w, sv->lv[d + 1].u, sv->lv[d + 1].b, i,
+                                          &G);
+                bound += tiles;
                 if (!active[i])
                     continue;
                 G.start = start;
-                start += tc * tc * tc;
+                start += tiles;
                 Lr.g[Lr.ngrids++] = G;
             }
             Lr.total = start;
@@ -2568,7 +2643,7 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
                 for (int h = 0; h < 2; ++h) {
                     const int f = pairs[k] + h;
                     if (fsblocks_[f] > 0)
-                        E_HIP(launch_bsweep(stream_, op, fscfg_[f], FL(f), fsblocks_[f], dcount_,
+                        E_HIP(launch_bsweep(stream_, op, order_, fscfg_[f], FL(f), fsblocks_[f], dcount_,
                                             fspro_[f] != 0));
                 }
                 k += 2;

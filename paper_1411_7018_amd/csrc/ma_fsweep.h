@@ -1,31 +1,34 @@
-// One complete 4-colour nonlinear Gauss-Seidel sweep per launch (Section 2:
-// the pointwise update of eqs. 2.7-2.9 applied colour by colour), for many
+// One complete nonlinear Gauss-Seidel sweep per launch (Section 2: the
+// pointwise update of eqs. 2.7-2.9 applied colour by colour), for many
 // grids at once: the block sweep.
 //
-// Colour c = ((i+j) mod 2) + 2 ((i+k) mod 2).  A colour-c node reads only
-// nodes of the three other colours, so a sweep is four phases, each
+// A node reads only nodes of other colours, so a sweep is one phase per colour
+// (4: c = ((i+j) mod 2) + 2 ((i+k) mod 2); 8: the parities of i, j, k), each
 // updating all nodes of one colour at once.  Launched phase by phase, a
-// sweep costs four kernel launches, which on the smaller grids of the
-// V-cycle take longer than the work itself.  The block sweep runs all four
+// sweep costs four or eight kernel launches, which on the smaller grids of the
+// V-cycle take longer than the work itself.  The block sweep runs all
 // phases in one launch:
 //
 // * A workgroup owns a TX x TY x TZ block of output nodes.  It loads the
-//   block with a halo of 4 nodes into LDS (rows de-interleaved by x parity,
+//   block with a halo into LDS (rows de-interleaved by x parity,
 //   so the nodes of one colour in a row are contiguous), and prefetches the
 //   right-hand side of every node it will update into registers.
-// * It applies phase c = 0..3 to the colour-c nodes of the block grown by
-//   3 - c nodes in every direction, with a workgroup barrier after each
-//   phase.  A phase-c value one node outside the grown block of phase c + 1
-//   is never needed, so the grown blocks shrink by one node per phase; the
-//   nodes outside the owned block are recomputed from the same values by
-//   the neighbouring workgroups.
+// * It applies phase c to the colour-c nodes of the block grown by ext(c) in
+//   every direction, with a workgroup barrier after each phase: the nodes
+//   whose values the later phases read, directly or through one another.  With
+//   4 colours each pair of colours meets along every axis, so the grown blocks
+//   shrink by one node per phase (3, 2, 1, 0).  With 8 colours two nodes of
+//   colours c < c' are neighbours only along the axes in whose parity bits c
+//   and c' differ (one or two of them), so ext(c) is per axis the largest
+//   ext(c') + 1 over those c'.  The nodes outside the owned block are
+//   recomputed from the same values by the neighbouring workgroups.
 // * It writes the owned block (and the Dirichlet layer next to it) to
 //   u_out.  The sweep reads u_in and writes u_out (out of place), so halos
 //   read from a neighbouring block are never modified during the launch.
 //
 // The update of a node evaluates the same expressions (hessian3 and the root
 // rule of ma_device.h) on the same values as the colour-phase kernels, so
-// the results are bitwise identical to four colour phases.
+// the results are bitwise identical to the colour phases.
 //
 // Algorithmic bytes per interior node and sweep: read u 8, read F 8,
 // write u 8.  The recomputation costs ALU work, which on the grids this
@@ -34,6 +37,8 @@
 
 #include "ma_device.h"
 #include "ma_internal.h"
+
+#include <type_traits>
 
 namespace mafas {
 
@@ -65,24 +70,43 @@ struct FsList {
 constexpr size_t fs_list_bytes(int ngrids) { return 16 + sizeof(FsGrid) * size_t(ngrids); }
 static_assert(offsetof(FsList, g) == 16, "list header is 16 bytes");
 
-template <int TX, int TY, int TZ>
+// Growth of phase c's block along an axis (0: x, 1: y, 2: z).
+__host__ __device__ constexpr int fs_ext(int order, int c, int axis)
+{
+    if (order == 0)
+        return 3 - c;
+    constexpr int e[8][3] = {{5, 3, 1}, {4, 3, 1}, {3, 2, 1}, {2, 2, 1},
+                             {3, 1, 0}, {2, 1, 0}, {1, 0, 0}, {0, 0, 0}};
+    return e[c][axis];
+}
+
+template <int ORDER, int TX, int TY, int TZ, int NT>
 struct FsShape {
-    static constexpr int H = 4;              // halo loaded around the block
-    static constexpr int LX = TX + 2 * H;    // LDS row length
-    static constexpr int LY = TY + 2 * H;    // LDS rows per plane
-    static constexpr int LZ = TZ + 2 * H;    // LDS planes
+    static constexpr int NC = ORDER == 0 ? 4 : 8;     // phases
+    // halo loaded around the block: the first phase's growth and one node
+    static constexpr int HX = fs_ext(ORDER, 0, 0) + 1, HY = fs_ext(ORDER, 0, 1) + 1,
+                         HZ = fs_ext(ORDER, 0, 2) + 1;
+    static constexpr int LX = TX + 2 * HX;   // LDS row length
+    static constexpr int LY = TY + 2 * HY;   // LDS rows per plane
+    static constexpr int LZ = TZ + 2 * HZ;   // LDS planes
     static constexpr int HW = LX / 2;        // one parity half of a row
     static constexpr int PL = LX * LY;       // doubles per plane
     static constexpr int NL = PL * LZ;       // doubles in LDS
-    // phase c covers (TX/2 + e) columns, TY + 2e rows and (TZ/2 + e) planes
-    // of its colour's sub-lattice, e = 3 - c
-    static constexpr int ncol(int c) { return TX / 2 + 3 - c; }
-    static constexpr int nrow(int c) { return TY + 2 * (3 - c); }
-    static constexpr int npl(int c) { return TZ / 2 + 3 - c; }
+    // phase c covers columns and planes of one parity and (4 colours) all
+    // rows or (8 colours) those of one parity of its grown block
+    static constexpr int ncol(int c) { return TX / 2 + fs_ext(ORDER, c, 0); }
+    static constexpr int nrow(int c)
+    {
+        return ORDER == 0 ? TY + 2 * fs_ext(ORDER, c, 1) : TY / 2 + fs_ext(ORDER, c, 1);
+    }
+    static constexpr int npl(int c) { return TZ / 2 + fs_ext(ORDER, c, 2); }
     static constexpr int count(int c) { return ncol(c) * nrow(c) * npl(c); }
+    // rounds of a workgroup over phase c, and those of the phases before it
+    static constexpr int rounds(int c) { return (count(c) + NT - 1) / NT; }
+    static constexpr int before(int c) { return c == 0 ? 0 : before(c - 1) + rounds(c - 1); }
     static constexpr int SX = TX + 2, SY = TY + 2, SZ = TZ + 2;   // store bound
-    static constexpr size_t lds_bytes() { return size_t(NL) * sizeof(double); }
-    static_assert(TX % 2 == 0 && TZ % 2 == 0, "TX and TZ must be even");
+    static_assert(TX % 2 == 0 && TY % 2 == 0 && TZ % 2 == 0, "block sides must be even");
+    static_assert(LX % 2 == 0, "LDS rows hold two parity halves");
 };
 
 // Workgroup barrier that orders LDS accesses only: global loads issued
@@ -103,16 +127,53 @@ __device__ __forceinline__ void lds_wave_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Block `tile` of grid G by a workgroup of NT threads; su: LDS.  Global
-// offsets are 32-bit: grids up to n = 1289.
-template <int OP, int TX, int TY, int TZ, int NT>
-__device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *__restrict__ su,
-                                            unsigned long long *__restrict__ ncount)
+// Phase C and those after it, the item counts of each a constant.
+template <int C, int NC, typename F>
+__device__ __forceinline__ void fs_phases(F f)
 {
-    using S = FsShape<TX, TY, TZ>;
-    constexpr int LX = S::LX, HW = S::HW, PL = S::PL, H = S::H;
-    constexpr int M0 = (S::count(0) + NT - 1) / NT, M1 = (S::count(1) + NT - 1) / NT;
-    constexpr int M2 = (S::count(2) + NT - 1) / NT, M3 = (S::count(3) + NT - 1) / NT;
+    if constexpr (C < NC) {
+        f(std::integral_constant<int, C>{});
+        fs_phases<C + 1, NC>(f);
+    }
+}
+
+// One step of the standalone Gauss-Seidel iteration: sweep q, u_{q-1} (in) to
+// u_q (out), with the residual norm of u_{q-1} taken from the block in LDS
+// before its first phase, and the stopping test of u_{q-2}.
+//
+// The test of an iterate comes a launch after its sums, and the iterate is
+// still whole then: launch q leaves the sums of squares of u_{q-1}, one per
+// block, in part_out; launch q + 1, which would overwrite u_{q-1}, first adds
+// them up -- every block the same sum in the same order -- and when the sum
+// meets the test (<= thr, or not finite) sets *stop to its number q and
+// stores nothing, like every launch after it (q > *stop).  So a sweep is one launch, and the host looks at the
+// sums once per batch of launches.  Bound by the latency of one block's chain
+// (launch, loads, residual, phases): the sums are loaded with the block and
+// added up with its residual, and the test is taken just before the phases.
+// n = 32, a sweep and its test: 29 us as colour launches, a residual, a
+// reduction and a host round trip, 9.3 us so (9.7 with the sums added up
+// before the block was loaded).
+struct GsStep {
+    const double *part_in;      // sums of squares of u_{q-2} (null: none yet)
+    double *part_out;           // of u_{q-1}
+    double *sum;                // total of part_in (written by block 0)
+    unsigned long long *count;  // uncertified updates of this sweep
+    int *stop;                  // 0, or the launch that stopped
+    int q;                      // this launch, from 1
+    double thr;
+};
+
+// Block `tile` of grid G by a workgroup of NT threads; su: LDS.  Global
+// offsets are 32-bit: grids up to n = 1289.  GS: a step of the Gauss-Seidel
+// iteration A, with sums over `blocks` blocks (waves: NT / 32 doubles of LDS).
+template <int OP, int ORDER, int TX, int TY, int TZ, int NT, bool GS>
+__device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *__restrict__ su,
+                                            unsigned long long *__restrict__ ncount,
+                                            const GsStep *A = nullptr, int blocks = 0,
+                                            double *__restrict__ waves = nullptr)
+{
+    using S = FsShape<ORDER, TX, TY, TZ, NT>;
+    constexpr int LX = S::LX, HW = S::HW, PL = S::PL;
     constexpr int KL = (S::NL + NT - 1) / NT;
     constexpr int KS = (S::SX * S::SY * S::SZ + NT - 1) / NT;
 
@@ -124,55 +185,70 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
     const int tz = rest / G.tiles_y;
     const int x0 = 1 + tx * TX, y0 = 1 + ty * TY, z0 = 1 + tz * TZ;
     const int x1 = min(x0 + TX, n), y1 = min(y0 + TY, n), z1 = min(z0 + TZ, n);
-    const int lx0 = x0 - H, ly0 = y0 - H, lz0 = z0 - H;
+    const int lx0 = x0 - S::HX, ly0 = y0 - S::HY, lz0 = z0 - S::HZ;
     const int sy = n + 1, sz = sy * sy;
     const auto uin = to_global(G.uin);
     const auto uout = to_global(G.uout);
     const auto F = to_global(G.F);
 
-    // Node of item m of phase c: rows j over the grown block, planes k and
-    // columns i of the colour's parities (k = j + c0 + c1, i = j + c0 mod 2).
-    // Returns false when the item lies outside the grid interior.
-    auto node = [&](int c, int item, int &i, int &j, int &k) -> bool {
-        const int e = 3 - c, c0 = c & 1, c1 = c >> 1;
-        const int nc = TX / 2 + e, np = TZ / 2 + e;
+    // Node of item m of phase c over the grown block: planes and columns of
+    // the colour's parities (4 colours: k = j + c0 + c1, i = j + c0 mod 2) and
+    // rows, all or those of its parity.  Returns false when the item lies
+    // outside the grid interior.
+    auto node = [&](auto cc, int item, int &i, int &j, int &k) -> bool {
+        constexpr int c = decltype(cc)::value;
+        constexpr int ex = fs_ext(ORDER, c, 0), ey = fs_ext(ORDER, c, 1), ez = fs_ext(ORDER, c, 2);
+        constexpr int nc = S::ncol(c);
         const int q = item % nc;
         const int r2 = item / nc;
-        const int kk = r2 % np;
-        const int jj = r2 / np;
-        j = y0 - e + jj;
-        const int pk = (j + c0 + c1) & 1, pi = (j + c0) & 1;
-        k = (z0 - e) + (((z0 - e) ^ pk) & 1) + 2 * kk;
-        i = (x0 - e) + (((x0 - e) ^ pi) & 1) + 2 * q;
-        return item < S::count(c) && i >= max(1, x0 - e) && i <= min(n - 1, x1 - 1 + e) &&
-               j >= max(1, y0 - e) && j <= min(n - 1, y1 - 1 + e) && k >= max(1, z0 - e) &&
-               k <= min(n - 1, z1 - 1 + e);
+        int pi, pk;
+        if (ORDER == 0) {
+            constexpr int c0 = c & 1, c1 = c >> 1, np = S::npl(c);
+            const int kk = r2 % np;
+            j = y0 - ey + r2 / np;
+            pk = (j + c0 + c1) & 1;
+            pi = (j + c0) & 1;
+            k = (z0 - ez) + (((z0 - ez) ^ pk) & 1) + 2 * kk;
+        } else {
+            constexpr int nr = S::nrow(c);
+            pi = c & 1;
+            pk = c >> 2;
+            j = (y0 - ey) + (((y0 - ey) ^ (c >> 1)) & 1) + 2 * (r2 % nr);
+            k = (z0 - ez) + (((z0 - ez) ^ pk) & 1) + 2 * (r2 / nr);
+        }
+        i = (x0 - ex) + (((x0 - ex) ^ pi) & 1) + 2 * q;
+        return item < S::count(c) && i >= max(1, x0 - ex) && i <= min(n - 1, x1 - 1 + ex) &&
+               j >= max(1, y0 - ey) && j <= min(n - 1, y1 - 1 + ey) && k >= max(1, z0 - ez) &&
+               k <= min(n - 1, z1 - 1 + ez);
     };
     auto lds_off = [&](int i, int j, int k) {
         const int lx = i - lx0;
         return (k - lz0) * PL + (j - ly0) * LX + (lx & 1) * HW + (lx >> 1);
     };
 
+    // ---- the sums of the iterate before u_in
+    int stop = 0;
+    double before = 0.0;
+    if (GS) {
+        stop = *A->stop;   // this launch's own value is not a stop yet
+        stop = stop != 0 && stop < A->q;
+        if (A->part_in)
+            for (int q = tid; q < blocks; q += NT)
+                before += A->part_in[q];
+    }
+
     // ---- right-hand sides of every item of this lane, in flight during
     // the block load (a lane without a node reads node 0 and discards it)
-    double f0[M0], f1[M1], f2[M2], f3[M3];
-    auto fetch = [&](int c, int m) {
-        int i, j, k;
-        const bool ok = node(c, tid + m * NT, i, j, k);
-        return F[ok ? i + sy * j + sz * k : 0];
-    };
+    double f[S::before(S::NC)];
+    fs_phases<0, S::NC>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
 #pragma unroll
-    for (int m = 0; m < M0; ++m)
-        f0[m] = fetch(0, m);
-#pragma unroll
-    for (int m = 0; m < M1; ++m)
-        f1[m] = fetch(1, m);
-#pragma unroll
-    for (int m = 0; m < M2; ++m)
-        f2[m] = fetch(2, m);
-#pragma unroll
-    for (int m = 0; m < M3; ++m)
-        f3[m] = fetch(3, m);
+        for (int m = 0; m < S::rounds(c); ++m) {
+            int i, j, k;
+            const bool ok = node(cc, tid + m * NT, i, j, k);
+            f[S::before(c) + m] = F[ok ? i + sy * j + sz * k : 0];
+        }
+    });
 
     // ---- the block and its halo into LDS (0 outside the grid): every load
     // of the lane first, then the LDS writes, so all of them are in flight
@@ -199,13 +275,8 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
     }
     lds_barrier();
 
-    // ---- the four phases
-    auto update = [&](int c, int m, double f) {
-        int i, j, k;
-        if (!node(c, tid + m * NT, i, j, k))
-            return;
-        const int off = lds_off(i, j, k);
-        double *C = su + off;
+    auto value = [&](int i, int j, int k, double fv, bool resid, bool &nc) {
+        double *C = su + lds_off(i, j, k);
         const double *D = C - PL;
         const double *U = C + PL;
         const int odd = (i - lx0) & 1;
@@ -213,32 +284,73 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
         const int xm = odd ? -HW : HW - 1;
         if (OP == OP_MA) {
             const Hess h = hessian3(D, C, U, xp, xm, LX, G.s, G.s4);
+            return resid ? fv - det3(h) : ma_point_update(h, C[0], fv, G.hk, nc);
+        }
+        const double lap = laplacian3(D, C, U, xp, xm, LX, G.s);
+        return resid ? fv - lap : lap_point_update(lap, C[0], fv, G.hk);
+    };
+
+    // ---- the residual of u_in on the owned nodes, and the test of the iterate
+    // before it
+    if (GS) {
+        if (stop)
+            return;
+        constexpr int KN = (TX * TY * TZ + NT - 1) / NT;
+        double acc = 0.0;
+#pragma unroll
+        for (int m = 0; m < KN; ++m) {
+            const int el = tid + m * NT;
+            const int i = x0 + el % TX, r = el / TX, j = y0 + r % TY, k = z0 + r / TY;
+            if (el < TX * TY * TZ && i < x1 && j < y1 && k < z1) {
+                bool nc = false;
+                const double rv = value(i, j, k, F[i + sy * j + sz * k], true, nc);
+                acc += rv * rv;
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            acc += __shfl_down(acc, off, 64);
+            before += __shfl_down(before, off, 64);
+        }
+        if ((tid & 63) == 0) {
+            waves[tid >> 6] = acc;
+            waves[NT / 64 + (tid >> 6)] = before;
+        }
+        lds_barrier();
+        double now = 0.0, prev = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            now += waves[w];
+            prev += waves[NT / 64 + w];
+        }
+        const bool done = A->part_in && (prev <= A->thr || !isfinite(prev));
+        if (tid == 0) {
+            A->part_out[tile] = now;
+            if (A->part_in && blockIdx.x == 0) {
+                *A->sum = prev;
+                if (done)
+                    *A->stop = A->q;
+            }
+        }
+        if (done)
+            return;
+    }
+
+    // ---- the phases
+    fs_phases<0, S::NC>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
+#pragma unroll
+        for (int m = 0; m < S::rounds(c); ++m) {
+            int i, j, k;
+            if (!node(cc, tid + m * NT, i, j, k))
+                continue;
             bool nc = false;
-            C[0] = ma_point_update(h, C[0], f, G.hk, nc);
+            su[lds_off(i, j, k)] = value(i, j, k, f[S::before(c) + m], false, nc);
             // recomputed halo nodes are counted by their own block
             if (nc && ncount && i >= x0 && i < x1 && j >= y0 && j < y1 && k >= z0 && k < z1)
                 atomicAdd(ncount + G.slot, 1ull);
-        } else {
-            const double lap = laplacian3(D, C, U, xp, xm, LX, G.s);
-            C[0] = lap_point_update(lap, C[0], f, G.hk);
         }
-    };
-#pragma unroll
-    for (int m = 0; m < M0; ++m)
-        update(0, m, f0[m]);
-    lds_barrier();
-#pragma unroll
-    for (int m = 0; m < M1; ++m)
-        update(1, m, f1[m]);
-    lds_barrier();
-#pragma unroll
-    for (int m = 0; m < M2; ++m)
-        update(2, m, f2[m]);
-    lds_barrier();
-#pragma unroll
-    for (int m = 0; m < M3; ++m)
-        update(3, m, f3[m]);
-    lds_barrier();
+        lds_barrier();
+    });
 
     // ---- the owned block and the Dirichlet layer next to it to u_out
     const int xs0 = x0 == 1 ? 0 : x0, xs1 = x1 == n ? n + 1 : x1;
@@ -258,11 +370,11 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
 // Blocks are dispatched round-robin over the 8 XCDs; tile_of_block gives
 // each XCD a contiguous range of tiles, so tiles that share halos share an
 // L2.  One tile per workgroup.
-template <int OP, int TX, int TY, int TZ, int NT>
+template <int OP, int ORDER, int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_bsweep(const FsList *__restrict__ L,
                                                 unsigned long long *__restrict__ ncount)
 {
-    __shared__ double su[FsShape<TX, TY, TZ>::NL];
+    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
     const int total = L->total;
     const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
     if (t >= total)
@@ -274,16 +386,26 @@ __global__ __launch_bounds__(NT) void k_bsweep(const FsList *__restrict__ L,
     const FsGrid G = L->g[g];   // the whole descriptor in one set of loads
     if ((L->stopped >> G.slot) & 1ull)
         return;
-    bsweep_tile<OP, TX, TY, TZ, NT>(G, t - G.start, su, ncount);
+    bsweep_tile<OP, ORDER, TX, TY, TZ, NT, false>(G, t - G.start, su, ncount);
 }
 
 // The same for one grid passed by value (gridDim.x = its tile count).
-template <int OP, int TX, int TY, int TZ, int NT>
+template <int OP, int ORDER, int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_bsweep1(FsGrid G, unsigned long long *__restrict__ ncount)
 {
-    __shared__ double su[FsShape<TX, TY, TZ>::NL];
+    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
     const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
-    bsweep_tile<OP, TX, TY, TZ, NT>(G, t, su, ncount);
+    bsweep_tile<OP, ORDER, TX, TY, TZ, NT, false>(G, t, su, ncount);
+}
+
+template <int ORDER, int TX, int TY, int TZ, int NT>
+__global__ __launch_bounds__(NT) void k_gs_step(FsGrid G, GsStep A)
+{
+    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
+    __shared__ double waves[NT / 32];
+    const int blocks = int(gridDim.x);
+    bsweep_tile<OP_MA, ORDER, TX, TY, TZ, NT, true>(G, tile_of_block(int(blockIdx.x), blocks), su,
+                                                    A.count, &A, blocks, waves);
 }
 
 } // namespace mafas

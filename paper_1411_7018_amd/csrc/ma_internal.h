@@ -24,21 +24,29 @@ size_t residual_partials(int n);
 hipError_t launch_sweep_color(hipStream_t st, int op, int order, int n, double *u,
                               const double *F, unsigned long long *nonconvex);
 
-// The block sweep (ma_fsweep.h): one sweep, all four colour phases in a
-// single launch reading u_in and writing u_out (4-colour ordering only);
-// u_out receives the Dirichlet layer too.  cfg: block shape index (< 0:
-// automatic for n).  Bitwise equal to launch_sweep_color.
-hipError_t launch_bsweep_one(hipStream_t st, int op, int cfg, int n, const double *u_in,
-                             double *u_out, const double *F, unsigned long long *nonconvex);
+// The block sweep (ma_fsweep.h): one sweep, all colour phases in a single
+// launch reading u_in and writing u_out; u_out receives the Dirichlet layer
+// too.  cfg: shape index of that ordering (< 0: automatic for n; the z-stream
+// shapes of the 4-colour ordering among them).  Bitwise equal to
+// launch_sweep_color.
+hipError_t launch_bsweep_one(hipStream_t st, int op, int order, int cfg, int n,
+                             const double *u_in, double *u_out, const double *F,
+                             unsigned long long *nonconvex);
 int bsweep_num_configs();
 // Automatic block shape for grids of up to n intervals whose 8^3 tiles number
 // tiles8 in all.
-int bsweep_pick(int n, long tiles8);
+int bsweep_pick(int order, int n, long tiles8);
+// One step of the standalone Gauss-Seidel iteration (GsStep in ma_fsweep.h);
+// part_in / part_out hold gs_blocks doubles.
+int gs_blocks(int order, int n);
+hipError_t launch_gs_step(hipStream_t st, int order, int n, const double *u_in, double *u_out,
+                          const double *F, const double *part_in, double *part_out, double *sum,
+                          unsigned long long *count, int *stop, int q, double thr);
 // automatic z-stream shape (config index) of an n grid
 int bsweep_zs_pick(int n);
 
 // --- residual and norm ----------------------------------------------------
-// r = F - S(u) (interior; 0 on the boundary; r may be null) and per-block sums
+// r = F - S(u) (0 on the boundary, written; r may be null) and per-block sums
 // of r^2 into partials[0..residual_partials(n)).
 hipError_t launch_residual(hipStream_t st, int op, int n, const double *u, const double *F,
                            double *r, double *partials);
@@ -46,10 +54,11 @@ hipError_t launch_residual(hipStream_t st, int op, int n, const double *u, const
 hipError_t launch_reduce(hipStream_t st, const double *partials, size_t count, double *out);
 
 // --- transfers --------------------------------------------------------------
-// FAS restriction nf -> nf/2: wc = uc = injection of uf; bc = S_H(wc) + I rf.
-// rmode 0: full weighting, 1: half-weighting.
-hipError_t launch_restrict(hipStream_t st, int op, int rmode, int nf, const double *uf,
-                           const double *rf, double *wc, double *uc, double *bc);
+// Residual and FAS restriction nf -> nf/2 in one launch: wc = uc = injection
+// of uf; bc = S_H(wc) + I (F - S(uf)).  rmode 0: full weighting, 1:
+// half-weighting.
+hipError_t launch_restrict(hipStream_t st, int rmode, int nf, const double *uf, const double *F,
+                           double *wc, double *uc, double *bc);
 // uf += trilinear(uc - wc) at fine interior nodes.
 hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc,
                           const double *wc);

@@ -4,6 +4,7 @@
 #include "ma.h"
 #include "ma_internal.h"
 
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -53,9 +54,20 @@ inline long fs_colour_count(int n)
     const long gx = ((n + 1) / 2 + 63) / 64, gy = n - 1, gz = n / 2;
     return gx * gy * gz * 64;
 }
+// largest n of a block sweep (its element offsets are 32-bit)
+constexpr int kBlockMaxN = 1289;
 // Largest n whose sweeps MA_SMOOTHER_AUTO runs as block sweeps (-1: none).
-inline int block_limit(const ma_params &p) { return p.block_n == 0 ? 64 : p.block_n; }
+// A sweep of Monge-Ampere, one launch against the colour launches, in us: 4
+// colours, n = 64: 13 / 14, 96: 26 / 22, 128: 47 / 33; 8 colours (a block
+// recomputes 2.2-2.7 x its updates, with 4 colours 2.9 x, and replaces eight
+// launches), n = 32: 9 / 20, 64: 15 / 23, 80: 17 / 26, 96: 33 / 30, 128: 60 / 41.
+inline int block_limit(int order, int block_n)
+{
+    return block_n == 0 ? (order == MA_COLOR4 ? 64 : 88) : block_n < kBlockMaxN ? block_n : kBlockMaxN;
+}
 size_t mixed_bytes(const ma_params *p);
+// launches of the Gauss-Seidel iteration between looks at its sums
+constexpr int kGsBatch = 32;
 
 hipError_t launch_fill(hipStream_t st, size_t count, double v, double *dst);
 hipError_t launch_fill_u64(hipStream_t st, size_t count, unsigned long long v,
@@ -80,6 +92,7 @@ struct ma_solver {
     long fs_cs = 0;
     double *partials = nullptr;           // norm partials of the single-grid kernels
     double *dsum = nullptr;
+    double *gs_work = nullptr;            // sums and counts of gs_steps (small grids)
     unsigned long long *dcount = nullptr; // counter of the single-grid kernels
     double *hpin = nullptr;               // pinned host scalars
     unsigned long long *hpin_u64 = nullptr;
@@ -97,11 +110,14 @@ struct ma_solver {
     ma_status fail(ma_status st, const std::string &msg);
     ma_status alloc(double **q, size_t count);
     ma_status allocate();
-    bool use_block(int l) const;
+    bool sweep_shape(int n, int *cfg) const;
     int rmode() const;
     // single-grid kernels behind the component entry points
     ma_status smooth(int l, double *u, const double *F, int count, int op);
     ma_status finish_norm(int n, double *l2);
+    ma_status read_norm(int n, double *l2);
+    ma_status gs_steps(double *u, const double *F, int max_sweeps, double thr,
+                       const std::function<bool(int, double)> &test, long long *nonconvex);
     ma_status own_engine(mafas::Engine **out, double *u, const double *f);
     ma_solver *view(int l);
     // One FMG-FAS iteration (Algorithm 2) on u, whose interior is not read;

@@ -8,10 +8,13 @@
 #include "ma_internal.h"
 #include "ma_runtime.h"
 
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace mafas;
@@ -91,6 +94,17 @@ bool valid_params(const ma_params *p, std::string &why)
     return true;
 }
 
+// Workspace of gs_steps (none: gs_solve sweeps and tests one by one).  A
+// sweep with its test, gs_steps against one by one, in us: 4 colours, n = 32:
+// 12 / 33, 64: 17 / 37, 96: 38 / 49, 128: 67 / 68; 8 colours, n = 32: 12 / 53,
+// 64: 19 / 53, 96: 71 / 58.
+size_t gs_doubles(const ma_params *p)
+{
+    if (p->n > (p->order == MA_COLOR4 ? 96 : 80) || p->smoother == MA_SMOOTHER_COLOR)
+        return 0;
+    return 2 * size_t(gs_blocks(p->order, p->n)) + 4 * kGsBatch + 1;
+}
+
 } // namespace
 
 // the message ma_last_error(NULL) returns, for calls that have no solver
@@ -121,7 +135,7 @@ size_t mafas::hierarchy_bytes(const ma_params *p)
     }
     if (p->order == MA_COLOR4 && p->precision == MA_FP64 && p->n >= 2)
         b += size_t(4 * fs_colour_count(p->n)) * sizeof(double);
-    b += residual_partials(p->n) * sizeof(double);
+    b += (residual_partials(p->n) + gs_doubles(p)) * sizeof(double);
     const size_t rows = size_t((p->n - 1 + 63) / 64) * size_t(p->n - 1) * size_t(p->n - 1);
     b += rows * sizeof(double) + (64 << 10) + 4096;
     if (p->precision == MA_MIXED)
@@ -310,8 +324,6 @@ ma_status ma_residual(ma_solver *s, const double *u, const double *f, double *r_
         return MA_ERR_ARG;
     if (!u || !f)
         return s->fail(MA_ERR_ARG, "u and f must be device pointers");
-    if (r_or_null)
-        MA_HIP(s, launch_fill(s->stream, npts(s->p.n), 0.0, r_or_null));
     MA_HIP(s, launch_residual(s->stream, OP_MA, s->p.n, u, f, r_or_null, s->partials));
     if (l2_host) {
         double l2;
@@ -347,9 +359,7 @@ ma_status ma_restrict(ma_solver *s, const double *u, const double *f, double *w_
     if (s->lv.size() < 2)
         return s->fail(MA_ERR_ARG, "n must be even and >= 4 for a coarser level");
     const int n = s->p.n;
-    MA_HIP(s, launch_residual(s->stream, OP_MA, n, u, f, s->lv[0].r, s->partials));
-    MA_HIP(s, launch_restrict(s->stream, OP_MA, s->rmode(), n, u, s->lv[0].r, w_c, s->lv[1].u,
-                              b_c));
+    MA_HIP(s, launch_restrict(s->stream, s->rmode(), n, u, f, w_c, s->lv[1].u, b_c));
     return MA_OK;
 }
 
@@ -383,38 +393,43 @@ ma_status ma_gs_solve(ma_solver *s, double *u, const double *f, double tol, int 
     };
     MA_TRY(norm(&r.res0));
     r.res = r.res0;
-    MA_HIP(s, launch_fill_u64(s->stream, 1, 0ull, s->dcount));
     ma_status st = MA_ERR_NOT_CONVERGED;
+    // the stopping test after sweep q of residual res; true: stop
+    auto test = [&](int q, double res) {
+        r.cycles = q;
+        r.res = res;
+        if (q <= 64)
+            r.history[q - 1] = res;
+        if (!std::isfinite(res))
+            st = MA_ERR_NONFINITE;
+        else if (res <= target * r.res0)
+            st = MA_OK;
+        return st != MA_ERR_NOT_CONVERGED;
+    };
     if (!std::isfinite(r.res0)) {
         st = MA_ERR_NONFINITE;
     } else if (r.res0 == 0.0) {
         st = MA_OK;
+    } else if (s->gs_work) {
+        MA_TRY(s->gs_steps(u, f, max_sweeps, sum_threshold(target * r.res0, n), test, &r.nonconvex));
     } else {
-        const double in = interior(n);
-        while (r.cycles < max_sweeps) {
+        MA_HIP(s, launch_fill_u64(s->stream, 1, 0ull, s->dcount));
+        for (int q = 1; q <= max_sweeps; ++q) {
             MA_TRY(s->smooth(0, u, f, 1, OP_MA));
-            r.cycles += 1;
-            r.point_updates += in;
-            r.alg_bytes += 24.0 * in + 16.0 * in;   // sweep + residual check
-            MA_TRY(norm(&r.res));
-            if (r.cycles <= 64)
-                r.history[r.cycles - 1] = r.res;
-            if (!std::isfinite(r.res)) {
-                st = MA_ERR_NONFINITE;
+            double res;
+            MA_TRY(norm(&res));
+            if (test(q, res))
                 break;
-            }
-            if (r.res <= target * r.res0) {
-                st = MA_OK;
-                break;
-            }
         }
+        MA_HIP(s, hipMemcpyAsync(s->hpin_u64, s->dcount, sizeof(unsigned long long),
+                                 hipMemcpyDeviceToHost, s->stream));
+        MA_HIP(s, hipStreamSynchronize(s->stream));
+        r.nonconvex = (long long)s->hpin_u64[0];
     }
+    r.point_updates = double(r.cycles) * interior(n);
+    r.alg_bytes = 40.0 * r.point_updates;   // sweep 24, residual check 16
     r.rel_res = r.res0 > 0.0 ? r.res / r.res0 : 0.0;
     r.converged = st == MA_OK;
-    MA_HIP(s, hipMemcpyAsync(s->hpin_u64, s->dcount, sizeof(unsigned long long),
-                             hipMemcpyDeviceToHost, s->stream));
-    MA_HIP(s, hipStreamSynchronize(s->stream));
-    r.nonconvex = (long long)s->hpin_u64[0];
     r.seconds = now_seconds() - t0;
     if (rep)
         *rep = r;
@@ -534,14 +549,15 @@ ma_status ma_solver::allocate()
     }
     MA_TRY(alloc(&partials, residual_partials(p.n)));
     MA_TRY(alloc(&dsum, 4));
+    MA_TRY(alloc(&gs_work, gs_doubles(&p)));
     {
         const hipError_t e = hipMalloc(reinterpret_cast<void **>(&dcount), 64);
         if (e != hipSuccess)
             return fail(MA_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
         owned.push_back(reinterpret_cast<double *>(dcount));
     }
-    if (hipHostMalloc(reinterpret_cast<void **>(&hpin), 4 * sizeof(double)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void **>(&hpin_u64), 4 * sizeof(unsigned long long)) !=
+    if (hipHostMalloc(reinterpret_cast<void **>(&hpin), 2 * kGsBatch * sizeof(double)) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&hpin_u64), 2 * kGsBatch * sizeof(unsigned long long)) !=
             hipSuccess)
         return fail(MA_ERR_OOM, "hipHostMalloc failed");
     if (p.precision == MA_MIXED)
@@ -552,35 +568,120 @@ ma_status ma_solver::allocate()
     return MA_OK;
 }
 
-// Block sweeps (4-colour FP64 sweeps of level l in one launch each): every
-// level with MA_SMOOTHER_FUSED, levels with coarse_n < n <= block_n with
-// MA_SMOOTHER_AUTO.
-bool ma_solver::use_block(int l) const
-{
-    if (p.order != MA_COLOR4 || p.smoother == MA_SMOOTHER_COLOR)
-        return false;
-    if (p.smoother == MA_SMOOTHER_FUSED)
-        return true;
-    const int n = lv[l].n;
-    return n <= block_limit(p) && n > p.coarse_n;
-}
-
 int ma_solver::rmode() const { return p.restriction == MA_RESTRICT_HALF ? 1 : 0; }
 
-// count single-grid sweeps of op on level l; the result ends in u.
+// Shape (launch_bsweep_one) of single-grid sweeps of an n grid, -1 for the
+// automatic block shape; false: one launch per colour phase.  One launch per
+// sweep where the engine's levels take it: block sweeps up to block_limit
+// and, with 4 colours, z-stream sweeps from zsweep_n on; in between the colour
+// phases are faster.
+bool ma_solver::sweep_shape(int n, int *cfg) const
+{
+    *cfg = -1;
+    if (p.smoother == MA_SMOOTHER_COLOR)
+        return false;
+    if (p.smoother == MA_SMOOTHER_FUSED && n <= kBlockMaxN) {
+        if (p.order == MA_COLOR4)
+            *cfg = p.tile_config - 1;
+        return true;
+    }
+    const int zn = p.zsweep_n != 0 ? p.zsweep_n : kZsweepAuto;
+    if (p.order == MA_COLOR4 && zn > 0 && n >= zn) {
+        *cfg = p.tile_config > kZsFirstConfig ? p.tile_config - 1 : bsweep_zs_pick(n);
+        return true;
+    }
+    if (p.order == MA_COLOR4 && p.tile_config > 0 && p.tile_config <= kZsFirstConfig)
+        *cfg = p.tile_config - 1;
+    return n <= block_limit(p.order, p.block_n);
+}
+
+// count single-grid sweeps of op on level l; the result ends in u: one-launch
+// sweeps go u -> t -> u, and an odd last one is copied back.
 ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op)
 {
     const int n = lv[l].n;
-    int done = 0;
-    if (use_block(l) && count >= 2) {
-        double *t = lv[l].t;
-        for (; done + 2 <= count; done += 2) {
-            MA_HIP(this, launch_bsweep_one(stream, op, p.tile_config - 1, n, u, t, F, dcount));
-            MA_HIP(this, launch_bsweep_one(stream, op, p.tile_config - 1, n, t, u, F, dcount));
+    int cfg;
+    if (!sweep_shape(n, &cfg)) {
+        for (int k = 0; k < count; ++k)
+            MA_HIP(this, launch_sweep_color(stream, op, p.order, n, u, F, dcount));
+        return MA_OK;
+    }
+    double *a = u, *b = lv[l].t;
+    for (int k = 0; k < count; ++k) {
+        MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg, n, a, b, F, dcount));
+        std::swap(a, b);
+    }
+    if (a != u)
+        MA_HIP(this, launch_copy(stream, npts(n), a, u));
+    return MA_OK;
+}
+
+// The standalone Gauss-Seidel iteration on u by launches of k_gs_step (one
+// sweep each, GsStep in ma_fsweep.h), kGsBatch of them between looks at the
+// sums.  Launch q sweeps iterate q - 1 (in u when q is odd, else in t) into
+// iterate q and tests iterate q - 2.  test(q, residual) is the host's test of
+// iterate q, the same on the same sum (thr: sum_threshold), so both stop at
+// the same iterate; *nonconvex counts the sweeps up to it.
+ma_status ma_solver::gs_steps(double *u, const double *F, int max_sweeps, double thr,
+                              const std::function<bool(int, double)> &test, long long *nonconvex)
+{
+    constexpr int B = kGsBatch, R = 2 * kGsBatch;   // ring of sums and counts
+    const int n = p.n, blocks = gs_blocks(p.order, n);
+    const double h = 1.0 / double(n);
+    double *part[2] = {gs_work, gs_work + blocks}, *sums = gs_work + 2 * blocks;
+    unsigned long long *counts = reinterpret_cast<unsigned long long *>(sums + R);
+    int *stop = reinterpret_cast<int *>(sums + 2 * R);
+    double *buf[2] = {u, lv[0].t};   // iterate q is in buf[q & 1]
+    MA_HIP(this, launch_fill(stream, 1, 0.0, sums + 2 * R));
+    *nonconvex = 0;
+    int launched = 0, tested = 0;   // sweeps launched, iterates tested
+    bool stopped = false;
+    std::vector<double> hs(R);
+    std::vector<unsigned long long> hc(R);
+    auto read = [&]() -> ma_status {
+        MA_HIP(this, hipMemcpyAsync(hpin, sums, R * sizeof(double), hipMemcpyDeviceToHost, stream));
+        MA_HIP(this, hipMemcpyAsync(hpin_u64, counts, R * sizeof(unsigned long long),
+                                    hipMemcpyDeviceToHost, stream));
+        MA_HIP(this, hipStreamSynchronize(stream));
+        std::copy(hpin, hpin + R, hs.begin());
+        std::copy(hpin_u64, hpin_u64 + R, hc.begin());
+        return MA_OK;
+    };
+    while (!stopped && launched < max_sweeps) {
+        const int m = std::min(B, max_sweeps - launched);
+        MA_HIP(this, launch_fill_u64(stream, B, 0ull, counts + launched % R));
+        for (int q = launched + 1; q <= launched + m; ++q) {
+            // iterate 0 is not tested: at least one sweep is done
+            const double *in = q >= 3 ? part[q & 1] : nullptr;
+            MA_HIP(this, launch_gs_step(stream, p.order, n, buf[(q - 1) & 1], buf[q & 1], F, in,
+                                        part[1 - (q & 1)], sums + (q - 1) % R, counts + (q - 1) % R,
+                                        stop, q, thr));
+        }
+        launched += m;
+        MA_TRY(read());
+        while (!stopped && tested < launched - 2) {
+            ++tested;
+            *nonconvex += (long long)hc[(tested - 1) % R];
+            stopped = test(tested, std::sqrt(hs[(tested + 1) % R] * h * h * h));
         }
     }
-    for (; done < count; ++done)
-        MA_HIP(this, launch_sweep_color(stream, op, p.order, n, u, F, dcount));
+    // at max_sweeps, the last two iterates: the block sums of one are there,
+    // not added up; the other's residual is still to be taken
+    while (!stopped && tested < launched) {
+        ++tested;
+        double res;
+        if (tested < launched) {
+            MA_HIP(this, launch_reduce(stream, part[tested & 1], blocks, dsum));
+            MA_TRY(read_norm(n, &res));
+        } else {
+            MA_HIP(this, launch_residual(stream, OP_MA, n, buf[tested & 1], F, nullptr, partials));
+            MA_TRY(finish_norm(n, &res));
+        }
+        *nonconvex += (long long)hc[(tested - 1) % R];
+        stopped = test(tested, res);
+    }
+    if (buf[tested & 1] != u)
+        MA_HIP(this, launch_copy(stream, npts(n), buf[tested & 1], u));
     return MA_OK;
 }
 
@@ -588,6 +689,12 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
 ma_status ma_solver::finish_norm(int n, double *l2)
 {
     MA_HIP(this, launch_reduce(stream, partials, residual_partials(n), dsum));
+    return read_norm(n, l2);
+}
+
+// the same of a sum in dsum
+ma_status ma_solver::read_norm(int n, double *l2)
+{
     MA_HIP(this, hipMemcpyAsync(hpin, dsum, sizeof(double), hipMemcpyDeviceToHost, stream));
     MA_HIP(this, hipStreamSynchronize(stream));
     const double h = 1.0 / double(n);

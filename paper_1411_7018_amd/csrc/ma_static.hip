@@ -23,12 +23,12 @@ namespace mafas {
 
 namespace {
 
-// Largest grid: the partials of n = MA_NOALLOC_MAX_N (8 x 128 x 511 blocks)
-// plus the reduced sum.
+// Largest grid: the partials of n = MA_NOALLOC_MAX_N (one per block of 64 x 4
+// columns x 8 planes) plus the reduced sum.
 constexpr int kMaxN = MA_NOALLOC_MAX_N;
 constexpr size_t kScratchDoubles = 524288;   // 4 MiB per device
-static_assert(kScratchDoubles >= 1 + (kMaxN - 1 + 63) / 64 * ((kMaxN - 1 + 3) / 4) *
-                                         size_t(kMaxN - 1),
+static_assert(kScratchDoubles >= 1 + (kMaxN + 64) / 64 * ((kMaxN + 4) / 4) *
+                                         size_t((kMaxN + 8) / 8),
               "scratch holds the partials of the largest grid");
 
 static __device__ __align__(256) double scratch[kScratchDoubles];
@@ -95,11 +95,6 @@ extern "C" ma_status ma_residual_noalloc(int n, const double *u, const double *f
     double *sum = sp;
     double *partials = sp + 1;
     const size_t cnt = residual_partials(n);
-    if (r_or_null) {
-        const size_t pts = size_t(n + 1) * size_t(n + 1) * size_t(n + 1);
-        if ((e = launch_fill(st, pts, 0.0, r_or_null)) != hipSuccess)
-            return fail(MA_ERR_DEVICE, hipGetErrorString(e));
-    }
     if ((e = launch_residual(st, OP_MA, n, u, f, r_or_null, partials)) != hipSuccess ||
         (e = launch_reduce(st, partials, cnt, sum)) != hipSuccess)
         return fail(MA_ERR_DEVICE, hipGetErrorString(e));
