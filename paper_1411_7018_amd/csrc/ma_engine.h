@@ -34,6 +34,7 @@ constexpr int kMaxTail = 6;            // levels per solve inside that kernel
 constexpr int kTailLdsThreads = 1024;  // threads of its LDS form
 constexpr int kTailFastN = 16;         // largest level of its 4-colour kernel
 constexpr int kTailLdsDoubles = 19456; // LDS of that form (152 KiB): levels 16, 8, 4, 2
+constexpr int kTailMixedFloats = 40832; // and of the mixed form (159.5 KiB), the same levels with H
 
 // One grid of one solve inside a batched launch.  Every work item is one
 // wavefront handling 64 nodes of one x-row (bx, by, bz) of a gx x gy x gz
@@ -51,7 +52,7 @@ struct GridItem {
     int pbase;     // first partial-sum slot (norm lists): gx*gy*gz slots
     double s;      // 1/h^2 of this grid
     double hk;     // h^2/2 (nonlinear update) or 1/(6s) (linear update)
-    void *p[6];    // operands, meaning set by the list kind
+    void *p[8];    // operands, meaning set by the list kind
 };
 
 // Work items of a grid, idle padding of the last y-strip included.
@@ -102,10 +103,33 @@ struct RrList {
 constexpr size_t rr_list_bytes(int ngrids) { return 16 + sizeof(RrGrid) * size_t(ngrids); }
 static_assert(offsetof(RrList, g) == 16, "list header is 16 bytes");
 
+// Fused residual and restriction of the mixed inner problem (k_mrrestrict).
+using Float2 = float __attribute__((ext_vector_type(2)));
+struct MrGrid {
+    const float *df, *bf;
+    const double *Uf;
+    float *wc, *dc, *bc;
+    double *Uc;
+    Float2 *Hc[3];  // H of a coarse level with row kernels (its b in split rows), else null
+    int n;
+    int tiles;      // per side in x and y
+    int start;      // first tile of this grid in the launch
+    int slot;       // solve index
+};
+struct MrList {
+    int ngrids;
+    int total;
+    unsigned long long stopped;
+    MrGrid g[kMaxGrids];
+};
+constexpr size_t mr_list_bytes(int ngrids) { return 16 + sizeof(MrGrid) * size_t(ngrids); }
+static_assert(offsetof(MrList, g) == 16, "list header is 16 bytes");
+
 // LDS form: offsets (in doubles) of each level's u, b, w, r in LDS, -1
 // where the level has no such array (w above the first level, r on the
 // coarsest).
-// md: the factor that divides by n + 1 (div18 in ma_engine.hip).
+// md: the factor that divides by n + 1 (div18 in ma_engine.hip).  Mixed inner
+// problem: u is delta's, offsets are in floats, md is H's (k_tail_mixed).
 struct TailLds {
     int u[kMaxTail], b[kMaxTail], w[kMaxTail], r[kMaxTail];
     unsigned md[kMaxTail];
@@ -132,14 +156,13 @@ enum ListKind {
     LK_RESTRICT,   // p: uf, rf, wc, uc, bc          items: coarse rows (n = fine n)
     LK_PROLONG,    // p: uf, uc, wc                  items: fine interior rows
     LK_NORM,       // p: u, F, partials              items: interior rows x plane chunks
-    LK_MSWEEP,     // p: d, b, U                     items: rows of one colour
+    LK_MSWEEP,     // p: d, b, U, H[3]               items: rows of one colour
     LK_MRESIDUAL,  // p: d, b, U, r                  items: interior rows
     LK_MRESTRICT,  // p: df, rf, Uc, wc, dc, bc      items: coarse rows (n = fine n)
     LK_MPROLONG,   // p: df, dc, wc                  items: fine interior rows
     LK_INJECT,     // p: Uf, Uc                      items: coarse rows (n = fine n)
     LK_ACCUM,      // p: u64, d                      items: interior rows
-    LK_ZERO,       // p: d (FP32)                    items: all rows
-    LK_RES32,      // p: u64, f, b0, partials        items: interior rows
+    LK_RES32,      // p: u64, f, b0, partials, H[3], d   items: as LK_NORM
 };
 
 // planes per work item of a norm list (a lane walks them along z)
@@ -196,10 +219,14 @@ hipError_t launch_tail(hipStream_t st, int mode, int order, int rmode, const Tai
                        unsigned long long *nfall);
 // fused residual + restriction (op: OP_MA / OP_LAP), one block per tile
 hipError_t launch_rrestrict(hipStream_t st, int op, int rmode, const RrList *L, int blocks);
-// the LDS form (MODE_MA, MODE_LAP; every entry with lds = 1); fast: every
-// entry's levels have at most kTailFastN intervals
+// the same for the mixed inner problem; form: also U and H of the coarse level
+hipError_t launch_mrrestrict(hipStream_t st, int rmode, const MrList *L, int blocks, int tz,
+                             bool form);
+// the LDS form (every entry with lds = 1); fast: every entry's levels have at
+// most kTailFastN intervals
 hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
-                           const TailList *T, int blocks, int nu1, int nu2, int nu0, unsigned long long *ncount);
+                           const TailList *T, int blocks, int nu1, int nu2, int nu0,
+                           unsigned long long *ncount, unsigned long long *nfall);
 
 struct SolveRef {
     ma_solver *s = nullptr;
@@ -349,8 +376,9 @@ class Engine {
     std::vector<int> rr_;
     std::vector<size_t> rroff_;            // byte offset of each RrList
     std::vector<int> rrblocks_;            // blocks per RrList launch
+    std::vector<int> rrtz_;                // and its tile height
     size_t rr_stride_ = 0;
-    int norm_ = -1, accum_ = -1, zero_ = -1;
+    int norm_ = -1, accum_ = -1;
 
     double *partials_ = nullptr;
     size_t partials_cap_ = 0;

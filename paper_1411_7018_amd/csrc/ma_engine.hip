@@ -293,7 +293,47 @@ __device__ __forceinline__ void pt_msweep(const GridItem &G, long p, long sy, lo
     const double *U = static_cast<const double *>(G.p[2]);
     const LevelConst lc = level_const(G.n);
     bool fb = false, nc = false;
-    d[p] = mixed_point(d, U, b[p], p, sy, sz, lc.s, lc.s4, lc.sf, lc.s4f, lc.hkf, fb, nc);
+    const Sym32 H = to32(hessian_at(U, p, 1, sy, sz, lc.s, lc.s4));
+    d[p] = mixed_point(H, d, UNode<const double *>{U, p, 1, sy, sz}, b[p], p, sy, sz, lc, fb, nc);
+    if (fb)
+        atomicAdd(nfall + G.slot, 1ull);
+    if (nc)
+        atomicAdd(ncount + G.slot, 1ull);
+}
+
+// Node (i, j, k) in an array whose rows hold their even columns first and then
+// the odd ones: a colour phase reads a half row.
+__device__ __forceinline__ int split_col(int i, int n)
+{
+    return (i & 1) * ((n + 2) >> 1) + (i >> 1);
+}
+__device__ __forceinline__ long split_at(int i, int j, int k, int n)
+{
+    const long sy = n + 1;
+    return (j + sy * k) * sy + split_col(i, n);
+}
+
+// The same on a multi-block level, with H = D^2 U from the arrays formed once
+// per outer step, and b in split rows like H.
+//
+// Of the 4.2 M updates of a colour at n = 256 each read 19 FP64 values of U for
+// H, formed again in every sweep, and did the second differences in FP64:
+// 75 us a colour.  Six stored floats a node, in
+// split rows so that a colour reads its own half only, leave 54 us.
+__device__ __forceinline__ void pt_msweep_h(const GridItem &G, int i, int j, int k, long sy,
+                                            long sz, unsigned long long *__restrict__ ncount,
+                                            unsigned long long *__restrict__ nfall)
+{
+    const long p = i + sy * j + sz * k, q = split_at(i, j, k, G.n);
+    const auto d = gptr<float>(G.p[0]);
+    const Float2 h0 = gptr<const Float2>(G.p[3])[q], h1 = gptr<const Float2>(G.p[4])[q],
+                 h2 = gptr<const Float2>(G.p[5])[q];
+    const Sym32 H{h0.x, h0.y, h1.x, h1.y, h2.x, h2.y};
+    const LevelConst lc{G.s, 0.25 * G.s, float(G.s), float(0.25 * G.s), float(G.hk)};
+    bool fb = false, nc = false;
+    const auto U = gptr<const double>(G.p[2]);
+    d[p] = mixed_point(H, d, UNode<decltype(U)>{U, p, 1, sy, sz}, gptr<const float>(G.p[1])[q], p,
+                       sy, sz, lc, fb, nc);
     if (fb)
         atomicAdd(nfall + G.slot, 1ull);
     if (nc)
@@ -311,6 +351,28 @@ __device__ __forceinline__ void pt_mresid(const GridItem &G, long p, long sy, lo
     static_cast<float *>(G.p[3])[p] = b[p] - t_of(H, adj32(H), E);
 }
 
+// I_h^H r of the mixed inner problem at fine index f.
+template <int RMODE, typename PR>
+__device__ __forceinline__ float mixed_rh(PR rf, long f, long fy, long fz)
+{
+#pragma clang fp contract(off)
+    if (RMODE == 0) {
+        const float w[3] = {0.25f, 0.5f, 0.25f};
+        float rh = 0.0f;
+#pragma unroll
+        for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+            for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+                for (int dx = -1; dx <= 1; ++dx)
+                    rh = fmaf(w[dz + 1] * w[dy + 1] * w[dx + 1],
+                              rf[f + dx + fy * dy + fz * dz], rh);
+        return rh;
+    }
+    return (fmaf(6.0f, rf[f], rf[f - 1] + rf[f + 1]) + (rf[f - fy] + rf[f + fy])
+            + (rf[f - fz] + rf[f + fz])) * (1.0f / 12.0f);
+}
+
 template <int RMODE>
 __device__ __forceinline__ void pt_mrestrict(const GridItem &G, int I, int J, int K)
 {
@@ -326,21 +388,7 @@ __device__ __forceinline__ void pt_mrestrict(const GridItem &G, int I, int J, in
     static_cast<float *>(G.p[4])[c] = v;
     float bv = 0.0f;
     if (I >= 1 && I <= nc - 1 && J >= 1 && J <= nc - 1 && K >= 1 && K <= nc - 1) {
-        float rh;
-        if (RMODE == 0) {
-            const float w[3] = {0.25f, 0.5f, 0.25f};
-            rh = 0.0f;
-#pragma unroll
-            for (int dz = -1; dz <= 1; ++dz)
-#pragma unroll
-                for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-                    for (int dx = -1; dx <= 1; ++dx)
-                        rh += (w[dz + 1] * w[dy + 1] * w[dx + 1]) * rf[f + dx + fy * dy + fz * dz];
-        } else {
-            rh = (6.0f * rf[f] + (rf[f - 1] + rf[f + 1]) + (rf[f - fy] + rf[f + fy])
-                  + (rf[f - fz] + rf[f + fz])) * (1.0f / 12.0f);
-        }
+        const float rh = mixed_rh<RMODE>(rf, f, fy, fz);
         const LevelConst lcc = level_const(nc);
         const Sym32 H = to32(hessian_at(Uc, c, 1, cy, cz, lcc.s, lcc.s4));
         const Sym32 E = hess32(df, f, 2, 2 * fy, 2 * fz, lcc.sf, lcc.s4f);
@@ -392,14 +440,17 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
             } else if (KIND == LK_SWEEP) {
                 pt_sweep<OP>(G, p, sy, sz, ncount);
             } else {
-                pt_msweep(G, p, sy, sz, ncount, nfall);
+                pt_msweep_h(G, i, j, k, sy, sz, ncount, nfall);
             }
         }
-    } else if (KIND == LK_NORM) {
+    } else if (KIND == LK_NORM || KIND == LK_RES32) {
         // Squared residuals of a 64-node row segment over kNormPlanes planes:
         // each lane walks along z keeping the 3x3 neighbourhoods of three
         // planes in registers, 9 loads per node instead of the 19 of the
-        // gathered stencil.
+        // gathered stencil.  LK_RES32 also stores what the next outer step of
+        // the mixed form takes from the same stencil: the residual in FP32,
+        // H = D^2 u (G.p[4]; null when the level has no row kernels) and the
+        // zero start of the correction.
         const int i = 1 + bx * 64 + t, j = 1 + by;
         const int k0 = 1 + bz * kNormPlanes, k1 = min(k0 + kNormPlanes, n);
         const int ic = min(i, n - 1);
@@ -429,7 +480,24 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
                 load(P3, k + 2);
                 fn = F[ic + sy * j + sz * (k + 1)];
             }
-            const double rv = resid_win<OP>(P0 + 4, P1 + 4, P2 + 4, G.s, fc);
+            double rv;
+            if (KIND == LK_RES32) {
+                const Hess h = hessian3(P0 + 4, P1 + 4, P2 + 4, 1, -1, 3, G.s, 0.25 * G.s);
+                rv = fc - det3(h);
+                if (i <= n - 1) {
+                    const long p = i + sy * j + sz * k;
+                    const long q = G.p[4] ? split_at(i, j, k, n) : p;
+                    gptr<float>(G.p[2])[q] = float(rv);
+                    gptr<float>(G.p[7])[p] = 0.0f;
+                    if (G.p[4]) {
+                        gptr<Float2>(G.p[4])[q] = Float2{float(h.xx), float(h.yy)};
+                        gptr<Float2>(G.p[5])[q] = Float2{float(h.zz), float(h.xy)};
+                        gptr<Float2>(G.p[6])[q] = Float2{float(h.xz), float(h.yz)};
+                    }
+                }
+            } else {
+                rv = resid_win<OP>(P0 + 4, P1 + 4, P2 + 4, G.s, fc);
+            }
             if (i <= n - 1)
                 acc += rv * rv;
 #pragma unroll
@@ -442,33 +510,20 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
         }
         const double sum = wave_sum64(acc);
         if (t == 0)
-            static_cast<double *>(G.p[2])[G.pbase + bx + G.gx * (by + G.gy * bz)] = sum;
-    } else if (KIND == LK_RESIDUAL || KIND == LK_RES32) {
+            static_cast<double *>(G.p[KIND == LK_NORM ? 2 : 3])[G.pbase + bx +
+                                                                G.gx * (by + G.gy * bz)] = sum;
+    } else if (KIND == LK_RESIDUAL) {
         const int i = 1 + bx * 64 + t, j = 1 + by, k = 1 + bz;
-        double rv = 0.0;
         if (i <= n - 1) {
             const long p = i + sy * j + sz * k;
-            rv = pt_resid<OP>(G, p, sy, sz);
-            if (KIND == LK_RESIDUAL)
-                gptr<double>(G.p[2])[p] = rv;
-            if (KIND == LK_RES32)
-                static_cast<float *>(G.p[2])[p] = float(rv);
+            gptr<double>(G.p[2])[p] = pt_resid<OP>(G, p, sy, sz);
         }
-        if (KIND == LK_RES32) {
-            const double sum = wave_sum64(rv * rv);
-            if (t == 0) {
-                const int local = bx + G.gx * (by + G.gy * bz);
-                static_cast<double *>(G.p[3])[G.pbase + local] = sum;
-            }
-        }
-    } else if (KIND == LK_RESTRICT || KIND == LK_MRESTRICT || KIND == LK_INJECT) {
+    } else if (KIND == LK_RESTRICT || KIND == LK_INJECT) {
         const int nc = n / 2;
         const int I = bx * 64 + t, J = by, K = bz;
         if (I <= nc) {
             if (KIND == LK_RESTRICT)
                 pt_restrict<OP, RMODE>(G, I, J, K);
-            else if (KIND == LK_MRESTRICT)
-                pt_mrestrict<RMODE>(G, I, J, K);
             else {
                 const long fy = n + 1, cy = nc + 1;
                 static_cast<double *>(G.p[1])[I + cy * J + cy * cy * K] =
@@ -481,20 +536,12 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
             prolong_row<double>(G, bx, t, 1 + by, 1 + bz);
         else
             prolong_row<float>(G, bx, t, 1 + by, 1 + bz);
-    } else if (KIND == LK_MRESIDUAL) {
-        const int i = 1 + bx * 64 + t, j = 1 + by, k = 1 + bz;
-        if (i <= n - 1)
-            pt_mresid(G, i + sy * j + sz * k, sy, sz);
     } else if (KIND == LK_ACCUM) {
         const int i = 1 + bx * 64 + t, j = 1 + by, k = 1 + bz;
         if (i <= n - 1) {
             const long p = i + sy * j + sz * k;
-            static_cast<double *>(G.p[0])[p] += double(static_cast<const float *>(G.p[1])[p]);
+            gptr<double>(G.p[0])[p] += double(gptr<const float>(G.p[1])[p]);
         }
-    } else if (KIND == LK_ZERO) {
-        const int i = bx * 64 + t, j = by, k = bz;
-        if (i <= n)
-            static_cast<float *>(G.p[0])[i + sy * j + sz * k] = 0.0f;
     }
 }
 
@@ -783,63 +830,76 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(const TailList *__restric
 }
 
 // Fused residual and FAS restriction (FP64 operators): one workgroup per
-// TC^3 block of coarse nodes.  It loads the fine u it needs into LDS,
+// TC x TC x TZ block of coarse nodes.  It loads the fine u it needs into LDS,
 // computes r = F - S(u) once per fine node of the block's footprint into
 // LDS, and restricts from LDS: injection into w_H and u_H and b_H =
 // S_H(w_H) + I_h^H r.  The fine residual never goes through memory, and the
 // arithmetic is that of resid_node and restrict_node, so the coarse arrays
 // are bitwise those of the separate residual and restriction launches.
-template <int TC>
+template <int TC, int TZ>
 struct RrShape {
     static constexpr int RU = 2 * TC + 3;    // u footprint per side (fine nodes)
     static constexpr int RR = 2 * TC + 1;    // r footprint per side
+    static constexpr int RUZ = 2 * TZ + 3, RRZ = 2 * TZ + 1;   // planes
     // LDS row strides, padded to 4 mod 8 doubles: the restriction reads the
     // footprints at x stride 2, and rows of 4 mod 8 doubles spread the 4 x 4
     // coarse nodes of a plane over more LDS banks than rows of 11 or 9
     static constexpr int UX = RU + (12 - RU % 8) % 8, RX = RR + (12 - RR % 8) % 8;
-    static constexpr int SU = UX * RU * RU, SR = RX * RR * RR;   // LDS doubles
+    static constexpr int SU = UX * RU * RUZ, SR = RX * RR * RRZ;   // LDS elements
 };
 
-template <int OP, int RMODE, int TC, int NT>
+// Element at a byte offset from a block-uniform base: one scalar base and a
+// 32-bit offset per lane.
+template <typename T>
+__device__ __forceinline__ T at_byte(const T *base, unsigned off)
+{
+    return *reinterpret_cast<const T __attribute__((address_space(1))) *>(
+        reinterpret_cast<const char __attribute__((address_space(1))) *>(to_global(base)) + off);
+}
+
+template <int OP, int RMODE, int TC, int TZ, int NT>
 __device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double *__restrict__ su,
                                                double *__restrict__ sr)
 {
-    using R = RrShape<TC>;
-    constexpr int RU = R::RU, RR = R::RR, UX = R::UX, RX = R::RX;
+    using R = RrShape<TC, TZ>;
+    constexpr int RU = R::RU, RR = R::RR, UX = R::UX, RX = R::RX, RUZ = R::RUZ, RRZ = R::RRZ;
     const int nf = G.n, nc = nf / 2;
     const int tx = tile % G.tiles_x, rest = tile / G.tiles_x;
     const int ty = rest % G.tiles_y, tz = rest / G.tiles_y;
-    const int I0 = tx * TC, J0 = ty * TC, K0 = tz * TC;
+    const int I0 = tx * TC, J0 = ty * TC, K0 = tz * TZ;
     const int ux0 = 2 * I0 - 2, uy0 = 2 * J0 - 2, uz0 = 2 * K0 - 2;   // u footprint origin
     const long fy = nf + 1, fz = fy * fy;
     const int tid = int(threadIdx.x);
-    const auto uf = to_global(G.uf);
-    const auto F = to_global(G.F);
+    // offsets are from the footprint's first plane inside the grid: 32 bits
+    // hold the planes of a footprint (n <= 2048: 19 x 34 MB)
+    const int zb = max(uz0, 0);
+    const double *ub = G.uf + fz * zb, *Fb = G.F + fz * zb;
+    const unsigned fzb = unsigned(fz) * 8u;
     // A thread takes one column (x, y) of a footprint and a run of its
     // planes: the column's offset and bounds are worked out once, and each
     // plane adds a plane stride.  Every global load of a thread is issued
     // before the first is used; outside the grid a load reads node 0 and is
     // discarded.
-    constexpr int CU2 = RU * RU, GU = NT / CU2, PU = (RU + GU - 1) / GU;   // u footprint
-    constexpr int CR2 = RR * RR, GR = NT / CR2, PR = (RR + GR - 1) / GR;   // r footprint
+    constexpr int CU2 = RU * RU, GU = NT / CU2, PU = (RUZ + GU - 1) / GU;   // u footprint
+    constexpr int CR2 = RR * RR, GR = NT / CR2, PR = (RRZ + GR - 1) / GR;   // r footprint
     static_assert(GU >= 1 && GR >= 1, "a block covers every column of a footprint");
     {
         const int col = tid % CU2, grp = tid / CU2;
         const int lx = col % RU, ly = col / RU, lz0 = grp * PU;
         const int gx = ux0 + lx, gy = uy0 + ly;
         const bool cin = grp < GU && gx >= 0 && gx <= nf && gy >= 0 && gy <= nf;
-        const long co = gx + fy * gy;
+        const unsigned co = unsigned(gx + (nf + 1) * gy + (uz0 + lz0 - zb) * int(fz)) * 8u;
         double v[PU];
 #pragma unroll
         for (int m = 0; m < PU; ++m) {
             const int gz = uz0 + lz0 + m;
-            const bool in = cin && lz0 + m < RU && gz >= 0 && gz <= nf;
-            const double x = uf[in ? co + fz * gz : 0];
+            const bool in = cin && lz0 + m < RUZ && gz >= 0 && gz <= nf;
+            const double x = at_byte(ub, in ? co + unsigned(m) * fzb : 0u);
             v[m] = in ? x : 0.0;
         }
 #pragma unroll
         for (int m = 0; m < PU; ++m)
-            if (grp < GU && lz0 + m < RU)
+            if (grp < GU && lz0 + m < RUZ)
                 su[lx + UX * (ly + RU * (lz0 + m))] = v[m];
     }
     // right-hand side of the fine interior nodes of the footprint (origin
@@ -849,19 +909,19 @@ __device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double
     const int rx = rcol % RR, ry = rcol / RR, rz0 = rgrp * PR;
     const int hx = ux0 + 1 + rx, hy = uy0 + 1 + ry;
     const bool rcin = rgrp < GR && hx >= 1 && hx <= nf - 1 && hy >= 1 && hy <= nf - 1;
-    const long rco = hx + fy * hy;
+    const unsigned rco = unsigned(hx + (nf + 1) * hy + (uz0 + 1 + rz0 - zb) * int(fz)) * 8u;
     double fv[PR];
 #pragma unroll
     for (int m = 0; m < PR; ++m) {
         const int gz = uz0 + 1 + rz0 + m;
-        const bool in = rcin && rz0 + m < RR && gz >= 1 && gz <= nf - 1;
-        fv[m] = F[in ? rco + fz * gz : 0];
+        const bool in = rcin && rz0 + m < RRZ && gz >= 1 && gz <= nf - 1;
+        fv[m] = at_byte(Fb, in ? rco + unsigned(m) * fzb : 0u);
     }
     lds_barrier();
     // r on the fine interior nodes of the footprint, walking the column up
     // its planes with the 3 x 3 neighbourhoods of three consecutive planes
     // in registers (the residual's expression is that of resid_val)
-    if (rgrp < GR && rz0 < RR) {
+    if (rgrp < GR && rz0 < RRZ) {
         const double *cb = static_cast<const double *>(su) + (rx + 1) + UX * (ry + 1);
         auto win = [&](double *W, int pz) {
             const double *b = cb + UX * RU * pz;
@@ -877,7 +937,7 @@ __device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double
 #pragma unroll
         for (int m = 0; m < PR; ++m) {
             const int lz = rz0 + m;
-            if (lz >= RR)
+            if (lz >= RRZ)
                 break;
             win(P2, lz + 2);
             const int gz = uz0 + 1 + lz;
@@ -898,7 +958,7 @@ __device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double
     const auto uc = to_global(G.uc);
     const auto bc = to_global(G.bc);
     const double sc = double(nc) * double(nc);
-    for (int el = tid; el < TC * TC * TC; el += NT) {
+    for (int el = tid; el < TC * TC * TZ; el += NT) {
         const int a = el % TC, b2 = el / TC;
         const int I = I0 + a, J = J0 + b2 % TC, K = K0 + b2 / TC;
         if (I > nc || J > nc || K > nc)
@@ -917,11 +977,11 @@ __device__ __forceinline__ void rrestrict_tile(const RrGrid &G, int tile, double
     }
 }
 
-template <int OP, int RMODE, int TC, int NT>
+template <int OP, int RMODE, int TC, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_rrestrict(const RrList *__restrict__ Lst)
 {
-    __shared__ double su[RrShape<TC>::SU];
-    __shared__ double sr[RrShape<TC>::SR];
+    __shared__ double su[RrShape<TC, TZ>::SU];
+    __shared__ double sr[RrShape<TC, TZ>::SR];
     const int total = Lst->total;
     const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
     if (t >= total)
@@ -933,16 +993,171 @@ __global__ __launch_bounds__(NT) void k_rrestrict(const RrList *__restrict__ Lst
     const RrGrid G = Lst->g[g];   // the whole descriptor in one set of loads
     if ((Lst->stopped >> G.slot) & 1ull)
         return;
-    rrestrict_tile<OP, RMODE, TC, NT>(G, t - G.start, su, sr);
+    rrestrict_tile<OP, RMODE, TC, TZ, NT>(G, t - G.start, su, sr);
 }
 
 // The same for one grid passed by value (gridDim.x = its tile count).
-template <int OP, int RMODE, int TC, int NT>
+template <int OP, int RMODE, int TC, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_rrestrict1(RrGrid G)
 {
-    __shared__ double su[RrShape<TC>::SU];
-    __shared__ double sr[RrShape<TC>::SR];
-    rrestrict_tile<OP, RMODE, TC, NT>(G, tile_of_block(int(blockIdx.x), int(gridDim.x)), su, sr);
+    __shared__ double su[RrShape<TC, TZ>::SU];
+    __shared__ double sr[RrShape<TC, TZ>::SR];
+    rrestrict_tile<OP, RMODE, TC, TZ, NT>(G, tile_of_block(int(blockIdx.x), int(gridDim.x)), su, sr);
+}
+
+// Fused residual and FAS restriction of the mixed inner problem, by the same
+// tiles: the residual b - T(delta) is formed in LDS from delta and U (FP64:
+// reading U is less than reading the six floats of H at every node), and the
+// coarse level gets w_H = d_H = injected delta and b_H = T_H(w_H) + I_h^H r.
+// form: the first inner cycle of an outer step, which also injects U and, when
+// the coarse level has row kernels (G.Hc, b in split rows), forms H there.
+// Bound by the loads of a tile's halo; n = 256: 270 us as a residual and a
+// restriction launch, 174 us so, and no injection launch.
+template <int RMODE, int TC, int TZ, int NT>
+__global__ __launch_bounds__(NT) void k_mrrestrict(const MrList *__restrict__ Lst, int form)
+{
+    using R = RrShape<TC, TZ>;
+    constexpr int RU = R::RU, RR = R::RR, UX = R::UX, RX = R::RX, RUZ = R::RUZ, RRZ = R::RRZ;
+    __shared__ double su[R::SU];
+    __shared__ float sd[R::SU];
+    __shared__ float sr[R::SR];
+    const int total = Lst->total;
+    const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
+    if (t >= total)
+        return;
+    const int ng = Lst->ngrids;
+    int g = 0;
+    while (g + 1 < ng && Lst->g[g + 1].start <= t)
+        ++g;
+    const MrGrid G = Lst->g[g];
+    if ((Lst->stopped >> G.slot) & 1ull)
+        return;
+    const int tile = t - G.start;
+    const int nf = G.n, nc = nf / 2;
+    const int tx = tile % G.tiles, rest = tile / G.tiles;
+    const int ty = rest % G.tiles, tz = rest / G.tiles;
+    const int I0 = tx * TC, J0 = ty * TC, K0 = tz * TZ;
+    const int ux0 = 2 * I0 - 2, uy0 = 2 * J0 - 2, uz0 = 2 * K0 - 2;   // footprint origin
+    const long fy = nf + 1, fz = fy * fy;
+    const int tid = int(threadIdx.x);
+    // offsets from the first plane inside the grid, as in rrestrict_tile
+    const int zb = max(uz0, 0);
+    const double *Ub = G.Uf + fz * zb;
+    const float *db = G.df + fz * zb, *bb = G.bf + fz * zb;
+    const unsigned fzb = unsigned(fz) * 4u;
+    // columns of the footprints, as in rrestrict_tile
+    constexpr int CU2 = RU * RU, GU = NT / CU2, PU = (RUZ + GU - 1) / GU;
+    constexpr int CR2 = RR * RR, GR = NT / CR2, PR = (RRZ + GR - 1) / GR;
+    static_assert(GU >= 1 && GR >= 1, "a block covers every column of a footprint");
+    {
+        const int col = tid % CU2, grp = tid / CU2;
+        const int lx = col % RU, ly = col / RU, lz0 = grp * PU;
+        const int gx = ux0 + lx, gy = uy0 + ly;
+        const bool cin = grp < GU && gx >= 0 && gx <= nf && gy >= 0 && gy <= nf;
+        const unsigned co = unsigned(gx + (nf + 1) * gy + (uz0 + lz0 - zb) * int(fz)) * 4u;
+        double v[PU];
+        float e[PU];
+#pragma unroll
+        for (int m = 0; m < PU; ++m) {
+            const int gz = uz0 + lz0 + m;
+            const bool in = cin && lz0 + m < RUZ && gz >= 0 && gz <= nf;
+            const unsigned o = in ? co + unsigned(m) * fzb : 0u;
+            v[m] = at_byte(Ub, 2u * o);
+            e[m] = at_byte(db, o);
+        }
+#pragma unroll
+        for (int m = 0; m < PU; ++m)
+            if (grp < GU && lz0 + m < RUZ) {
+                su[lx + UX * (ly + RU * (lz0 + m))] = v[m];
+                sd[lx + UX * (ly + RU * (lz0 + m))] = e[m];
+            }
+    }
+    const int rcol = tid % CR2, rgrp = tid / CR2;
+    const int rx = rcol % RR, ry = rcol / RR, rz0 = rgrp * PR;
+    const int hx = ux0 + 1 + rx, hy = uy0 + 1 + ry;
+    const bool rcin = rgrp < GR && hx >= 1 && hx <= nf - 1 && hy >= 1 && hy <= nf - 1;
+    const unsigned rco =
+        unsigned((hy + (uz0 + 1 + rz0 - zb) * (nf + 1)) * (nf + 1) + split_col(hx, nf)) * 4u;
+    float bv[PR];
+#pragma unroll
+    for (int m = 0; m < PR; ++m) {
+        const int gz = uz0 + 1 + rz0 + m;
+        const bool in = rcin && rz0 + m < RRZ && gz >= 1 && gz <= nf - 1;
+        bv[m] = at_byte(bb, in ? rco + unsigned(m) * fzb : 0u);
+    }
+    const LevelConst lf = level_const(nf), lc = level_const(nc);
+    lds_barrier();
+    if (rgrp < GR && rz0 < RRZ) {
+        const int c0 = (rx + 1) + UX * (ry + 1);
+        auto win = [&](auto *W, const auto *src, int pz) {
+            const auto *q = src + c0 + UX * RU * pz;
+#pragma unroll
+            for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+                for (int dx = -1; dx <= 1; ++dx)
+                    W[(dy + 1) * 3 + (dx + 1)] = q[dx + UX * dy];
+        };
+        double P0[9], P1[9], P2[9];
+        float E0[9], E1[9], E2[9];
+        win(P0, su, rz0);
+        win(E0, sd, rz0);
+        win(P1, su, rz0 + 1);
+        win(E1, sd, rz0 + 1);
+#pragma unroll
+        for (int m = 0; m < PR; ++m) {
+            const int lz = rz0 + m;
+            if (lz >= RRZ)
+                break;
+            win(P2, su, lz + 2);
+            win(E2, sd, lz + 2);
+            const int gz = uz0 + 1 + lz;
+            float rv = 0.0f;
+            if (rcin && gz >= 1 && gz <= nf - 1) {
+                const Sym32 H = to32(hessian3(P0 + 4, P1 + 4, P2 + 4, 1, -1, 3, lf.s, lf.s4));
+                rv = bv[m] - t_of(H, adj32(H), hess32_win(E0 + 4, E1 + 4, E2 + 4, lf.sf, lf.s4f));
+            }
+            sr[rx + RX * (ry + RR * lz)] = rv;
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                P0[q] = P1[q];
+                P1[q] = P2[q];
+                E0[q] = E1[q];
+                E1[q] = E2[q];
+            }
+        }
+    }
+    lds_barrier();
+    const long cy = nc + 1, cz = cy * cy;
+    for (int el = tid; el < TC * TC * TZ; el += NT) {
+        const int a = el % TC, b2 = el / TC;
+        const int I = I0 + a, J = J0 + b2 % TC, K = K0 + b2 / TC;
+        if (I > nc || J > nc || K > nc)
+            continue;
+        const int fu = (2 * I - ux0) + UX * (2 * J - uy0) + UX * RU * (2 * K - uz0);
+        const int fr = (2 * I - ux0 - 1) + RX * (2 * J - uy0 - 1) + RX * RR * (2 * K - uz0 - 1);
+        const long c = I + cy * J + cz * K;
+        const long q = G.Hc[0] ? split_at(I, J, K, nc) : c;
+        const float v = sd[fu];
+        to_global(G.wc)[c] = v;
+        to_global(G.dc)[c] = v;
+        if (form)
+            to_global(G.Uc)[c] = su[fu];
+        float b = 0.0f;
+        if (I >= 1 && I <= nc - 1 && J >= 1 && J <= nc - 1 && K >= 1 && K <= nc - 1) {
+            const Sym32 H = to32(hessian_at(static_cast<const double *>(su), fu, 2, 2 * UX,
+                                            2 * UX * RU, lc.s, lc.s4));
+            const Sym32 E = hess32(static_cast<const float *>(sd), fu, 2, 2 * UX, 2 * UX * RU,
+                                   lc.sf, lc.s4f);
+            b = t_of(H, adj32(H), E) +
+                mixed_rh<RMODE>(static_cast<const float *>(sr), fr, RX, RX * RR);
+            if (form && G.Hc[0]) {
+                to_global(G.Hc[0])[q] = Float2{H.xx, H.yy};
+                to_global(G.Hc[1])[q] = Float2{H.zz, H.xy};
+                to_global(G.Hc[2])[q] = Float2{H.xz, H.yz};
+            }
+        }
+        to_global(G.bc)[q] = b;
+    }
 }
 
 // Prolongation of one grid passed by value, one wavefront per work item (rows
@@ -959,29 +1174,198 @@ __global__ __launch_bounds__(64) void k_prolong1(GridItem G)
         prolong_row<double>(G, bx, int(threadIdx.x), 1 + by, 1 + bz);
 }
 
+// Coarse levels of the mixed inner problem in LDS (top level n <= kTailFastN):
+// delta, b, w and r of every level as in k_tail_lds, and H of every interior
+// node, formed once at entry from the top level's U (a lower level's injected U
+// is U at that level's stride).  Offsets (TailLds) are in floats; md is that
+// of H, one array of m^3 floats for each of its six components.
+// Bound by the chain of its ~140 phases; 16, 8, 4, 2: 153 us from global
+// memory with H formed for every update, 88 us so.
+template <int ORDER>
+__device__ __forceinline__ void tail_mixed_sweep(const TailEntry &E, int l, float *S,
+                                                 unsigned long long *__restrict__ ncount,
+                                                 unsigned long long *__restrict__ nfall)
+{
+    const GridItem &G = E.lv[l].sw;
+    const int n = G.n, m = n - 1, hn = n / 2, tid = int(threadIdx.x);
+    const int sy = n + 1, sz = sy * sy, M = m * m * m;
+    const int cnt = colour_count<ORDER>(n);
+    float *d = S + E.L.u[l];
+    const float *b = S + E.L.b[l], *h = S + E.L.md[l];
+    const LevelConst lc{G.s, 0.25 * G.s, float(G.s), float(0.25 * G.s), float(G.hk)};
+    const auto U = gptr<const double>(E.lv[0].sw.p[2]);
+    const long uy = E.lv[0].sw.n + 1, st = 1l << l;
+    const int ii = tid % hn, r = tid / hn;
+    const int jj = r % hn, kk = r / hn;
+    for (int c = 0; c < (ORDER == 0 ? 4 : 8); ++c) {
+        int i, j, k;
+        if (ORDER == 0) {
+            const int c0 = c & 1, c1 = c >> 1;
+            k = 1 + kk;
+            j = (((c0 + c1 + k) & 1) ? 1 : 2) + 2 * jj;
+            i = (((c0 + j) & 1) ? 1 : 2) + 2 * ii;
+        } else {
+            i = ((c & 1) ? 1 : 2) + 2 * ii;
+            j = (((c >> 1) & 1) ? 1 : 2) + 2 * jj;
+            k = (((c >> 2) & 1) ? 1 : 2) + 2 * kk;
+        }
+        if (tid < cnt && i <= n - 1 && j <= n - 1 && k <= n - 1) {
+            const int p = i + sy * j + sz * k, q = (i - 1) + m * ((j - 1) + m * (k - 1));
+            const Sym32 H{h[q],         h[q + M],     h[q + 2 * M],
+                          h[q + 3 * M], h[q + 4 * M], h[q + 5 * M]};
+            const UNode<decltype(U)> un{U, st * (i + uy * (j + uy * k)), st, st * uy, st * uy * uy};
+            bool fb = false, nc = false;
+            d[p] = mixed_point(H, d, un, b[p], p, sy, sz, lc, fb, nc);
+            if (fb)
+                atomicAdd(nfall + G.slot, 1ull);
+            if (nc)
+                atomicAdd(ncount + G.slot, 1ull);
+        }
+        lds_barrier();
+    }
+}
+
+template <int ORDER, int RMODE>
+__global__ __launch_bounds__(kTailLdsThreads) void k_tail_mixed(
+    const TailList *__restrict__ T, int nu1, int nu2, int nu0,
+    unsigned long long *__restrict__ ncount, unsigned long long *__restrict__ nfall)
+{
+    __shared__ float S[kTailMixedFloats];
+    if (int(blockIdx.x) >= T->nsolves)
+        return;
+    const TailEntry &E = T->e[blockIdx.x];
+    if ((T->stopped >> E.lv[0].sw.slot) & 1ull)
+        return;
+    const int L = E.nlev;
+    const int tid = int(threadIdx.x);
+    constexpr int NT = kTailLdsThreads;
+    const int n0 = E.lv[0].sw.n, N0 = (n0 + 1) * (n0 + 1) * (n0 + 1);
+    const auto gd = gptr<float>(E.lv[0].sw.p[0]);
+    const auto gb = gptr<const float>(E.lv[0].sw.p[1]);
+    const auto U = gptr<const double>(E.lv[0].sw.p[2]);
+    for (int q = tid; q < N0; q += NT) {
+        S[E.L.u[0] + q] = gd[q];
+        S[E.L.b[0] + q] = gb[q];
+    }
+    for (int l = 0; l < L; ++l) {
+        const GridItem &G = E.lv[l].sw;
+        const int m = G.n - 1, M = m * m * m;
+        const long uy = n0 + 1, st = 1l << l;
+        float *h = S + E.L.md[l];
+        for (int q = tid; q < M; q += NT) {
+            const int i = 1 + q % m, rr = q / m;
+            const int j = 1 + rr % m, k = 1 + rr / m;
+            const Sym32 H = to32(hessian_at(U, st * (i + uy * (j + uy * k)), st, st * uy,
+                                            st * uy * uy, G.s, 0.25 * G.s));
+            h[q] = H.xx;
+            h[q + M] = H.yy;
+            h[q + 2 * M] = H.zz;
+            h[q + 3 * M] = H.xy;
+            h[q + 4 * M] = H.xz;
+            h[q + 5 * M] = H.yz;
+        }
+    }
+    lds_barrier();
+    for (int l = 0; l < L; ++l) {
+        const int cnt = l < L - 1 ? nu1 : nu0;
+        for (int s = 0; s < cnt; ++s)
+            tail_mixed_sweep<ORDER>(E, l, S, ncount, nfall);
+        if (l == L - 1)
+            break;
+        const int n = E.lv[l].sw.n, m = n - 1, M = m * m * m;
+        const int sy = n + 1, sz = sy * sy;
+        const float *d = S + E.L.u[l], *b = S + E.L.b[l], *h = S + E.L.md[l];
+        float *r = S + E.L.r[l];
+        const float sf = float(E.lv[l].sw.s), s4f = 0.25f * sf;
+        for (int q = tid; q < M; q += NT) {
+            const int i = 1 + q % m, rr = q / m;
+            const int j = 1 + rr % m, k = 1 + rr / m;
+            const int p = i + sy * j + sz * k;
+            const Sym32 H{h[q],         h[q + M],     h[q + 2 * M],
+                          h[q + 3 * M], h[q + 4 * M], h[q + 5 * M]};
+            r[p] = b[p] - t_of(H, adj32(H), hess32(d, p, 1, sy, sz, sf, s4f));
+        }
+        lds_barrier();
+        const int nc = n / 2, mc = nc + 1, mi = nc - 1, MC = mi * mi * mi;
+        const float *hc = S + E.L.md[l + 1];
+        float *wc = S + E.L.w[l + 1], *dc = S + E.L.u[l + 1], *bc = S + E.L.b[l + 1];
+        const float sfc = float(E.lv[l + 1].sw.s), s4fc = 0.25f * sfc;
+        for (int q = tid; q < mc * mc * mc; q += NT) {
+            const int I = q % mc, rr = q / mc;
+            const int J = rr % mc, K = rr / mc;
+            const int f = 2 * I + sy * (2 * J) + sz * (2 * K);
+            const float v = d[f];
+            wc[q] = v;
+            dc[q] = v;
+            float bv = 0.0f;
+            if (I >= 1 && I <= nc - 1 && J >= 1 && J <= nc - 1 && K >= 1 && K <= nc - 1) {
+                const int qi = (I - 1) + mi * ((J - 1) + mi * (K - 1));
+                const Sym32 H{hc[qi],          hc[qi + MC],     hc[qi + 2 * MC],
+                              hc[qi + 3 * MC], hc[qi + 4 * MC], hc[qi + 5 * MC]};
+                bv = t_of(H, adj32(H), hess32(d, f, 2, 2 * sy, 2 * sz, sfc, s4fc)) +
+                     mixed_rh<RMODE>(static_cast<const float *>(r), f, sy, sz);
+            }
+            bc[q] = bv;
+        }
+        lds_barrier();
+    }
+    for (int l = L - 2; l >= 0; --l) {
+        const int n = E.lv[l].sw.n, m = n - 1;
+        const float *dc = S + E.L.u[l + 1], *wc = S + E.L.w[l + 1];
+        for (int q = tid; q < m * m * m; q += NT) {
+            const int i = 1 + q % m, rr = q / m;
+            const int j = 1 + rr % m, k = 1 + rr / m;
+            prolong_node<float>(n, i, j, k, S + E.L.u[l], dc, wc);
+        }
+        lds_barrier();
+        for (int s = 0; s < nu2; ++s)
+            tail_mixed_sweep<ORDER>(E, l, S, ncount, nfall);
+    }
+    for (int q = tid; q < N0; q += NT)
+        gd[q] = S[E.L.u[0] + q];
+}
+
 // Threads per tile: 256 when the launch has many tiles (throughput), 512
-// when it has few (one tile's residual rounds are the latency).
+// when it has few (one tile's residual rounds are the latency).  The mixed
+// form, bound by its instructions, also takes tiles of 8 coarse planes then,
+// which halves the halo and the set-up per node (n = 256: 199 -> 174 us); the
+// FP64 form is bound by its loads and loses by it (n = 384: 396 -> 418 us).
 constexpr int kRrManyTiles = 2048;
 
 template <int OP, int RMODE>
 hipError_t launch_rr_t(hipStream_t st, const RrList *L, int blocks)
 {
+    constexpr int T = kRrTile;
     if (blocks >= kRrManyTiles)
-        hipLaunchKernelGGL((k_rrestrict<OP, RMODE, kRrTile, 256>), dim3(blocks), dim3(256), 0, st, L);
+        hipLaunchKernelGGL((k_rrestrict<OP, RMODE, T, T, 256>), dim3(blocks), dim3(256), 0, st, L);
     else
-        hipLaunchKernelGGL((k_rrestrict<OP, RMODE, kRrTile, 512>), dim3(blocks), dim3(512), 0, st, L);
+        hipLaunchKernelGGL((k_rrestrict<OP, RMODE, T, T, 512>), dim3(blocks), dim3(512), 0, st, L);
+    return hipGetLastError();
+}
+
+template <int RMODE>
+hipError_t launch_mrr_t(hipStream_t st, const MrList *L, int blocks, int tz, int form)
+{
+    constexpr int T = kRrTile;
+    if (tz == 8)
+        hipLaunchKernelGGL((k_mrrestrict<RMODE, T, 8, 256>), dim3(blocks), dim3(256), 0, st, L,
+                           form);
+    else
+        hipLaunchKernelGGL((k_mrrestrict<RMODE, T, T, 512>), dim3(blocks), dim3(512), 0, st, L,
+                           form);
     return hipGetLastError();
 }
 
 template <int RMODE>
 hipError_t launch_rr1_t(hipStream_t st, const RrGrid &G, int blocks)
 {
+    constexpr int T = kRrTile;
     if (blocks >= kRrManyTiles)
-        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, kRrTile, 256>), dim3(blocks), dim3(256), 0,
-                           st, G);
+        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, T, T, 256>), dim3(blocks), dim3(256), 0, st,
+                           G);
     else
-        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, kRrTile, 512>), dim3(blocks), dim3(512), 0,
-                           st, G);
+        hipLaunchKernelGGL((k_rrestrict1<OP_MA, RMODE, T, T, 512>), dim3(blocks), dim3(512), 0, st,
+                           G);
     return hipGetLastError();
 }
 
@@ -1561,6 +1945,18 @@ hipError_t launch_tail_lds_t(hipStream_t st, int order, bool fast, const TailLis
     return hipGetLastError();
 }
 
+template <int RMODE>
+hipError_t launch_tail_mixed_t(hipStream_t st, int order, const TailList *T, int blocks, int nu1,
+                               int nu2, int nu0, unsigned long long *nc, unsigned long long *nf)
+{
+    const dim3 grid(blocks), block(kTailLdsThreads);
+    if (order == 1)
+        hipLaunchKernelGGL((k_tail_mixed<1, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc, nf);
+    else
+        hipLaunchKernelGGL((k_tail_mixed<0, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc, nf);
+    return hipGetLastError();
+}
+
 template <int KIND, int OP>
 hipError_t launch_k(hipStream_t st, int order, int color, int rmode, const BatchList *L,
                     int blocks, unsigned long long *nc, unsigned long long *nf)
@@ -1634,12 +2030,8 @@ void item_dims(int kind, int order, int n, int *gx, int *gy, int *gz)
         *gz = nc + 1;
         break;
     }
-    case LK_ZERO:
-        *gx = (n + 1 + 63) / 64;
-        *gy = n + 1;
-        *gz = n + 1;
-        break;
-    case LK_NORM:  // interior rows, planes in chunks of kNormPlanes
+    case LK_NORM:
+    case LK_RES32:  // interior rows, planes in chunks of kNormPlanes
         *gx = (n - 1 + 63) / 64;
         *gy = n - 1;
         *gz = (n - 1 + kNormPlanes - 1) / kNormPlanes;
@@ -1673,18 +2065,12 @@ hipError_t launch_batched(hipStream_t st, int kind, int op, int order, int color
         return launch_k<LK_PROLONG, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
     case LK_MSWEEP:
         return launch_k<LK_MSWEEP, OP_MA>(st, order, color, 0, L, blocks, nc, nf);
-    case LK_MRESIDUAL:
-        return launch_k<LK_MRESIDUAL, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
-    case LK_MRESTRICT:
-        return launch_k<LK_MRESTRICT, OP_MA>(st, 0, 0, rmode, L, blocks, nc, nf);
     case LK_MPROLONG:
         return launch_k<LK_MPROLONG, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
     case LK_INJECT:
         return launch_k<LK_INJECT, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
     case LK_ACCUM:
         return launch_k<LK_ACCUM, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
-    case LK_ZERO:
-        return launch_k<LK_ZERO, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
     case LK_RES32:
         return launch_k<LK_RES32, OP_MA>(st, 0, 0, 0, L, blocks, nc, nf);
     default:
@@ -1743,38 +2129,50 @@ hipError_t launch_tail(hipStream_t st, int mode, int order, int rmode, const Tai
 
 hipError_t launch_rrestrict(hipStream_t st, int op, int rmode, const RrList *L, int blocks)
 {
-    if (blocks <= 0)
-        return hipErrorInvalidValue;
     if (op == OP_MA)
         return rmode == 0 ? launch_rr_t<OP_MA, 0>(st, L, blocks) : launch_rr_t<OP_MA, 1>(st, L, blocks);
     return rmode == 0 ? launch_rr_t<OP_LAP, 0>(st, L, blocks) : launch_rr_t<OP_LAP, 1>(st, L, blocks);
 }
 
-// Tiles of an nf grid; *G its descriptor.
-static int rr_grid(int nf, const double *uf, const double *F, double *wc, double *uc, double *bc,
-                   int slot, RrGrid *G)
+hipError_t launch_mrrestrict(hipStream_t st, int rmode, const MrList *L, int blocks, int tz,
+                             bool form)
 {
-    std::memset(G, 0, sizeof(*G));
-    G->uf = uf;
-    G->F = F;
-    G->wc = wc;
-    G->uc = uc;
-    G->bc = bc;
-    G->n = nf;
-    G->slot = slot;
-    G->tiles_x = G->tiles_y = G->tiles_z = (nf / 2 + 1 + kRrTile - 1) / kRrTile;
-    G->s = double(nf) * double(nf);
-    return G->tiles_x * G->tiles_y * G->tiles_z;
+    if (rmode == 0)
+        return launch_mrr_t<0>(st, L, blocks, tz, form ? 1 : 0);
+    return launch_mrr_t<1>(st, L, blocks, tz, form ? 1 : 0);
+}
+
+// Tiles per side of the fused restriction from an nf grid, and in z for tiles
+// of tz planes.
+static int rr_side(int nf, int tz = kRrTile) { return (nf / 2 + 1 + tz - 1) / tz; }
+static long rr_tiles(int nf, int tz)
+{
+    return long(rr_side(nf)) * rr_side(nf) * rr_side(nf, tz);
+}
+
+static RrGrid rr_grid(int nf, const double *uf, const double *F, double *wc, double *uc, double *bc,
+                      int slot)
+{
+    RrGrid G;
+    std::memset(&G, 0, sizeof(G));
+    G.uf = uf;
+    G.F = F;
+    G.wc = wc;
+    G.uc = uc;
+    G.bc = bc;
+    G.n = nf;
+    G.slot = slot;
+    G.tiles_x = G.tiles_y = G.tiles_z = rr_side(nf);
+    G.s = double(nf) * double(nf);
+    return G;
 }
 
 hipError_t launch_restrict(hipStream_t st, int rmode, int nf, const double *uf, const double *F,
                            double *wc, double *uc, double *bc)
 {
-    RrGrid G;
-    const int blocks = rr_grid(nf, uf, F, wc, uc, bc, 0, &G);
-    if (rmode == 0)
-        return launch_rr1_t<0>(st, G, blocks);
-    return launch_rr1_t<1>(st, G, blocks);
+    const RrGrid G = rr_grid(nf, uf, F, wc, uc, bc, 0);
+    const int blocks = int(rr_tiles(nf, kRrTile));
+    return rmode == 0 ? launch_rr1_t<0>(st, G, blocks) : launch_rr1_t<1>(st, G, blocks);
 }
 
 hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc, const double *wc)
@@ -1792,12 +2190,14 @@ hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc, 
 }
 
 hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
-                           const TailList *T, int blocks, int nu1, int nu2, int nu0, unsigned long long *nc)
+                           const TailList *T, int blocks, int nu1, int nu2, int nu0,
+                           unsigned long long *nc, unsigned long long *nf)
 {
     if (blocks <= 0 || blocks > kMaxGrids)
         return hipErrorInvalidValue;
-    if (mode != Engine::MODE_MA && mode != Engine::MODE_LAP)
-        return hipErrorInvalidValue;
+    if (mode == Engine::MODE_MIXED)
+        return rmode == 0 ? launch_tail_mixed_t<0>(st, order, T, blocks, nu1, nu2, nu0, nc, nf)
+                          : launch_tail_mixed_t<1>(st, order, T, blocks, nu1, nu2, nu0, nc, nf);
     const bool ma = mode == Engine::MODE_MA;
     if (rmode == 0)
         return ma ? launch_tail_lds_t<OP_MA, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc)
@@ -2149,6 +2549,8 @@ GridItem Engine::grid(int kind, int i, int l, Mode mode) const
         G.p[0] = s->mx[l].d;
         G.p[1] = s->mx[l].b;
         G.p[2] = P(level_u(i, l, mode));
+        for (int q = 0; q < 3; ++q)
+            G.p[3 + q] = s->mixed_h(l, q);
         break;
     case LK_MRESIDUAL:
         G.p[0] = s->mx[l].d;
@@ -2177,14 +2579,14 @@ GridItem Engine::grid(int kind, int i, int l, Mode mode) const
         G.p[0] = solves_[i].u;
         G.p[1] = s->mx[0].d;
         break;
-    case LK_ZERO:
-        G.p[0] = s->mx[0].d;
-        break;
     case LK_RES32:
         G.p[0] = solves_[i].u;
         G.p[1] = P(solves_[i].f);
         G.p[2] = s->mx[0].b;
         G.p[3] = partials_;
+        for (int q = 0; q < 3 && multiblock_levels(i) > 0; ++q)
+            G.p[4 + q] = s->mixed_h(0, q);
+        G.p[7] = s->mx[0].d;
         break;
     default:
         break;
@@ -2279,22 +2681,22 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                 return cnt > k;
             }, false));
         auto nc = [&](int i) { return d < levels(i) - 1; };
-        res_[d] = make(mixed ? LK_MRESIDUAL : LK_RESIDUAL, d, true, nc, false);
-        rst_[d] = make(mixed ? LK_MRESTRICT : LK_RESTRICT, d, true, nc, false);
+        if (!mixed) {
+            res_[d] = make(LK_RESIDUAL, d, true, nc, false);
+            rst_[d] = make(LK_RESTRICT, d, true, nc, false);
+        }
         pro_[d] = make(mixed ? LK_MPROLONG : LK_PROLONG, d, true, nc, false);
         for (int k = 0; k < nu2_; ++k)
             swu_[d].push_back(make(SW, d, true, nc, false));
     }
     if (mixed)
         for (int d = 0; d + 1 < Dall_; ++d)
-            inj_[d] = make(LK_INJECT, d, false, [&](int i) { return d < levels(i) - 1; }, false);
+            inj_[d] = make(LK_INJECT, d, false, [&](int i) {
+                return d < levels(i) - 1 && d >= multiblock_levels(i);
+            }, false);
     auto all = [](int) { return true; };
     norm_ = make(mixed ? LK_RES32 : LK_NORM, 0, false, all, true);
-    accum_ = zero_ = -1;
-    if (mixed) {
-        accum_ = make(LK_ACCUM, 0, false, all, false);
-        zero_ = make(LK_ZERO, 0, false, all, false);
-    }
+    accum_ = mixed ? make(LK_ACCUM, 0, false, all, false) : -1;
     if (overflow)
         return fail(MA_ERR_ARG, "too many grids in one batched launch");
     if (size_t(pnext) > partials_cap_)
@@ -2306,12 +2708,14 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
     auto lds_layout = [&](int i, TailLds &Ld) {
         const int m = multiblock_levels(i), L = levels(i);
         int off = 0;
+        if (mixed && solves_[i].s->lv[m].n > kTailFastN)
+            return false;
         for (int l = 0; l < kMaxTail; ++l) {
             Ld.u[l] = Ld.b[l] = Ld.w[l] = Ld.r[l] = -1;
             if (l >= L - m)
                 continue;
             const int n = solves_[i].s->lv[m + l].n, N = int(npts(n));
-            const int U = (n + 1) * (n + 1) * tail_pitch(n);
+            const int U = mixed ? N : (n + 1) * (n + 1) * tail_pitch(n);
             Ld.md[l] = ((1u << 18) + n) / (n + 1);
             Ld.u[l] = off;
             off += U;
@@ -2325,10 +2729,14 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                 Ld.r[l] = off;
                 off += N;
             }
+            if (mixed) {
+                Ld.md[l] = unsigned(off);
+                off += 6 * (n - 1) * (n - 1) * (n - 1);
+            }
         }
-        return off <= kTailLdsDoubles;
+        return off <= (mixed ? kTailMixedFloats : kTailLdsDoubles);
     };
-    tail_lds_ = !mixed;
+    tail_lds_ = true;
     tail_fast_ = true;
     for (int i = 0; i < S && tail_lds_; ++i) {
         if (!solves_[i].s || levels(i) - multiblock_levels(i) <= 0)
@@ -2483,40 +2891,70 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
     // COLOR smoother keeps the separate launches as the reference form).
     rroff_.clear();
     rrblocks_.clear();
-    rr_stride_ = rr_list_bytes(S);
+    rrtz_.clear();
+    rr_stride_ = mixed ? mr_list_bytes(S) : rr_list_bytes(S);
     rr_.assign(D_, -1);
-    if (!mixed && smoother_ != MA_SMOOTHER_COLOR) {
-        for (int d = 0; d < D_; ++d) {
-            RrList Lr;
-            Lr.ngrids = 0;
-            Lr.stopped = 0;
-            int start = 0;
-            long bound = 0;
-            for (int i = 0; i < S; ++i) {
-                if (!solves_[i].s || multiblock_levels(i) <= d || d >= levels(i) - 1)
-                    continue;
-                const ma_solver *sv = solves_[i].s;
-                RrGrid G;
-                const int tiles = rr_grid(sv->lv[d].n, level_u(i, d, mode), level_F(i, d, mode),
-                                          sv->lv[d + 1].w, sv->lv[d + 1].u, sv->lv[d + 1].b, i,
-                                          &G);
-                bound += tiles;
-                if (!active[i])
-                    continue;
+    for (int d = 0; d < D_ && (mixed || smoother_ != MA_SMOOTHER_COLOR); ++d) {
+        auto has = [&](int i) {
+            return solves_[i].s && multiblock_levels(i) > d && d < levels(i) - 1;
+        };
+        long tiles4 = 0;
+        for (int i = 0; i < S; ++i)
+            if (has(i))
+                tiles4 += rr_tiles(solves_[i].s->lv[d].n, kRrTile);
+        if (tiles4 == 0)
+            continue;
+        const int tz = mixed && tiles4 >= kRrManyTiles ? 8 : kRrTile;
+        RrList Lr;
+        MrList Lm;
+        Lr.ngrids = Lm.ngrids = 0;
+        Lr.stopped = Lm.stopped = 0;
+        int start = 0;
+        long bound = 0;
+        for (int i = 0; i < S; ++i) {
+            if (!has(i))
+                continue;
+            const ma_solver *sv = solves_[i].s;
+            const int n = sv->lv[d].n, tiles = int(rr_tiles(n, tz));
+            bound += tiles;
+            if (!active[i])
+                continue;
+            if (mixed) {
+                MrGrid G;
+                std::memset(&G, 0, sizeof(G));
+                G.df = sv->mx[d].d;
+                G.bf = sv->mx[d].b;
+                G.Uf = level_u(i, d, mode);
+                G.wc = sv->mx[d + 1].w;
+                G.dc = sv->mx[d + 1].d;
+                G.bc = sv->mx[d + 1].b;
+                G.Uc = sv->mx[d + 1].U;
+                for (int q = 0; q < 3 && d + 1 < multiblock_levels(i); ++q)
+                    G.Hc[q] = static_cast<Float2 *>(sv->mixed_h(d + 1, q));
+                G.n = n;
+                G.slot = i;
+                G.tiles = rr_side(n);
                 G.start = start;
-                start += tiles;
+                Lm.g[Lm.ngrids++] = G;
+            } else {
+                RrGrid G = rr_grid(n, level_u(i, d, mode), level_F(i, d, mode), sv->lv[d + 1].w,
+                                   sv->lv[d + 1].u, sv->lv[d + 1].b, i);
+                G.start = start;
                 Lr.g[Lr.ngrids++] = G;
             }
-            Lr.total = start;
-            if (bound == 0)
-                continue;
-            rr_[d] = int(rroff_.size());
-            const size_t off = hbuf_.size();
-            rroff_.push_back(off);
-            rrblocks_.push_back(int(bound));
-            hbuf_.resize(off + rr_stride_, 0);
-            std::memcpy(hbuf_.data() + off, &Lr, rr_list_bytes(Lr.ngrids));
+            start += tiles;
         }
+        Lr.total = Lm.total = start;
+        rr_[d] = int(rroff_.size());
+        const size_t off = hbuf_.size();
+        rroff_.push_back(off);
+        rrblocks_.push_back(int(bound));
+        rrtz_.push_back(tz);
+        hbuf_.resize(off + rr_stride_, 0);
+        if (mixed)
+            std::memcpy(hbuf_.data() + off, &Lm, mr_list_bytes(Lm.ngrids));
+        else
+            std::memcpy(hbuf_.data() + off, &Lr, rr_list_bytes(Lr.ngrids));
     }
 
     // Byte offsets of every list header (count first): a solve that stops
@@ -2655,26 +3093,34 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
         }
         return MA_OK;
     };
-    auto vcycle = [&]() -> ma_status {
+    auto vcycle = [&](bool first) -> ma_status {
         for (int d = 0; d < D_; ++d) {
             if (profile_ && d == 0)
                 MA_TRY(prof_mark());
             MA_TRY(sweeps(swd_[d], bsd_[d]));
             if (profile_ && d == 0)
                 MA_TRY(prof_mark());
-            if (rr_[d] >= 0) {
+            if (mixed) {
+                if (rr_[d] >= 0)
+                    E_HIP(launch_mrrestrict(stream_, rmode_,
+                                            reinterpret_cast<const MrList *>(dl_ + rroff_[rr_[d]]),
+                                            rrblocks_[rr_[d]], rrtz_[rr_[d]], first));
+            } else if (rr_[d] >= 0) {
                 E_HIP(launch_rrestrict(stream_, op, rmode_,
                                        reinterpret_cast<const RrList *>(dl_ + rroff_[rr_[d]]),
                                        rrblocks_[rr_[d]]));
             } else {
-                MA_TRY(go(mixed ? LK_MRESIDUAL : LK_RESIDUAL, res_[d], 0));
-                MA_TRY(go(mixed ? LK_MRESTRICT : LK_RESTRICT, rst_[d], 0));
+                MA_TRY(go(LK_RESIDUAL, res_[d], 0));
+                MA_TRY(go(LK_RESTRICT, rst_[d], 0));
             }
         }
+        if (mixed && first && !tail_lds_)   // U below the coarse kernel's top level
+            for (int d = 0; d + 1 < Dall_; ++d)
+                MA_TRY(go(LK_INJECT, inj_[d], 0));
         if (tail_blocks_ > 0 && tail_lds_)
             E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_, tail_fast_,
                                   reinterpret_cast<const TailList *>(dl_ + toff_), tail_blocks_,
-                                  nu1_, nu2_, nu0_, dcount_));
+                                  nu1_, nu2_, nu0_, dcount_, dfall_));
         else if (tail_blocks_ > 0)
             E_HIP(launch_tail(stream_, int(mode), order_, rmode_,
                               reinterpret_cast<const TailList *>(dl_ + toff_), tail_blocks_, nu1_,
@@ -2693,14 +3139,11 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
     };
     if (cycle) {
         if (mixed) {
-            for (int d = 0; d + 1 < Dall_; ++d)
-                MA_TRY(go(LK_INJECT, inj_[d], 0));
-            MA_TRY(go(LK_ZERO, zero_, 0));
             for (int it = 0; it < inner_; ++it)
-                MA_TRY(vcycle());
+                MA_TRY(vcycle(it == 0));
             MA_TRY(go(LK_ACCUM, accum_, 0));
         } else {
-            MA_TRY(vcycle());
+            MA_TRY(vcycle(true));
         }
     }
     MA_TRY(go(mixed ? LK_RES32 : LK_NORM, norm_, 0));
@@ -2736,6 +3179,7 @@ std::vector<int> Engine::shape() const
     s.push_back(int(rroff_.size()));
     s.push_back(rroff_.empty() ? 0 : int(rroff_[0]));
     s.insert(s.end(), rrblocks_.begin(), rrblocks_.end());
+    s.insert(s.end(), rrtz_.begin(), rrtz_.end());
     s.push_back(int(stoff_));
     s.push_back(int(solves_.size()));
     return s;

@@ -124,6 +124,12 @@ struct ma_solver {
     // adds its non-certified updates, point updates and algorithmic bytes.
     ma_status fmg(double *u, const double *f, long long *nonconvex, double *updates,
                   double *bytes);
+    // H of a mixed solve's level l, two floats a node each (xx yy, zz xy, xz yz),
+    // in FP64 arrays that its inner cycles leave alone
+    void *mixed_h(int l, int q) const
+    {
+        return q == 0 ? lv[l].r : q == 1 ? lv[l].t : l == 0 ? R : lv[l].u;
+    }
     ma_status mixed_allocate();
     void mixed_release();
 };
