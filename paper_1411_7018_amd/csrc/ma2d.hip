@@ -184,9 +184,11 @@ __device__ __forceinline__ double fmg_value(U uc, int nc, int i, int j)
 // about 150 B a node and sweep and cost 2-4 us each on the coarse levels.
 // Section 4 solves, phase launches against legs and the coarse-level kernel:
 // 8193^2 red-black 16.9 -> 4.7 ms, 1537^2 4-colour 2.9 -> 0.77 ms, 129^2
-// 1.45 -> 0.23 ms.  At 8193^2 a leg takes 0.97-1.16 ms, bound by the ~65
-// vector instructions (55 of them 64-bit) of an update on 1.9 x the nodes;
-// its memory traffic alone would take 0.4 ms.  From 512^2 down it takes
+// 1.45 -> 0.23 ms.  At 8193^2 a leg takes 0.99-1.11 ms: the ~65 vector
+// instructions (55 of them 64-bit) of an update on 1.9 x the nodes keep the
+// vector units busy 60% of it, its memory traffic alone would take 0.4 ms, and
+// a tile's load and phases overlap only with other tiles', so the wavefronts
+// count: within 64 registers (launch bound) 6-8% faster than with 70.  From 512^2 down it takes
 // 7-11 us, mostly the latency of its load, phases and store.
 //   IN   LEG_U    the values of uin
 //        LEG_PRO  uin plus the bilinear interpolation of uc - wc (the
@@ -214,9 +216,15 @@ __device__ __forceinline__ double fmg_value(U uc, int nc, int i, int j)
 enum { LEG_U, LEG_PRO, LEG_FMG };
 enum { LEG_PLAIN, LEG_RESTRICT, LEG_NORM };
 
-template <int ORDER>
+// BIG: the tile of 4-colour legs from n = kLegBigN on, whose wider halo makes
+// 32 x 32 tiles update 2.2 x their nodes (52 x 44: 1.8 x).  A leg of two sweeps
+// and the restriction, 32 x 32 / 52 x 44, us: n = 384: 8.7 / 11.0, 768: 18.5 /
+// 18.2, 1536: 64 / 43.  Red-black legs (1.9 x) gain nothing by 56 x 44 tiles:
+// 4096: 239 / 250, 8192: 993 / 980.
+constexpr int kLegBigN = 768;
+template <int ORDER, bool BIG>
 struct LegShape {
-    static constexpr int TX = 32, TY = 32;
+    static constexpr int TX = BIG ? 52 : 32, TY = BIG ? 44 : 32;
     static constexpr int HX = ORDER == MA2D_RED_BLACK ? 6 : 10, HY = 6;
     static constexpr int LX = TX + 2 * HX, LY = TY + 2 * HY;   // loaded tile
     static constexpr int QX = LX / 2, QY = LY / 2;             // quads
@@ -286,10 +294,10 @@ __device__ __forceinline__ double update1(double c, const Nine &a, double F, dou
     return c + x * hh;
 }
 
-template <int ORDER, int IN, int OUT>
-__global__ __launch_bounds__(LegShape<ORDER>::NT) void k2_leg(LegArgs A)
+template <int ORDER, int IN, int OUT, bool BIG>
+__global__ __launch_bounds__((LegShape<ORDER, BIG>::NT), 8) void k2_leg(LegArgs A)
 {
-    using Sh = LegShape<ORDER>;
+    using Sh = LegShape<ORDER, BIG>;
     constexpr int QX = Sh::QX, QY = Sh::QY, LX = Sh::LX, LY = Sh::LY, HX = Sh::HX, HY = Sh::HY;
     constexpr bool RB = ORDER == MA2D_RED_BLACK;
     // red-black: the two buffers a colour's values alternate between; the
@@ -996,11 +1004,19 @@ int tail_level(const int *ns, int L)
     return l;
 }
 
-int leg_tiles(int n) { return (n + 1 + LegShape<MA2D_RED_BLACK>::TX - 1) / LegShape<MA2D_RED_BLACK>::TX; }
-static_assert(LegShape<MA2D_RED_BLACK>::TX == LegShape<MA2D_COLOR4>::TX &&
-                  LegShape<MA2D_RED_BLACK>::TY == LegShape<MA2D_RED_BLACK>::TX &&
-                  LegShape<MA2D_COLOR4>::TY == LegShape<MA2D_COLOR4>::TX,
-              "one tile count serves both orderings and both axes");
+// Tiles of a leg in x and y.
+bool leg_big(int order, int n) { return order == MA2D_COLOR4 && n >= kLegBigN; }
+dim3 leg_grid(int order, int n)
+{
+    using Small = LegShape<MA2D_COLOR4, false>;
+    using Big = LegShape<MA2D_COLOR4, true>;
+    static_assert(LegShape<MA2D_RED_BLACK, false>::TX == Small::TX &&
+                      LegShape<MA2D_RED_BLACK, false>::TY == Small::TY,
+                  "the small tile serves both orderings");
+    const int tx = leg_big(order, n) ? Big::TX : Small::TX;
+    const int ty = leg_big(order, n) ? Big::TY : Small::TY;
+    return dim3((n + tx) / tx, (n + ty) / ty);
+}
 
 dim3 residual_grid(int n)
 {
@@ -1009,11 +1025,10 @@ dim3 residual_grid(int n)
 
 // sums of squares of the finest level: one per tile of a leg or per block of
 // the residual kernel
-size_t partials2(int n)
+size_t partials2(int order, int n)
 {
-    const dim3 g = residual_grid(n);
-    const size_t t = size_t(leg_tiles(n));
-    return std::max(size_t(g.x) * g.y, t * t);
+    const dim3 g = residual_grid(n), t = leg_grid(order, n);
+    return std::max(size_t(g.x) * g.y, size_t(t.x) * t.y);
 }
 
 } // namespace
@@ -1078,13 +1093,13 @@ struct Leg {
     int sweeps = 0;
 };
 
-template <int ORDER>
+template <int ORDER, bool BIG>
 void launch_leg_t(hipStream_t st, const Leg &g, const LegArgs &A, int tiles)
 {
-    const dim3 grid(tiles), block(LegShape<ORDER>::NT);
+    const dim3 grid(tiles), block(LegShape<ORDER, BIG>::NT);
 #define MA2D_LEG(IN, OUT)                                                                        \
     if (g.in == IN && g.out == OUT)                                                              \
-        hipLaunchKernelGGL((k2_leg<ORDER, IN, OUT>), grid, block, 0, st, A);
+        hipLaunchKernelGGL((k2_leg<ORDER, IN, OUT, BIG>), grid, block, 0, st, A);
     MA2D_LEG(LEG_U, LEG_PLAIN)
     MA2D_LEG(LEG_U, LEG_RESTRICT)
     MA2D_LEG(LEG_FMG, LEG_PLAIN)
@@ -1108,7 +1123,8 @@ ma_status leg2(ma2d_solver *s, int l, const Leg &g, const double *uin, double *u
     A.n = s->ns[l];
     A.sweeps = g.sweeps;
     A.half = s->p.restriction == MA_RESTRICT_HALF ? 1 : 0;
-    A.tiles_x = leg_tiles(A.n);
+    const dim3 t = leg_grid(s->p.order, A.n);
+    A.tiles_x = int(t.x);
     if (g.in != LEG_U) {
         A.uc = s->u[l + 1];
         A.wc = s->w[l + 1];
@@ -1117,11 +1133,13 @@ ma_status leg2(ma2d_solver *s, int l, const Leg &g, const double *uin, double *u
         A.cw = s->w[l + 1];
         A.cb = s->b[l + 1];
     }
-    const int tiles = A.tiles_x * A.tiles_x;
+    const int tiles = int(t.x * t.y);
     if (s->p.order == MA2D_RED_BLACK)
-        launch_leg_t<MA2D_RED_BLACK>(s->st, g, A, tiles);
+        launch_leg_t<MA2D_RED_BLACK, false>(s->st, g, A, tiles);
+    else if (leg_big(s->p.order, A.n))
+        launch_leg_t<MA2D_COLOR4, true>(s->st, g, A, tiles);
     else
-        launch_leg_t<MA2D_COLOR4>(s->st, g, A, tiles);
+        launch_leg_t<MA2D_COLOR4, false>(s->st, g, A, tiles);
     H2_HIP(s, hipGetLastError());
     return MA_OK;
 }
@@ -1235,7 +1253,7 @@ ma_status tail2(ma2d_solver *s, int l, const double *x, double *u, const double 
 // FAS V-cycle on level l from x to u (x may be u).  fmg: the interior starts
 // as the FMG interpolation of the next level's u, and x holds the boundary.
 // norm: the last leg leaves the sums of squared residuals of the result in
-// part (leg_tiles^2 of them; levels above the coarse-level kernel with a
+// part (one per tile; levels above the coarse-level kernel with a
 // coarser level).
 ma_status vcycle2(ma2d_solver *s, int l, const double *x, double *u, const double *b,
                   bool fmg = false, bool norm = false)
@@ -1320,8 +1338,8 @@ ma_status cycle2(ma2d_solver *s, double *u, const double *f, bool fmg, double *l
         return MA_OK;
     if (!fused)
         return residual2(s, u, f, nullptr, l2);
-    const size_t t = size_t(leg_tiles(s->p.n));
-    return finish_norm2(s, t * t, l2);
+    const dim3 t = leg_grid(s->p.order, s->p.n);
+    return finish_norm2(s, size_t(t.x) * t.y, l2);
 }
 
 ma_status read_count(ma2d_solver *s, long long *out)
@@ -1372,7 +1390,7 @@ size_t ma2d_footprint_bytes(const ma2d_params *p)
     size_t b = 0;
     for (int l = 0; l < L && l <= tail_level(ns, L); ++l)
         b += (l == 0 ? 1 : 4) * pts2(ns[l]) * sizeof(double);
-    return b + partials2(p->n) * sizeof(double) + 4096;
+    return b + partials2(p->order, p->n) * sizeof(double) + 4096;
 }
 
 ma_status ma2d_create(const ma2d_params *p, void *hip_stream, ma2d_solver **out)
@@ -1412,7 +1430,7 @@ ma_status ma2d_create(const ma2d_params *p, void *hip_stream, ma2d_solver **out)
             st = s->alloc(&s->t[l], c);
     }
     if (st == MA_OK)
-        st = s->alloc(&s->part, partials2(p->n));
+        st = s->alloc(&s->part, partials2(p->order, p->n));
     if (st == MA_OK)
         st = s->alloc(&s->dsum, 4);
     if (st == MA_OK) {
