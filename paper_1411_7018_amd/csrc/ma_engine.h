@@ -291,7 +291,9 @@ class Engine {
     ma_status read_counters(std::vector<unsigned long long> &nonconvex,
                             std::vector<unsigned long long> &fallbacks);
     // Work of one tick of mode for solve i: point updates and algorithmic bytes.
-    void tick_cost(Mode mode, int i, double *updates, double *bytes) const;
+    void tick_cost(Mode mode, int i, double *updates, double *bytes, int l0 = 0) const;
+    ma_status begin_cycles(hipStream_t *st);
+    ma_status cycle_from(int l, unsigned long long *count);
     // profile: finest-level smoothing time, launches and bytes since the last call
     void take_profile(double *seconds, int *launches, double *bytes);
     const std::string &error() const { return err_; }
@@ -309,6 +311,7 @@ class Engine {
   private:
     ma_status rebuild(Mode mode, const std::vector<char> &active);
     ma_status enqueue(Mode mode, bool cycle);
+    ma_status enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count);
     ma_status launch(Mode mode, bool cycle, const std::vector<char> &active, int ticks = 1);
     ma_status collect(std::vector<double> &norms);
     ma_status plain(Mode mode, bool cycle, const std::vector<char> &active,
@@ -350,6 +353,8 @@ class Engine {
     std::vector<int> lng_;                 // grids per list
     std::vector<int> lgrid_;               // blocks per list launch (0: never any grid)
     size_t toff_ = 0;                      // byte offset of the tail table
+    bool sub_cycles_ = false;              // build tsub_ too
+    std::vector<size_t> tsub_;             // byte offsets of the tail tables of cycle_from
     int tail_blocks_ = 0;                  // blocks of the tail launch (0: no tail)
     bool tail_lds_ = false;                // the tail launch is the LDS form
     bool tail_fast_ = false;               // and its levels have at most kTailFastN intervals

@@ -2705,8 +2705,8 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
     // coarse-level table, after the lists.  The LDS form of the coarse-level
     // kernel runs when every solve's coarse levels fit its LDS (decided over
     // all solves of the engine, so it does not change when solves pause).
-    auto lds_layout = [&](int i, TailLds &Ld) {
-        const int m = multiblock_levels(i), L = levels(i);
+    auto lds_layout = [&](int i, int m, TailLds &Ld) {
+        const int L = levels(i);
         int off = 0;
         if (mixed && solves_[i].s->lv[m].n > kTailFastN)
             return false;
@@ -2742,9 +2742,24 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
         if (!solves_[i].s || levels(i) - multiblock_levels(i) <= 0)
             continue;
         TailLds Ld;
-        tail_lds_ = levels(i) - multiblock_levels(i) <= kMaxTail && lds_layout(i, Ld);
+        tail_lds_ = levels(i) - multiblock_levels(i) <= kMaxTail && lds_layout(i, multiblock_levels(i), Ld);
         tail_fast_ &= solves_[i].s->lv[multiblock_levels(i)].n <= kTailFastN;
     }
+    // entry of solve i whose levels start at level m
+    auto tail_entry = [&](TailEntry &E, int i, int m) {
+        const int L = levels(i);
+        E.nlev = L - m;
+        E.lds = lds_layout(i, m, E.L) ? 1 : 0;
+        for (int d = m; d < L; ++d) {
+            TailLevel &V = E.lv[d - m];
+            V.sw = grid(mixed ? LK_MSWEEP : LK_SWEEP, i, d, mode);
+            if (d < L - 1) {
+                V.res = grid(mixed ? LK_MRESIDUAL : LK_RESIDUAL, i, d, mode);
+                V.rst = grid(mixed ? LK_MRESTRICT : LK_RESTRICT, i, d, mode);
+                V.pro = grid(mixed ? LK_MPROLONG : LK_PROLONG, i, d, mode);
+            }
+        }
+    };
     toff_ = hbuf_.size();
     hbuf_.resize(toff_ + tail_bytes(S), 0);
     {
@@ -2759,26 +2774,24 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             if (L - m > kMaxTail)
                 return fail(MA_ERR_ARG, "too many coarse levels for the coarse-level kernel");
             ++bound;
-            if (!active[i])
-                continue;
-            TailEntry &E = T->e[nt++];
-            E.nlev = L - m;
-            E.lds = lds_layout(i, E.L) ? 1 : 0;
-            for (int l = 0; l < L - m; ++l) {
-                const int d = m + l;
-                TailLevel &V = E.lv[l];
-                V.sw = grid(mixed ? LK_MSWEEP : LK_SWEEP, i, d, mode);
-                if (d < L - 1) {
-                    V.res = grid(mixed ? LK_MRESIDUAL : LK_RESIDUAL, i, d, mode);
-                    V.rst = grid(mixed ? LK_MRESTRICT : LK_RESTRICT, i, d, mode);
-                    V.pro = grid(mixed ? LK_MPROLONG : LK_PROLONG, i, d, mode);
-                }
-            }
+            if (active[i])
+                tail_entry(T->e[nt++], i, m);
         }
         T->nsolves = nt;
         T->stopped = 0;
         tail_blocks_ = bound;
     }
+    // the same from every lower level of a lone solve on, for cycle_from
+    tsub_.clear();
+    if (sub_cycles_)
+        for (int d = multiblock_levels(0) + 1; d < levels(0); ++d) {
+            tsub_.push_back(hbuf_.size());
+            hbuf_.resize(hbuf_.size() + tail_bytes(1), 0);
+            TailList *T = reinterpret_cast<TailList *>(hbuf_.data() + tsub_.back());
+            tail_entry(T->e[0], 0, d);
+            T->nsolves = 1;
+            T->stopped = 0;
+        }
 
     // Block-sweep lists, after the tail table.  Sweeps 2q and 2q + 1 of a
     // depth run as a block sweep u -> t followed by t -> u when the depth's
@@ -3058,7 +3071,9 @@ ma_status Engine::prof_mark()
     return MA_OK;
 }
 
-ma_status Engine::enqueue(Mode mode, bool cycle)
+// A V-cycle from depth d0 down and up again on the engine stream; first: the
+// first of a tick; count: where its non-convex updates are counted.
+ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count)
 {
     const bool mixed = mode == MODE_MIXED;
     const int op = mode == MODE_LAP ? OP_LAP : OP_MA;
@@ -3067,7 +3082,7 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
     auto go = [&](int kind, int idx, int color) -> ma_status {
         if (lgrid_[idx] == 0)
             return MA_OK;
-        E_HIP(launch_batched(stream_, kind, op, order_, color, rmode_, L(idx), lgrid_[idx], dcount_,
+        E_HIP(launch_batched(stream_, kind, op, order_, color, rmode_, L(idx), lgrid_[idx], count,
                              dfall_));
         return MA_OK;
     };
@@ -3081,7 +3096,7 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
                 for (int h = 0; h < 2; ++h) {
                     const int f = pairs[k] + h;
                     if (fsblocks_[f] > 0)
-                        E_HIP(launch_bsweep(stream_, op, order_, fscfg_[f], FL(f), fsblocks_[f], dcount_,
+                        E_HIP(launch_bsweep(stream_, op, order_, fscfg_[f], FL(f), fsblocks_[f], count,
                                             fspro_[f] != 0));
                 }
                 k += 2;
@@ -3093,57 +3108,68 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
         }
         return MA_OK;
     };
-    auto vcycle = [&](bool first) -> ma_status {
-        for (int d = 0; d < D_; ++d) {
-            if (profile_ && d == 0)
-                MA_TRY(prof_mark());
-            MA_TRY(sweeps(swd_[d], bsd_[d]));
-            if (profile_ && d == 0)
-                MA_TRY(prof_mark());
-            if (mixed) {
-                if (rr_[d] >= 0)
-                    E_HIP(launch_mrrestrict(stream_, rmode_,
-                                            reinterpret_cast<const MrList *>(dl_ + rroff_[rr_[d]]),
-                                            rrblocks_[rr_[d]], rrtz_[rr_[d]], first));
-            } else if (rr_[d] >= 0) {
-                E_HIP(launch_rrestrict(stream_, op, rmode_,
-                                       reinterpret_cast<const RrList *>(dl_ + rroff_[rr_[d]]),
-                                       rrblocks_[rr_[d]]));
-            } else {
-                MA_TRY(go(LK_RESIDUAL, res_[d], 0));
-                MA_TRY(go(LK_RESTRICT, rst_[d], 0));
-            }
+    for (int d = d0; d < D_; ++d) {
+        if (profile_ && d == 0)
+            MA_TRY(prof_mark());
+        MA_TRY(sweeps(swd_[d], bsd_[d]));
+        if (profile_ && d == 0)
+            MA_TRY(prof_mark());
+        if (mixed) {
+            if (rr_[d] >= 0)
+                E_HIP(launch_mrrestrict(stream_, rmode_,
+                                        reinterpret_cast<const MrList *>(dl_ + rroff_[rr_[d]]),
+                                        rrblocks_[rr_[d]], rrtz_[rr_[d]], first));
+        } else if (rr_[d] >= 0) {
+            E_HIP(launch_rrestrict(stream_, op, rmode_,
+                                   reinterpret_cast<const RrList *>(dl_ + rroff_[rr_[d]]),
+                                   rrblocks_[rr_[d]]));
+        } else {
+            MA_TRY(go(LK_RESIDUAL, res_[d], 0));
+            MA_TRY(go(LK_RESTRICT, rst_[d], 0));
         }
-        if (mixed && first && !tail_lds_)   // U below the coarse kernel's top level
-            for (int d = 0; d + 1 < Dall_; ++d)
-                MA_TRY(go(LK_INJECT, inj_[d], 0));
-        if (tail_blocks_ > 0 && tail_lds_)
-            E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_, tail_fast_,
-                                  reinterpret_cast<const TailList *>(dl_ + toff_), tail_blocks_,
-                                  nu1_, nu2_, nu0_, dcount_, dfall_));
-        else if (tail_blocks_ > 0)
-            E_HIP(launch_tail(stream_, int(mode), order_, rmode_,
-                              reinterpret_cast<const TailList *>(dl_ + toff_), tail_blocks_, nu1_,
-                              nu2_, nu0_, dcount_, dfall_));
-        for (int d = D_ - 1; d >= 0; --d) {
-            // a fused depth prolongs inside its first post-smoothing sweep
-            if (!pro_fused_[d])
-                MA_TRY(go(mixed ? LK_MPROLONG : LK_PROLONG, pro_[d], 0));
-            if (profile_ && d == 0)
-                MA_TRY(prof_mark());
-            MA_TRY(sweeps(swu_[d], bsu_[d]));
-            if (profile_ && d == 0)
-                MA_TRY(prof_mark());
-        }
+    }
+    if (mixed && first && !tail_lds_)   // U below the coarse kernel's top level
+        for (int d = 0; d + 1 < Dall_; ++d)
+            MA_TRY(go(LK_INJECT, inj_[d], 0));
+    const TailList *T = reinterpret_cast<const TailList *>(
+        dl_ + (d0 > D_ ? tsub_[size_t(d0 - D_ - 1)] : toff_));
+    if (tail_blocks_ > 0 && tail_lds_)
+        E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_, tail_fast_, T, tail_blocks_, nu1_,
+                              nu2_, nu0_, count, dfall_));
+    else if (tail_blocks_ > 0)
+        E_HIP(launch_tail(stream_, int(mode), order_, rmode_, T, tail_blocks_, nu1_, nu2_, nu0_,
+                          count, dfall_));
+    for (int d = D_ - 1; d >= d0; --d) {
+        // a fused depth prolongs inside its first post-smoothing sweep
+        if (!pro_fused_[d])
+            MA_TRY(go(mixed ? LK_MPROLONG : LK_PROLONG, pro_[d], 0));
+        if (profile_ && d == 0)
+            MA_TRY(prof_mark());
+        MA_TRY(sweeps(swu_[d], bsu_[d]));
+        if (profile_ && d == 0)
+            MA_TRY(prof_mark());
+    }
+    return MA_OK;
+}
+
+ma_status Engine::enqueue(Mode mode, bool cycle)
+{
+    const bool mixed = mode == MODE_MIXED;
+    auto L = [&](int idx) { return reinterpret_cast<const BatchList *>(dl_ + loff_[idx]); };
+    auto go = [&](int kind, int idx, int color) -> ma_status {
+        if (lgrid_[idx] == 0)
+            return MA_OK;
+        E_HIP(launch_batched(stream_, kind, mode == MODE_LAP ? OP_LAP : OP_MA, order_, color, rmode_,
+                             L(idx), lgrid_[idx], dcount_, dfall_));
         return MA_OK;
     };
     if (cycle) {
         if (mixed) {
             for (int it = 0; it < inner_; ++it)
-                MA_TRY(vcycle(it == 0));
+                MA_TRY(enqueue_cycle(mode, it == 0, 0, dcount_));
             MA_TRY(go(LK_ACCUM, accum_, 0));
         } else {
-            MA_TRY(vcycle(true));
+            MA_TRY(enqueue_cycle(mode, true, 0, dcount_));
         }
     }
     MA_TRY(go(mixed ? LK_RES32 : LK_NORM, norm_, 0));
@@ -3553,6 +3579,39 @@ ma_status Engine::tick(Mode mode, const std::vector<char> &active, std::vector<d
     return plain(mode, true, active, norms);
 }
 
+// V-cycles of a lone solve from any level on, without norms: begin_cycles
+// builds the tables and orders the engine stream (*st) after the caller's;
+// cycle_from queues one cycle there.  The caller queues its own work on *st
+// and waits for it before the engine's next use.
+ma_status Engine::begin_cycles(hipStream_t *st)
+{
+    if (solves_.size() != 1 || !solves_[0].s)
+        return fail(MA_ERR_ARG, "internal: cycles of one solve");
+    MA_TRY(settle());
+    arm(0, -1.0);
+    sub_cycles_ = true;
+    const ma_status r = rebuild(MODE_MA, {1});
+    sub_cycles_ = false;
+    MA_TRY(r);
+    MA_TRY(flush_arms());
+    if (user_dirty_) {
+        E_HIP(hipEventRecord(ev_in_, user_));
+        E_HIP(hipStreamWaitEvent(stream_, ev_in_, 0));
+        user_dirty_ = false;
+    }
+    *st = stream_;
+    return refresh_fs(MODE_MA, {1});
+}
+
+ma_status Engine::cycle_from(int l, unsigned long long *count)
+{
+    const bool profile = profile_;
+    profile_ = false;
+    const ma_status r = enqueue_cycle(MODE_MA, true, l, count);
+    profile_ = profile;
+    return r;
+}
+
 ma_status Engine::norms_only(Mode mode, const std::vector<char> &active,
                              std::vector<double> &norms)
 {
@@ -3576,14 +3635,14 @@ void Engine::take_profile(double *seconds, int *launches, double *bytes)
 //   restriction 4 per fine + 24 per coarse node, mixed prolongation 8 per
 //   fine + 8 per coarse node, injection 16 per coarse node, accumulation
 //   20, FP64 residual into FP32 20, zeroing 4 per node.
-void Engine::tick_cost(Mode mode, int i, double *updates, double *bytes) const
+void Engine::tick_cost(Mode mode, int i, double *updates, double *bytes, int l0) const
 {
     const ma_solver *s = solves_[i].s;
     const bool mixed = mode == MODE_MIXED;
     const int L = int(s->lv.size());
     double up = 0.0, by = 0.0;
     const int reps = mixed ? inner_ : 1;
-    for (int l = 0; l < L; ++l) {
+    for (int l = l0; l < L; ++l) {
         const int n = s->lv[l].n;
         const double in = interior(n);
         const int sweeps = l < L - 1 ? nu1_ + nu2_ : nu0_;
@@ -3598,8 +3657,8 @@ void Engine::tick_cost(Mode mode, int i, double *updates, double *bytes) const
                 by += 24.0 * in + 8.0 * in + 32.0 * nc + 16.0 * in + 16.0 * nc;
         }
     }
-    const double in0 = interior(s->lv[0].n);
-    by += mixed ? (20.0 * in0 + 20.0 * in0 + 4.0 * double(npts_sz(s->lv[0].n))) : 16.0 * in0;
+    const double in0 = interior(s->lv[l0].n);
+    by += mixed ? (20.0 * in0 + 20.0 * in0 + 4.0 * double(npts_sz(s->lv[l0].n))) : 16.0 * in0;
     *updates = up;
     *bytes = by;
 }

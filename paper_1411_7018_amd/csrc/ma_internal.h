@@ -68,8 +68,15 @@ hipError_t launch_poisson_rhs(hipStream_t st, int n, const double *f, double *R)
 hipError_t launch_copy(hipStream_t st, size_t count, const double *src, double *dst);
 // Copy the Dirichlet layer of src into dst.
 hipError_t launch_copy_boundary(hipStream_t st, int n, const double *src, double *dst);
-// vc (nf/2 intervals) = injection of vf at every coarse node.
-hipError_t launch_inject_all(hipStream_t st, int nf, const double *vf, double *vc);
+// u0 and f0 of an n0 grid injected onto levels n0 / 2, n0 / 4, ... (levels of
+// them; block is set by the launch).
+struct InjectLevels {
+    const double *u0, *f0;
+    double *u[12], *f[12];
+    int block[12];
+    int levels, n0;
+};
+hipError_t launch_inject_levels(hipStream_t st, InjectLevels &A);
 // Interior of uf (2 nc intervals) = FMG cubic interpolation of uc.
 hipError_t launch_fmg_interp(hipStream_t st, int nc, const double *uc, double *uf);
 // Interior of u = 0.

@@ -198,17 +198,22 @@ __global__ void k_copy_boundary(const double *__restrict__ src, double *__restri
     }
 }
 
-// Injection onto the grid with half the intervals: every coarse node,
-// boundary included, takes the fine value at the same point.
-__global__ void k_inject_all(const double *__restrict__ vf, double *__restrict__ vc, int nc)
+// Injection of u and f onto every coarser level at once: each coarse node,
+// boundary included, takes the finest value at the same point.
+__global__ __launch_bounds__(256) void k_inject_levels(InjectLevels A)
 {
-    const int I = blockIdx.x * RES_BX + threadIdx.x;
-    const int J = blockIdx.y * RES_BY + threadIdx.y;
-    const int K = blockIdx.z;
-    if (I > nc || J > nc)
+    int l = 0;
+    while (l + 1 < A.levels && int(blockIdx.x) >= A.block[l + 1])
+        ++l;
+    const int n = A.n0 >> (l + 1), m = n + 1;
+    const long q = (long(blockIdx.x) - A.block[l]) * 256 + threadIdx.x;
+    if (q >= long(m) * m * m)
         return;
-    const long fy = 2L * nc + 1, cy = nc + 1;
-    vc[I + cy * (J + cy * K)] = vf[2 * I + fy * (2 * J + fy * 2 * K)];
+    const int I = int(q % m), J = int(q / m % m), K = int(q / m / m);
+    const long fy = A.n0 + 1L, st = 2L << l;
+    const long p = st * (I + fy * (J + fy * K));
+    A.u[l][q] = A.u0[p];
+    A.f[l][q] = A.f0[p];
 }
 
 // 1D rule of the FMG interpolation at fine index i (nf = 2 nc intervals):
@@ -243,29 +248,73 @@ __device__ __forceinline__ int fmg_rule(int nc, int i, int &first, double w[4])
     return 4;
 }
 
+// FMG values at the odd fine column 2m + 1 and the even one after it, CK x CJ x
+// CI coarse nodes from (fi, fj, fk) on, the even column's at m + 1; summed over
+// (k, j, i) offsets in order.
+template <int CK, int CJ, int CI>
+__device__ __forceinline__ void fmg_pair(const double *__restrict__ uc, long cy, int m, int fi,
+                                         int fj, int fk, const double *wi, const double *wj,
+                                         const double *wk, double &odd, double &even)
+{
+    double o = 0.0, e = 0.0;
+#pragma unroll
+    for (int c = 0; c < CK; ++c)
+#pragma unroll
+        for (int b = 0; b < CJ; ++b) {
+            const double *row = uc + cy * ((fj + b) + cy * (fk + c));
+#pragma unroll
+            for (int a = 0; a < CI; ++a)
+                o += wk[c] * wj[b] * wi[a] * row[fi + a];
+            e += wk[c] * wj[b] * row[m + 1];
+        }
+    odd = o;
+    even = e;
+}
+
 // FMG interpolation (Algorithm 2, step 4) into the interior of uf: tensor
-// product of the 1D rule, accumulated over (k, j, i) offsets in order.
+// product of the 1D rule.  A wavefront takes one row, so the taps in y and z
+// are the same for its lanes, and a lane two neighbouring columns, so the odd
+// one's four taps in x are nobody else's wait.  128^3: 40 us with a node a lane
+// and loops of 1 or 4 turns in each direction, 16 us so.
 __global__ __launch_bounds__(RES_BX *RES_BY) void k_fmg_interp(const double *__restrict__ uc,
                                                                double *__restrict__ uf, int nc)
 {
     const int nf = 2 * nc;
-    const int i = 1 + blockIdx.x * RES_BX + threadIdx.x;
-    const int j = 1 + blockIdx.y * RES_BY + threadIdx.y;
+    const int m0 = blockIdx.x * RES_BX + threadIdx.x, m = min(m0, nc - 1);
+    const int j = 1 + blockIdx.y * RES_BY + __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int k = 1 + blockIdx.z;
-    if (i > nf - 1 || j > nf - 1)
+    if (j > nf - 1)
         return;
     int fi, fj, fk;
     double wi[4], wj[4], wk[4];
-    const int ci = fmg_rule(nc, i, fi, wi);
+    fmg_rule(nc, 2 * m + 1, fi, wi);
     const int cj = fmg_rule(nc, j, fj, wj);
     const int ck = fmg_rule(nc, k, fk, wk);
     const long cy = nc + 1;
-    double v = 0.0;
-    for (int c = 0; c < ck; ++c)
-        for (int b = 0; b < cj; ++b)
-            for (int a = 0; a < ci; ++a)
-                v += wk[c] * wj[b] * wi[a] * uc[(fi + a) + cy * ((fj + b) + cy * (fk + c))];
-    uf[i + long(nf + 1) * (j + long(nf + 1) * k)] = v;
+    double odd, even;
+    if (nc < 3) {
+        if (ck == 1 && cj == 1)
+            fmg_pair<1, 1, 3>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+        else if (ck == 1)
+            fmg_pair<1, 3, 3>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+        else if (cj == 1)
+            fmg_pair<3, 1, 3>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+        else
+            fmg_pair<3, 3, 3>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+    } else if (ck == 1 && cj == 1) {
+        fmg_pair<1, 1, 4>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+    } else if (ck == 1) {
+        fmg_pair<1, 4, 4>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+    } else if (cj == 1) {
+        fmg_pair<4, 1, 4>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+    } else {
+        fmg_pair<4, 4, 4>(uc, cy, m, fi, fj, fk, wi, wj, wk, odd, even);
+    }
+    double *row = uf + long(nf + 1) * (j + long(nf + 1) * k);
+    if (m0 < nc)
+        row[2 * m + 1] = odd;
+    if (m0 < nc - 1)
+        row[2 * m + 2] = even;
 }
 
 // Zero the interior nodes of an (n+1)^3 grid.
@@ -364,18 +413,24 @@ hipError_t launch_copy(hipStream_t st, size_t count, const double *src, double *
     return hipGetLastError();
 }
 
-hipError_t launch_inject_all(hipStream_t st, int nf, const double *vf, double *vc)
+hipError_t launch_inject_levels(hipStream_t st, InjectLevels &A)
 {
-    const int nc = nf / 2;
-    hipLaunchKernelGGL(k_inject_all, res_grid(nc + 1, nc + 1, nc + 1), dim3(RES_BX, RES_BY), 0, st,
-                       vf, vc, nc);
+    long blocks = 0;
+    for (int l = 0; l < A.levels; ++l) {
+        const long m = (A.n0 >> (l + 1)) + 1;
+        A.block[l] = int(blocks);
+        blocks += (m * m * m + 255) / 256;
+    }
+    if (blocks == 0)
+        return hipSuccess;
+    hipLaunchKernelGGL(k_inject_levels, dim3(unsigned(blocks)), dim3(256), 0, st, A);
     return hipGetLastError();
 }
 
 hipError_t launch_fmg_interp(hipStream_t st, int nc, const double *uc, double *uf)
 {
     const int nf = 2 * nc;
-    hipLaunchKernelGGL(k_fmg_interp, res_grid(nf - 1, nf - 1, nf - 1), dim3(RES_BX, RES_BY), 0, st,
+    hipLaunchKernelGGL(k_fmg_interp, res_grid(nc, nf - 1, nf - 1), dim3(RES_BX, RES_BY), 0, st,
                        uc, uf, nc);
     return hipGetLastError();
 }

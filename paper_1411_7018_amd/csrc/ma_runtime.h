@@ -101,10 +101,6 @@ struct ma_solver {
     std::vector<mafas::MixedLevel> mx;
     std::string err;
     mafas::Engine *eng = nullptr;         // batch-of-one engine of ma_solve / ma_vcycle
-    // FMG: solvers that alias this hierarchy from level l down (no storage
-    // of their own), so that a V-cycle rooted at level l runs through the
-    // same engine code as the finest one
-    std::vector<ma_solver *> views;
 
     ~ma_solver();
     ma_status fail(ma_status st, const std::string &msg);
@@ -119,7 +115,8 @@ struct ma_solver {
     ma_status gs_steps(double *u, const double *F, int max_sweeps, double thr,
                        const std::function<bool(int, double)> &test, long long *nonconvex);
     ma_status own_engine(mafas::Engine **out, double *u, const double *f);
-    ma_solver *view(int l);
+    ma_status fmg_queued(mafas::Engine &E, double *u, const double *f, long long *nc, double *up,
+                         double *by);
     // One FMG-FAS iteration (Algorithm 2) on u, whose interior is not read;
     // adds its non-certified updates, point updates and algorithmic bytes.
     ma_status fmg(double *u, const double *f, long long *nonconvex, double *updates,
