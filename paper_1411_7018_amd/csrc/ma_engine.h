@@ -226,7 +226,8 @@ hipError_t launch_mrrestrict(hipStream_t st, int rmode, const MrList *L, int blo
 // most kTailFastN intervals
 hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
                            const TailList *T, int blocks, int nu1, int nu2, int nu0,
-                           unsigned long long *ncount, unsigned long long *nfall);
+                           unsigned long long *ncount, unsigned long long *nfall,
+                           const NormRing *norm);
 
 struct SolveRef {
     ma_solver *s = nullptr;
@@ -311,7 +312,8 @@ class Engine {
   private:
     ma_status rebuild(Mode mode, const std::vector<char> &active);
     ma_status enqueue(Mode mode, bool cycle);
-    ma_status enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count);
+    ma_status enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count,
+                            const NormRing *norm = nullptr);
     ma_status launch(Mode mode, bool cycle, const std::vector<char> &active, int ticks = 1);
     ma_status collect(std::vector<double> &norms);
     ma_status plain(Mode mode, bool cycle, const std::vector<char> &active,
@@ -353,6 +355,7 @@ class Engine {
     std::vector<int> lng_;                 // grids per list
     std::vector<int> lgrid_;               // blocks per list launch (0: never any grid)
     size_t toff_ = 0;                      // byte offset of the tail table
+    bool norm_in_tail_ = false;            // ticks are one coarse-level launch, norm included
     bool sub_cycles_ = false;              // build tsub_ too
     std::vector<size_t> tsub_;             // byte offsets of the tail tables of cycle_from
     int tail_blocks_ = 0;                  // blocks of the tail launch (0: no tail)

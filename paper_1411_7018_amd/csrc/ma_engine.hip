@@ -610,6 +610,23 @@ __global__ __launch_bounds__(64) void k_fsplit(int n, const double *__restrict__
     }
 }
 
+// The sum of squares of solve `slot` into the host ring, and its stopping test
+// (see k_batched_reduce); k and t: R.seq and R.thr of the slot.
+__device__ __forceinline__ void put_norm(const NormRing &R, int slot, double s, unsigned k,
+                                         double t)
+{
+    const int e = int(k % unsigned(kNormRing)) * kMaxGrids + slot;
+    R.sum[e] = s;
+    R.stamp[e] = k;
+    R.seq[slot] = k + 1u;
+    if (t >= 0.0 && (s <= t || !isfinite(s))) {
+        const unsigned nh = R.stop[0];
+        for (unsigned q = 0; q < nh; ++q)
+            atomicOr(reinterpret_cast<unsigned long long *>(R.base + R.stop[1 + q] + 8),
+                     1ull << slot);
+    }
+}
+
 // Fixed-order per-grid sum of the partials of a norm list: thread t adds
 // partials t, t + 1024, ... in order, then a fixed shuffle tree per wave and
 // the 16 wave sums in order.  The sum of solve `slot` goes to the pinned
@@ -655,19 +672,7 @@ __global__ __launch_bounds__(1024) void k_batched_reduce(const BatchList *__rest
         double s = 0.0;
         for (int w = 0; w < 16; ++w)
             s += part[w];
-        const int slot = G.slot;
-        const unsigned k = R.seq[slot];
-        const int e = int(k % unsigned(kNormRing)) * kMaxGrids + slot;
-        R.sum[e] = s;
-        R.stamp[e] = k;
-        R.seq[slot] = k + 1u;
-        const double t = R.thr[slot];
-        if (t >= 0.0 && (s <= t || !isfinite(s))) {
-            const unsigned nh = R.stop[0];
-            for (unsigned q = 0; q < nh; ++q)
-                atomicOr(reinterpret_cast<unsigned long long *>(R.base + R.stop[1 + q] + 8),
-                         1ull << slot);
-        }
+        put_norm(R, G.slot, s, R.seq[G.slot], R.thr[G.slot]);
     }
 }
 
@@ -1799,7 +1804,7 @@ struct TailSize {
 template <int OP, int RMODE>
 __global__ __launch_bounds__(kTailLdsThreads) void k_tail_lds4(
     const TailList *__restrict__ T, int nu1, int nu2, int nu0,
-    unsigned long long *__restrict__ ncount)
+    unsigned long long *__restrict__ ncount, NormRing ring)
 {
     __shared__ double S[kTailLdsDoubles];
     if (int(blockIdx.x) >= T->nsolves)
@@ -1808,6 +1813,9 @@ __global__ __launch_bounds__(kTailLdsThreads) void k_tail_lds4(
     const int slot = E.lv[0].sw.slot;
     if ((T->stopped >> slot) & 1ull)
         return;
+    // read here, where no thread waits for them
+    const unsigned seq = ring.sum ? ring.seq[slot] : 0u;
+    const double thr = ring.sum ? ring.thr[slot] : -1.0;
     TailCtx X;
     X.S = S;
     X.tid = int(threadIdx.x);
@@ -1929,17 +1937,77 @@ __global__ __launch_bounds__(kTailLdsThreads) void k_tail_lds4(
             gu[q] = u0[row * P0 + (i & 1) * H0 + (i >> 1)];
         }
     }
+
+    // ---- the norm of the result, when the launch is the whole cycle: squares
+    // summed in the order of LK_NORM and k_batched_reduce (a lane per column of
+    // a row, over kNormPlanes planes; then the row pieces), so the sum does not
+    // depend on which kernel takes it.  A wavefront takes a row piece: 16
+    // columns x 4 planes, twice, then a column's eight residuals through LDS.
+    // n = 16: 9 us and two gaps as two launches, 4.4 us so.
+    if (ring.sum == nullptr)
+        return;
+    constexpr int kPieces = (kTailFastN - 1) * ((kTailFastN - 1 + kNormPlanes - 1) / kNormPlanes);
+    static_assert((kTailFastN + 1) * (kTailFastN + 1) * (tail_pitch(kTailFastN) + kTailFastN + 1) +
+                              NT / 64 * 128 + 64 <= kTailLdsDoubles &&
+                      kPieces <= 64 && kTailFastN - 1 <= 16 && kNormPlanes == 8,
+                  "the residuals and row sums fit behind u and b");
+    const int mi = n0 - 1, PZ0 = m0 * P0, gz = (mi + kNormPlanes - 1) / kNormPlanes;
+    const double s0 = double(n0) * double(n0);
+    const double *b0 = S + m0 * m0 * P0;
+    double *part = S + m0 * m0 * P0 + N0, *r = part + 64 + (tid >> 6) * 128;
+    const int lane = tid & 63, ci = lane & 15, kk = lane >> 4;
+    const int i = 1 + min(ci, mi - 1), x = (i & 1) * H0 + (i >> 1);
+    const int xw = (i & 1) ? i >> 1 : H0 + (i >> 1) - 1;   // column i - 1; i + 1 is next to it
+    for (int q = tid >> 6; q < mi * gz; q += NT / 64) {
+        const int j = 1 + q % mi, k0 = 1 + q / mi * kNormPlanes;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k0 + kk + 4 * h, row = min(k, n0 - 1) * m0 + j;
+            const double *C = u0 + row * P0 + x, *W = u0 + row * P0 + xw;
+            double V[3][9];   // the planes below, at and above
+#pragma unroll
+            for (int z = 0; z < 3; ++z)
+#pragma unroll
+                for (int y = 0; y < 3; ++y) {
+                    const int o = (z - 1) * PZ0 + (y - 1) * P0;
+                    V[z][3 * y] = W[o];
+                    V[z][3 * y + 1] = C[o];
+                    V[z][3 * y + 2] = W[o + 1];
+                }
+            const double rv =
+                resid_win<OP>(V[0] + 4, V[1] + 4, V[2] + 4, s0, b0[row * m0 + x]);
+            r[lane + 64 * h] = k < n0 && ci < mi ? rv : 0.0;
+        }
+        lds_wave_order();
+        double acc = 0.0;
+#pragma unroll
+        for (int k = 0; k < kNormPlanes; ++k) {
+            const double rv = r[16 * k + ci];
+            acc = fma(rv, rv, acc);
+        }
+        lds_wave_order();
+        for (int off = 8; off > 0; off >>= 1)   // lanes 16 on would add zeros
+            acc += __shfl_down(acc, off, 16);
+        if (lane == 0)
+            part[q] = acc;
+    }
+    lds_barrier();
+    if (tid < 64) {
+        const double v = wave_sum64(tid < mi * gz ? part[tid] : 0.0);
+        if (tid == 0)
+            put_norm(ring, slot, v, seq, thr);
+    }
 }
 
 template <int OP, int RMODE>
 hipError_t launch_tail_lds_t(hipStream_t st, int order, bool fast, const TailList *T, int blocks,
-                             int nu1, int nu2, int nu0, unsigned long long *nc)
+                             int nu1, int nu2, int nu0, unsigned long long *nc, const NormRing &ring)
 {
     const dim3 grid(blocks), block(kTailLdsThreads);
     if (order == 1)
         hipLaunchKernelGGL((k_tail_lds<OP, 1, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
     else if (fast)
-        hipLaunchKernelGGL((k_tail_lds4<OP, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
+        hipLaunchKernelGGL((k_tail_lds4<OP, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc, ring);
     else
         hipLaunchKernelGGL((k_tail_lds<OP, 0, RMODE>), grid, block, 0, st, T, nu1, nu2, nu0, nc);
     return hipGetLastError();
@@ -2191,19 +2259,22 @@ hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc, 
 
 hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool fast,
                            const TailList *T, int blocks, int nu1, int nu2, int nu0,
-                           unsigned long long *nc, unsigned long long *nf)
+                           unsigned long long *nc, unsigned long long *nf, const NormRing *norm)
 {
     if (blocks <= 0 || blocks > kMaxGrids)
         return hipErrorInvalidValue;
+    if (norm && (order != 0 || !fast || mode == Engine::MODE_MIXED))
+        return hipErrorInvalidValue;
+    const NormRing ring = norm ? *norm : NormRing{};
     if (mode == Engine::MODE_MIXED)
         return rmode == 0 ? launch_tail_mixed_t<0>(st, order, T, blocks, nu1, nu2, nu0, nc, nf)
                           : launch_tail_mixed_t<1>(st, order, T, blocks, nu1, nu2, nu0, nc, nf);
     const bool ma = mode == Engine::MODE_MA;
     if (rmode == 0)
-        return ma ? launch_tail_lds_t<OP_MA, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc)
-                  : launch_tail_lds_t<OP_LAP, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc);
-    return ma ? launch_tail_lds_t<OP_MA, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc)
-              : launch_tail_lds_t<OP_LAP, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc);
+        return ma ? launch_tail_lds_t<OP_MA, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc, ring)
+                  : launch_tail_lds_t<OP_LAP, 0>(st, order, fast, T, blocks, nu1, nu2, nu0, nc, ring);
+    return ma ? launch_tail_lds_t<OP_MA, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc, ring)
+              : launch_tail_lds_t<OP_LAP, 1>(st, order, fast, T, blocks, nu1, nu2, nu0, nc, ring);
 }
 
 // ---------------------------------------------------------------------------
@@ -2760,6 +2831,11 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             }
         }
     };
+    // a cycle that is one coarse-level launch takes its norm there too (again
+    // over all solves)
+    norm_in_tail_ = !mixed && order_ == 0 && tail_lds_ && tail_fast_;
+    for (int i = 0; i < S; ++i)
+        norm_in_tail_ &= !solves_[i].s || multiblock_levels(i) == 0;
     toff_ = hbuf_.size();
     hbuf_.resize(toff_ + tail_bytes(S), 0);
     {
@@ -3073,7 +3149,8 @@ ma_status Engine::prof_mark()
 
 // A V-cycle from depth d0 down and up again on the engine stream; first: the
 // first of a tick; count: where its non-convex updates are counted.
-ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count)
+ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count,
+                                const NormRing *norm)
 {
     const bool mixed = mode == MODE_MIXED;
     const int op = mode == MODE_LAP ? OP_LAP : OP_MA;
@@ -3135,7 +3212,7 @@ ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long lon
         dl_ + (d0 > D_ ? tsub_[size_t(d0 - D_ - 1)] : toff_));
     if (tail_blocks_ > 0 && tail_lds_)
         E_HIP(launch_tail_lds(stream_, int(mode), order_, rmode_, tail_fast_, T, tail_blocks_, nu1_,
-                              nu2_, nu0_, count, dfall_));
+                              nu2_, nu0_, count, dfall_, norm));
     else if (tail_blocks_ > 0)
         E_HIP(launch_tail(stream_, int(mode), order_, rmode_, T, tail_blocks_, nu1_, nu2_, nu0_,
                           count, dfall_));
@@ -3155,6 +3232,8 @@ ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long lon
 ma_status Engine::enqueue(Mode mode, bool cycle)
 {
     const bool mixed = mode == MODE_MIXED;
+    const NormRing ring{dnorm_, dstamp_, dseq_, dthr_, dl_,
+                        reinterpret_cast<const unsigned *>(dl_ + stoff_)};
     auto L = [&](int idx) { return reinterpret_cast<const BatchList *>(dl_ + loff_[idx]); };
     auto go = [&](int kind, int idx, int color) -> ma_status {
         if (lgrid_[idx] == 0)
@@ -3169,15 +3248,16 @@ ma_status Engine::enqueue(Mode mode, bool cycle)
                 MA_TRY(enqueue_cycle(mode, it == 0, 0, dcount_));
             MA_TRY(go(LK_ACCUM, accum_, 0));
         } else {
-            MA_TRY(enqueue_cycle(mode, true, 0, dcount_));
+            MA_TRY(enqueue_cycle(mode, true, 0, dcount_, norm_in_tail_ ? &ring : nullptr));
+            if (norm_in_tail_)
+                return MA_OK;
         }
     }
     MA_TRY(go(mixed ? LK_RES32 : LK_NORM, norm_, 0));
     // one block per solve of the engine (blocks past the list's grids
     // return): the launch shape does not change when solves pause or stop
     E_HIP(launch_batched_reduce(stream_, L(norm_), int(solves_.size()), partials_,
-                                NormRing{dnorm_, dstamp_, dseq_, dthr_, dl_,
-                                         reinterpret_cast<const unsigned *>(dl_ + stoff_)}));
+                                ring));
     return MA_OK;
 }
 
@@ -3191,7 +3271,7 @@ std::vector<int> Engine::shape() const
     s.push_back(int(stride_));
     s.push_back(int(toff_));
     s.push_back(tail_blocks_);
-    s.push_back((tail_lds_ ? 1 : 0) + (tail_fast_ ? 2 : 0));
+    s.push_back((tail_lds_ ? 1 : 0) + (tail_fast_ ? 2 : 0) + (norm_in_tail_ ? 4 : 0));
     s.push_back(strip_rows_);
     s.push_back(int(loff_.size()));
     s.insert(s.end(), lgrid_.begin(), lgrid_.end());
@@ -3235,7 +3315,9 @@ ma_status Engine::launch(Mode mode, bool cycle, const std::vector<char> &active,
         MA_TRY(refresh_fs(mode, active));
     const int m = int(mode) + (profile_ ? 3 : 0) + (ticks == 2 ? 6 : 0);
     size_t nev = 0;
-    if (cycle && graphs_) {
+    // a tick of one kernel goes without a graph, whose launch leaves the stream
+    // idle for longer (a 17^3 solve of 18 ticks: 1090 -> 994 us)
+    if (cycle && graphs_ && !norm_in_tail_) {
         if (gseg_[m].empty() || graph_dl_[m] != dl_ || graph_shape_[m] != shape())
             MA_TRY(capture(m, mode, ticks));
         // segment k is followed by timing event k (profiled form only)
