@@ -56,10 +56,16 @@ namespace mafas {
 template <int TX, int TY>
 struct ZsShape {
     static constexpr int H = 4;              // halo loaded around the column
-    static constexpr int LX = TX + 2 * H;    // LDS row length
+    static constexpr int LX = TX + 2 * H;    // columns loaded
     static constexpr int LY = TY + 2 * H;    // LDS rows per plane
-    static constexpr int HW = LX / 2;        // one parity half of a row
-    static constexpr int PL = LX * LY;       // doubles per plane
+    // A row holds its even columns, then from HW on the odd ones.  HW is 8 mod
+    // 16 doubles, so the two halves of 16 columns as they are loaded go to
+    // different banks, and the pitch is odd, which spreads the rows of the
+    // narrow update items (see node_of) over the banks.
+    static constexpr int HW = (LX / 2 + 7) / 16 * 16 + 8;
+    static constexpr int LP = (HW + LX / 2) | 1;   // row pitch
+    static constexpr int PE = LX * LY;       // elements of a plane
+    static constexpr int PL = LP * LY;       // doubles of a plane
     static constexpr int R = 10;             // planes in the ring
     static constexpr int NL = PL * R;        // doubles in LDS
     // colour c covers TX/2 + e columns and TY/2 + e rows of its colour's
@@ -88,6 +94,24 @@ struct ZsShape {
                         : pad64(count(0) + count(1)) + count(2);
     }
     static constexpr int items = first(3) + count(3);
+    // Column and row of item `local` of a colour grown by e: the first TX / 2
+    // columns row by row, then the e columns beside them.  A pass over LDS takes
+    // 16 lanes; with 16 columns a row they read one row, where rows of 16 + e
+    // (every item row by row) straddled two whose banks overlap.  Bank
+    // conflicts of the 32 x 24 reads: 1.63 cycles a pass, with this order and
+    // pitch 1.07.  A sweep, us: n = 384: 618 -> 595, 256 (32 x 26): 185 -> 177.
+    __device__ static __forceinline__ void node_of(int local, int e, int &col, int &r)
+    {
+        constexpr int W = TX / 2;
+        const int nr = TY / 2 + e, m = W * nr, rest = local - m;
+        if (local < m) {
+            col = local % W;
+            r = local / W;
+        } else {
+            r = e == 0 ? 0 : rest / e;
+            col = W + rest - r * e;
+        }
+    }
     static constexpr size_t lds_bytes() { return size_t(NL) * sizeof(double); }
     // coarse-correction ring of a prolonging sweep: the footprint's first
     // x is odd (1 + tx TX - H), so its coarse nodes span LX / 2 + 2 columns
@@ -112,8 +136,8 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
                                             unsigned long long *__restrict__ ncount)
 {
     using S = ZsShape<TX, TY>;
-    constexpr int LX = S::LX, HW = S::HW, PL = S::PL, H = S::H, R = S::R;
-    constexpr int KL = (PL + NT - 1) / NT;        // plane elements per thread
+    constexpr int LX = S::LX, LP = S::LP, HW = S::HW, PE = S::PE, PL = S::PL, H = S::H, R = S::R;
+    constexpr int KL = (PE + NT - 1) / NT;        // plane elements per thread
     constexpr int MI = (S::items + NT - 1) / NT;  // update items per thread and step
     constexpr int SX = TX + 2, SY = TY + 2;       // store bound (with Dirichlet layer)
     constexpr int KS = (SX * SY + NT - 1) / NT;
@@ -141,9 +165,9 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
         const int el = tid + k * NT;
         const int ly = el / LX, lx = el - (el / LX) * LX;
         const int gx = lx0 + lx, gy = ly0 + ly;
-        const bool in = el < PL && gx >= 0 && gx <= n && gy >= 0 && gy <= n;
+        const bool in = el < PE && gx >= 0 && gx <= n && gy >= 0 && gy <= n;
         gofs[k] = in ? unsigned(gx + sy * gy) * 8u : kBufOob;
-        lofs[k] = el < PL ? ly * LX + (lx & 1) * HW + (lx >> 1) : -1;
+        lofs[k] = el < PE ? ly * LP + (lx & 1) * HW + (lx >> 1) : -1;
     }
     const unsigned plane_bytes = unsigned(sz) * 8u;
     auto slot = [&](int p) { return ((p + 2 * R) % R) * PL; };   // p >= -2R
@@ -180,7 +204,7 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
             const int el = tid + k * NT;
             const int ly = el / LX, lx = el - (el / LX) * LX;
             const int gx = lx0 + lx, gy = ly0 + ly;
-            const bool inxy = el < PL && gx >= 1 && gx <= n - 1 && gy >= 1 && gy <= n - 1;
+            const bool inxy = el < PE && gx >= 1 && gx <= n - 1 && gy >= 1 && gy <= n - 1;
             fco[k] = inxy ? ((gy >> 1) - cya) * CX + ((gx >> 1) - cxa) : 0;
             fpar[k] = inxy ? 4 | (gx & 1) | ((gy & 1) << 1) : 0;
         }
@@ -332,8 +356,8 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
         const int local = q - (cc == 0 ? S::first(0) : cc == 1 ? S::first(1)
                                : cc == 2 ? S::first(2) : S::first(3));
         const int e = 3 - cc, c0 = cc & 1, c1 = cc >> 1;
-        const int nc = TX / 2 + e;
-        const int r = local / nc, col = local - (local / nc) * nc;
+        int r, col;
+        S::node_of(c < 0 ? 0 : local, e, col, r);
         const int xa = x0 - e, ya = y0 - e;
         ic[m] = c;
         plo[m] = max(1, z0 - e);
@@ -344,7 +368,7 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
             const int i = xa + ((xa + c1 + sp) & 1) + 2 * col;
             const int j = ya + ((ya + c1 + sp + c0) & 1) + 2 * r;
             const int lx = i - lx0;
-            lio[m][sp] = (j - ly0) * LX + (lx & 1) * HW + (lx >> 1);
+            lio[m][sp] = (j - ly0) * LP + (lx & 1) * HW + (lx >> 1);
             // byte offset of the node in plane P = s - 2c from plane s - 6
             gio[m][sp] = unsigned(i + sy * j + (6 - 2 * cc) * sz) * 8u;
             okxy[m][sp] = c >= 0 && i >= max(1, xa) && i <= min(n - 1, x1 - 1 + e) &&
@@ -407,14 +431,14 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
             constexpr int xp = odd ? 1 - HW : HW;
             constexpr int xm = odd ? -HW : HW - 1;
             if (OP == OP_MA) {
-                const Hess h = hessian3(D, C, U, xp, xm, LX, G.s, G.s4);
+                const Hess h = hessian3(D, C, U, xp, xm, LP, G.s, G.s4);
                 bool nc = false;
                 C[0] = ma_point_update(h, C[0], f, G.hk, nc);
                 // recomputed halo nodes are counted by their own column / chunk
                 if (nc)
                     nown += own[m][sp] && P >= z0 && P < z1;
             } else {
-                const double lap = laplacian3(D, C, U, xp, xm, LX, G.s);
+                const double lap = laplacian3(D, C, U, xp, xm, LP, G.s);
                 C[0] = lap_point_update(lap, C[0], f, G.hk);
             }
         };
@@ -447,7 +471,7 @@ __device__ __forceinline__ void zsweep_tile(const FsGrid &G, int tile, double *_
         const bool in = el < SX * SY && gx < xs1 && gy < ys1;
         const int lx = gx - lx0;
         sofs[k] = in ? unsigned(gx + sy * gy) * 8u : kBufOob;
-        sl[k] = in ? (gy - ly0) * LX + (lx & 1) * HW + (lx >> 1) : 0;
+        sl[k] = in ? (gy - ly0) * LP + (lx & 1) * HW + (lx >> 1) : 0;
     }
     auto store_plane = [&](int q, int so) {
         const double *b = su + so;
