@@ -154,12 +154,12 @@ enum ListKind {
     LK_SWEEP,      // p: u, F                        items: rows of one colour
     LK_RESIDUAL,   // p: u, F, r                     items: interior rows
     LK_RESTRICT,   // p: uf, rf, wc, uc, bc          items: coarse rows (n = fine n)
-    LK_PROLONG,    // p: uf, uc, wc                  items: fine interior rows
+    LK_PROLONG,    // p: uf, uc, wc                  items: rows of coarse cells
     LK_NORM,       // p: u, F, partials              items: interior rows x plane chunks
     LK_MSWEEP,     // p: d, b, U, H[3]               items: rows of one colour
     LK_MRESIDUAL,  // p: d, b, U, r                  items: interior rows
     LK_MRESTRICT,  // p: df, rf, Uc, wc, dc, bc      items: coarse rows (n = fine n)
-    LK_MPROLONG,   // p: df, dc, wc                  items: fine interior rows
+    LK_MPROLONG,   // p: df, dc, wc                  items: rows of coarse cells
     LK_INJECT,     // p: Uf, Uc                      items: coarse rows (n = fine n)
     LK_ACCUM,      // p: u64, d                      items: interior rows
     LK_RES32,      // p: u64, f, b0, partials, H[3], d   items: as LK_NORM

@@ -192,66 +192,90 @@ __device__ __forceinline__ void prolong_node(int nf, int i, int j, int k, PF uf,
     uf[p] += d;
 }
 
-// The same prolongation for the 64 fine nodes i = 1 + 64 bx + t of one row
-// kernel item, every lane of the wave taking part.  Lane t loads the coarse
-// column its node starts from (i >> 1); a node with odd i also needs the next
-// column, which is the column lane t + 1 starts from, so it takes that
-// difference from lane t + 1 instead of loading it.  Half the coarse loads of
-// prolong_node, and the same terms summed in the same order.
-template <int NJ, int NK, typename T, typename PC>
-__device__ __forceinline__ T prolong_sum_row(long cy, long cz, int X, int J0, int K0, int oi, T w,
-                                             PC uc, PC wc)
+// The value of v in the next lane; e in lane 63.  Every lane active.
+template <typename T>
+__device__ __forceinline__ T lane_after(T v, T e)
 {
-    T a[NK * NJ], b[NK * NJ];
-#pragma unroll
-    for (int c = 0; c < NK; ++c)
-#pragma unroll
-        for (int m = 0; m < NJ; ++m) {
-            const long q = X + cy * (J0 + m) + cz * (K0 + c);
-            a[c * NJ + m] = uc[q];
-            b[c * NJ + m] = wc[q];
-        }
-    T d = T(0);
-#pragma unroll
-    for (int c = 0; c < NK; ++c)
-#pragma unroll
-        for (int m = 0; m < NJ; ++m) {
-            const T e0 = a[c * NJ + m] - b[c * NJ + m];
-            const T e1 = __shfl_down(e0, 1, 64);
-            d += w * e0;
-            if (oi)
-                d += w * e1;
-        }
-    return d;
+    constexpr int kShl1 = 0x130;   // DPP wave_shl:1
+    if constexpr (sizeof(T) == 8) {
+        const long long vb = __builtin_bit_cast(long long, v), eb = __builtin_bit_cast(long long, e);
+        const int lo = __builtin_amdgcn_update_dpp(int(eb), int(vb), kShl1, 0xf, 0xf, false);
+        const int hi =
+            __builtin_amdgcn_update_dpp(int(eb >> 32), int(vb >> 32), kShl1, 0xf, 0xf, false);
+        return __builtin_bit_cast(T, (static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+    } else {
+        return __builtin_bit_cast(
+            T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, e), __builtin_bit_cast(int, v),
+                                           kShl1, 0xf, 0xf, false));
+    }
 }
 
+// The same prolongation of the eight fine nodes 2X, 2X + 1 | 2J, 2J + 1 | 2K,
+// 2K + 1 of coarse cell (X, J, K), X = 64 bx + t, by lane t, every lane taking
+// part: the cell's corners at X come from memory, those at X + 1 from the next
+// lane (lane 63 and the last cell load theirs).  Each node's terms and order
+// are those of prolong_node.
+// Bound by HBM on large grids; a lane a fine node took 4.5 coarse loads for
+// each.  Fine n = 128, us: 15 -> 8.5, 298: 160 -> 99; FP32, 256: 94 -> 33.
 template <typename T>
-__device__ __forceinline__ void prolong_row(const GridItem &G, int bx, int t, int j, int k)
+__device__ __forceinline__ void prolong_cell(const GridItem &G, int bx, int t, int J, int K)
 {
+    using Pair = T __attribute__((ext_vector_type(2), aligned(sizeof(T))));
     const int nf = G.n, nc = nf / 2;
     const long sy = nf + 1, sz = sy * sy, cy = nc + 1, cz = cy * cy;
-    const int i = 1 + bx * 64 + t;
-    const int oi = i & 1, oj = j & 1, ok = k & 1;
-    const int J0 = j >> 1, K0 = k >> 1;
-    // i >> 1; clamped only for lanes past the end of the row, whose sums
-    // are not used
-    const int X = min(bx * 32 + (t >> 1) + (t & 1), nc);
-    const T one = T(1), half = T(0.5);
-    const T wi = oi ? half : one, wj = oj ? half : one, wk = ok ? half : one;
-    const T w = wk * wj * wi;
+    const int X0 = bx * 64 + t, X = min(X0, nc - 1);
+    const bool edge = t == 63 || X0 >= nc - 1;
     const auto uc = gptr<const T>(G.p[1]);
     const auto wc = gptr<const T>(G.p[2]);
-    T d;
-    if (oj == 0 && ok == 0)
-        d = prolong_sum_row<1, 1, T>(cy, cz, X, J0, K0, oi, w, uc, wc);
-    else if (ok == 0)
-        d = prolong_sum_row<2, 1, T>(cy, cz, X, J0, K0, oi, w, uc, wc);
-    else if (oj == 0)
-        d = prolong_sum_row<1, 2, T>(cy, cz, X, J0, K0, oi, w, uc, wc);
-    else
-        d = prolong_sum_row<2, 2, T>(cy, cz, X, J0, K0, oi, w, uc, wc);
-    if (i <= nf - 1)
-        gptr<T>(G.p[0])[i + sy * j + sz * k] += d;
+    const long q = X + cy * J + cz * K;
+    T e[2][2], f[2][2], g[2][2];
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+            e[z][y] = uc[q + cy * y + cz * z] - wc[q + cy * y + cz * z];
+    if (edge) {
+#pragma unroll
+        for (int z = 0; z < 2; ++z)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+                g[z][y] = uc[q + 1 + cy * y + cz * z] - wc[q + 1 + cy * y + cz * z];
+    }
+#pragma unroll
+    for (int z = 0; z < 2; ++z)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) {
+            f[z][y] = lane_after(e[z][y], e[z][y]);
+            if (edge)
+                f[z][y] = g[z][y];
+        }
+    const auto uf = gptr<T>(G.p[0]);
+#pragma unroll
+    for (int ok = 0; ok < 2; ++ok)
+#pragma unroll
+        for (int oj = 0; oj < 2; ++oj) {
+            const int j = 2 * J + oj, k = 2 * K + ok;
+            if (j == 0 || k == 0 || X0 >= nc)
+                continue;
+            const T wk = ok ? T(0.5) : T(1), wj = oj ? T(0.5) : T(1);
+            const T w0 = wk * wj, w1 = wk * wj * T(0.5);
+            T d0 = T(0), d1 = T(0);
+#pragma unroll
+            for (int z = 0; z <= ok; ++z)
+#pragma unroll
+                for (int y = 0; y <= oj; ++y) {
+                    d0 += w0 * e[z][y];
+                    d1 += w1 * e[z][y];
+                    d1 += w1 * f[z][y];
+                }
+            Pair __attribute__((address_space(1))) *p =
+                (Pair __attribute__((address_space(1))) *)(uf + (2 * X + sy * j + sz * k));
+            Pair v = *p;
+            if (X > 0)   // column 0 is the boundary
+                v.x += d0;
+            v.y += d1;
+            *p = v;
+        }
 }
 
 // The same phases on a grid of a device table (global memory).
@@ -533,9 +557,9 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
     } else if (KIND == LK_PROLONG || KIND == LK_MPROLONG) {
         // every lane takes part (lanes exchange coarse differences)
         if (KIND == LK_PROLONG)
-            prolong_row<double>(G, bx, t, 1 + by, 1 + bz);
+            prolong_cell<double>(G, bx, t, by, bz);
         else
-            prolong_row<float>(G, bx, t, 1 + by, 1 + bz);
+            prolong_cell<float>(G, bx, t, by, bz);
     } else if (KIND == LK_ACCUM) {
         const int i = 1 + bx * 64 + t, j = 1 + by, k = 1 + bz;
         if (i <= n - 1) {
@@ -1166,7 +1190,7 @@ __global__ __launch_bounds__(NT) void k_mrrestrict(const MrList *__restrict__ Ls
 }
 
 // Prolongation of one grid passed by value, one wavefront per work item (rows
-// in y-strips walked along z, as in a batched launch).
+// of cells in y-strips walked along z, as in a batched launch).
 __global__ __launch_bounds__(64) void k_prolong1(GridItem G)
 {
     const int it = tile_of_block(int(blockIdx.x), int(gridDim.x));
@@ -1176,7 +1200,7 @@ __global__ __launch_bounds__(64) void k_prolong1(GridItem G)
     rest /= G.w;
     const int bz = rest % G.gz, by = (rest / G.gz) * G.w + jj;
     if (by < G.gy)
-        prolong_row<double>(G, bx, int(threadIdx.x), 1 + by, 1 + bz);
+        prolong_cell<double>(G, bx, int(threadIdx.x), by, bz);
 }
 
 // Coarse levels of the mixed inner problem in LDS (top level n <= kTailFastN):
@@ -2103,6 +2127,12 @@ void item_dims(int kind, int order, int n, int *gx, int *gy, int *gz)
         *gx = (n - 1 + 63) / 64;
         *gy = n - 1;
         *gz = (n - 1 + kNormPlanes - 1) / kNormPlanes;
+        break;
+    case LK_PROLONG:
+    case LK_MPROLONG:  // rows of coarse cells
+        *gx = (n / 2 + 63) / 64;
+        *gy = n / 2;
+        *gz = n / 2;
         break;
     default:  // interior rows
         *gx = (n - 1 + 63) / 64;
