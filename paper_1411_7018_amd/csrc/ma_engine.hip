@@ -17,6 +17,7 @@
 // independent, so the order in which they are visited does not matter.
 #include "ma_engine.h"
 #include "ma_mixed_device.h"
+#include "ma_walk.h"
 
 #include <algorithm>
 #include <cmath>
@@ -468,46 +469,23 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
             }
         }
     } else if (KIND == LK_NORM || KIND == LK_RES32) {
-        // Squared residuals of a 64-node row segment over kNormPlanes planes:
-        // each lane walks along z keeping the 3x3 neighbourhoods of three
-        // planes in registers, 9 loads per node instead of the 19 of the
-        // gathered stencil.  LK_RES32 also stores what the next outer step of
-        // the mixed form takes from the same stencil: the residual in FP32,
-        // H = D^2 u (G.p[4]; null when the level has no row kernels) and the
-        // zero start of the correction.
+        // Squared residuals of a 64-node row segment over kNormPlanes planes,
+        // walked along z (ma_walk.h).  LK_RES32 also stores what the next outer
+        // step of the mixed form takes from the same stencil: the residual in
+        // FP32, H = D^2 u (G.p[4]; null when the level has no row kernels) and
+        // the zero start of the correction.  With nine loads a node and one
+        // plane in flight, us: n = 128: 12.4, 384: 314; so: 11.3, 302.
         const int i = 1 + bx * 64 + t, j = 1 + by;
-        const int k0 = 1 + bz * kNormPlanes, k1 = min(k0 + kNormPlanes, n);
-        const int ic = min(i, n - 1);
-        const auto u = gptr<const double>(G.p[0]);
-        const auto F = gptr<const double>(G.p[1]);
-        double P0[9], P1[9], P2[9];
-        auto load = [&](double *P, int kk) {
-            const long b0 = ic + sy * j + sz * kk;
-#pragma unroll
-            for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-                for (int dx = -1; dx <= 1; ++dx)
-                    P[(dy + 1) * 3 + (dx + 1)] = u[b0 + dx + sy * dy];
-        };
-        // the next plane's loads are issued before this plane's residual,
-        // so each iteration's arithmetic overlaps the loads of the next
-        double P3[9];
-        load(P0, k0 - 1);
-        load(P1, k0);
-        load(P2, k0 + 1);   // k0 + 1 <= k1 <= n
-        double fc = F[ic + sy * j + sz * k0];
+        const int k0 = 1 + bz * kNormPlanes;
         double acc = 0.0;
-        for (int k = k0; k < k1; ++k) {
-            double fn = 0.0;
-            const bool more = k + 1 < k1;   // uniform across the wavefront
-            if (more) {
-                load(P3, k + 2);
-                fn = F[ic + sy * j + sz * (k + 1)];
-            }
+        walk_planes<kNormPlanes>(gptr<const double>(G.p[0]), gptr<const double>(G.p[1]), n, i, j,
+                                 k0, min(k0 + kNormPlanes, n), t,
+                                 [&](int k, const PlaneTerms &C, const PlaneTerms &D,
+                                     const PlaneTerms &U, double f) {
             double rv;
             if (KIND == LK_RES32) {
-                const Hess h = hessian3(P0 + 4, P1 + 4, P2 + 4, 1, -1, 3, G.s, 0.25 * G.s);
-                rv = fc - det3(h);
+                const Hess h = hessian_planes(D, C, U, G.s, 0.25 * G.s);
+                rv = f - det3(h);
                 if (i <= n - 1) {
                     const long p = i + sy * j + sz * k;
                     const long q = G.p[4] ? split_at(i, j, k, n) : p;
@@ -519,19 +497,14 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
                         gptr<Float2>(G.p[6])[q] = Float2{float(h.xz), float(h.yz)};
                     }
                 }
+            } else if (OP == OP_MA) {
+                rv = f - det3(hessian_planes(D, C, U, G.s, 0.25 * G.s));
             } else {
-                rv = resid_win<OP>(P0 + 4, P1 + 4, P2 + 4, G.s, fc);
+                rv = f - laplacian_planes(D, C, U, G.s);
             }
             if (i <= n - 1)
-                acc += rv * rv;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                P0[q] = P1[q];
-                P1[q] = P2[q];
-                P2[q] = P3[q];
-            }
-            fc = fn;
-        }
+                acc = fma(rv, rv, acc);
+        });
         const double sum = wave_sum64(acc);
         if (t == 0)
             static_cast<double *>(G.p[KIND == LK_NORM ? 2 : 3])[G.pbase + bx +

@@ -2,6 +2,7 @@
 // the linear 7-point V-cycle used for the initial guess.  All grid functions
 // are (n+1)^3 x-fastest arrays; Dirichlet nodes are read, never written.
 #include "ma_device.h"
+#include "ma_walk.h"
 #include "ma_internal.h"
 #include "ma_runtime.h"
 
@@ -84,10 +85,9 @@ __global__ __launch_bounds__(64) void k_sweep_color(double *__restrict__ u,
 // ---------------------------------------------------------------------------
 // Residual r = F - S(u) (0 on the boundary; r may be null) and per-block sums
 // of r^2 over interior nodes.  A wavefront takes 64 columns of one row and
-// walks kResPlanes planes along z with the 3 x 3 neighbourhoods of three
-// planes in registers: 9 loads a node instead of the 19 of the gathered
-// stencil, the next plane's issued before this plane's residual.  Bound by
-// HBM; 298^3 with r: 375 us as a gather and a separate clear of r, 250 us so.
+// walks kResPlanes planes along z (ma_walk.h).  Bound by HBM; 298^3 with r: 375
+// us as a gather and a separate clear of r, 250 us with nine loads a node and a
+// plane in flight, 204 us so.
 // ---------------------------------------------------------------------------
 constexpr int kResPlanes = 8;
 
@@ -104,43 +104,21 @@ __global__ __launch_bounds__(RES_BX *RES_BY) void k_residual(const double *__res
     const bool col = i >= 1 && i <= n - 1 && j >= 1 && j <= n - 1;
     const int sy = n + 1;
     const long sz = long(sy) * sy;
-    // a lane outside the interior walks the nearest interior column
-    const long base = min(max(i, 1), n - 1) + long(sy) * min(max(j, 1), n - 1);
-    auto load = [&](double *W, int k) {
-        const double *p = u + base + sz * min(max(k, 0), n);
-#pragma unroll
-        for (int dy = -1; dy <= 1; ++dy)
-#pragma unroll
-            for (int dx = -1; dx <= 1; ++dx)
-                W[(dy + 1) * 3 + (dx + 1)] = p[dx + sy * dy];
-    };
-    auto rhs = [&](int k) { return F[base + sz * min(max(k, 1), n - 1)]; };
-    double P0[9], P1[9], P2[9], P3[9], fn, acc = 0.0;
-    load(P0, k0 - 1);
-    load(P1, k0);
-    load(P2, k0 + 1);
-    fn = rhs(k0);
-    for (int k = k0; k < k1; ++k) {
-        const double f = fn;
-        load(P3, k + 2);
-        fn = rhs(k + 1);
+    double acc = 0.0;
+    walk_planes<kResPlanes>(u, F, n, i, min(max(j, 1), n - 1), k0, k1, int(threadIdx.x),
+                            [&](int k, const PlaneTerms &C, const PlaneTerms &D,
+                                const PlaneTerms &U, double f) {
         double rv;
         if (OP == OP_MA)
-            rv = f - det3(hessian3(P0 + 4, P1 + 4, P2 + 4, 1, -1, 3, s, s4));
+            rv = f - det3(hessian_planes(D, C, U, s, s4));
         else
-            rv = f - laplacian3(P0 + 4, P1 + 4, P2 + 4, 1, -1, 3, s);
+            rv = f - laplacian_planes(D, C, U, s);
         if (!col || k < 1 || k > n - 1)
             rv = 0.0;
-        acc += rv * rv;
+        acc = fma(rv, rv, acc);
         if (r && i <= n && j <= n)
             r[i + long(sy) * j + sz * k] = rv;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            P0[q] = P1[q];
-            P1[q] = P2[q];
-            P2[q] = P3[q];
-        }
-    }
+    });
     const double t = block_sum<RES_BX * RES_BY / 64>(acc);
     if (threadIdx.x == 0 && threadIdx.y == 0)
         partials[blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * size_t(blockIdx.z))] = t;
