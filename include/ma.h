@@ -110,8 +110,8 @@ typedef struct {
     int graphs;            /* 1: replay each cycle from a captured hipGraph      */
     int coarse_n;          /* levels with n <= coarse_n (0..32) run inside one
                               single-workgroup kernel per solve; 0: off         */
-    int max_blocks;        /* cap on the blocks of one batched launch (multiple
-                              of 8, 0 automatic = 16384)                         */
+    int max_blocks;        /* cap on the wavefronts of one batched launch
+                              (multiple of 8, 0 automatic = 16384)               */
     int strip_rows;        /* x-rows per y-strip in the work order of a batched
                               launch (strips are walked along z; 0 automatic)    */
     int zsweep_n;          /* MA_SMOOTHER_AUTO, 4-colour FP64: z-stream sweeps

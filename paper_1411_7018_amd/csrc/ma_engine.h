@@ -169,7 +169,7 @@ enum ListKind {
 constexpr int kNormPlanes = 8;
 void item_dims(int kind, int order, int n, int *gx, int *gy, int *gz);
 
-// blocks: grid size (a multiple of 8; blocks are split evenly over the XCDs)
+// blocks: wavefronts (a multiple of 8; split evenly over the XCDs)
 hipError_t launch_batched(hipStream_t st, int kind, int op, int order, int color, int rmode,
                           const BatchList *dlist, int blocks, unsigned long long *ncount,
                           unsigned long long *nfall);
@@ -353,7 +353,7 @@ class Engine {
     std::vector<char> hbuf_;               // host copy of the lists and the tail table
     std::vector<size_t> loff_;             // byte offset of each list
     std::vector<int> lng_;                 // grids per list
-    std::vector<int> lgrid_;               // blocks per list launch (0: never any grid)
+    std::vector<int> lgrid_;               // wavefronts per list launch (0: never any grid)
     size_t toff_ = 0;                      // byte offset of the tail table
     bool norm_in_tail_ = false;            // ticks are one coarse-level launch, norm included
     bool sub_cycles_ = false;              // build tsub_ too

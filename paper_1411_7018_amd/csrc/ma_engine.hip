@@ -542,15 +542,19 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
     }
 }
 
+// Wavefronts per block, each on items of its own: four times fewer blocks to
+// dispatch than with one (an 8-colour phase at n = 160: 12.2 -> 11.3 us).
+constexpr int kRowWaves = 4;
 // gridDim.x is a multiple of 8: gridDim.x / 8 blocks per XCD chunk.
 template <int KIND, int OP, int ORDER, int RMODE>
-__global__ __launch_bounds__(64) void k_batched(const BatchList *__restrict__ L, int color,
+__global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__restrict__ L, int color,
                                                 unsigned long long *__restrict__ ncount,
                                                 unsigned long long *__restrict__ nfall)
 {
-    const int bpx = int(gridDim.x >> 3);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = int(threadIdx.x & 63);
+    const int bpx = int(gridDim.x >> 3) * kRowWaves;
     const int total = L->total;
-    const int xcd = blockIdx.x & 7, lb = blockIdx.x >> 3;
+    const int xcd = blockIdx.x & 7, lb = int(blockIdx.x >> 3) * kRowWaves + wave;
     const int per = (total + 7) >> 3;
     const int lo = xcd * per;
     const int hi = min(total, lo + per);
@@ -582,8 +586,7 @@ __global__ __launch_bounds__(64) void k_batched(const BatchList *__restrict__ L,
         // the stopped test after the descriptor's other fields, so they load
         // together
         if (by < G.gy && !((stopped >> G.slot) & 1ull))
-            run_item<KIND, OP, ORDER, RMODE>(G, bx, by, bz, color, int(threadIdx.x), ncount,
-                                             nfall);
+            run_item<KIND, OP, ORDER, RMODE>(G, bx, by, bz, color, t, ncount, nfall);
     }
 }
 
@@ -2026,7 +2029,8 @@ template <int KIND, int OP>
 hipError_t launch_k(hipStream_t st, int order, int color, int rmode, const BatchList *L,
                     int blocks, unsigned long long *nc, unsigned long long *nf)
 {
-    const dim3 grid(blocks), block(64);
+    // blocks is in wavefronts
+    const dim3 grid((blocks / kRowWaves + 7) / 8 * 8), block(64 * kRowWaves);
     if (order == 0) {
         if (rmode == 0)
             hipLaunchKernelGGL((k_batched<KIND, OP, 0, 0>), grid, block, 0, st, L, color, nc, nf);
