@@ -65,8 +65,10 @@ typedef enum { MA_RESTRICT_FULL = 0, MA_RESTRICT_HALF = 1 } ma_restriction;
  * applies to the 4-colour ordering in MA_FP64 only. */
 typedef enum {
     MA_SMOOTHER_AUTO = 0,      /* block sweeps on levels with n <= block_n,
-                                  z-stream sweeps from zsweep_n on, one launch
-                                  per colour phase elsewhere                  */
+                                  z-stream sweeps from zsweep_n on (4 colours)
+                                  or two launches of four phases from n = 136
+                                  on (8 colours), one launch per colour phase
+                                  elsewhere                                   */
     MA_SMOOTHER_COLOR = 1,     /* one in-place launch per colour phase          */
     MA_SMOOTHER_FUSED = 2      /* block sweeps on every level                    */
 } ma_smoother;

@@ -35,7 +35,12 @@ constexpr BCfg kCfg[] = {{8, 8, 8, 256, 0},   {8, 8, 8, 512, 0},  {8, 8, 8, 1024
 constexpr int kZsPureConfig = 11;
 // 8-colour block sweeps: enough threads for the first phase (its block grows
 // by 5, 3, 1 nodes) in one round.
-constexpr BCfg kCfg8[] = {{8, 8, 4, 256, 0}, {8, 8, 8, 320, 0}, {16, 8, 8, 512, 0}};
+// Then the first and the last four phases of a sweep, a launch each (u -> t -> u):
+// the phases of a launch lie in planes of one parity, so its halo is one plane
+// and 4 x 2 nodes, a block recomputes 1.15 x its updates, and a sweep reads u
+// twice where eight colour launches read it eight times.
+constexpr BCfg kCfg8[] = {{8, 8, 4, 256, 0},  {8, 8, 8, 320, 0}, {16, 8, 8, 512, 0},
+                          {32, 8, 8, 512, 0}, {32, 8, 8, 512, 0}};
 constexpr int kNumCfg8 = int(sizeof(kCfg8) / sizeof(kCfg8[0]));
 
 const BCfg &shape_of(int order, int cfg) { return order == 0 ? kCfg[cfg] : kCfg8[cfg]; }
@@ -113,18 +118,22 @@ hipError_t zgo_one(hipStream_t st, const FsGrid &G, unsigned long long *nc)
     return hipGetLastError();
 }
 
-template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0>
+template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0, int PH = ORDER == 0 ? 4 : 8,
+          int GRP = 0>
 hipError_t go_list(hipStream_t st, const FsList *L, int blocks, unsigned long long *nc)
 {
-    hipLaunchKernelGGL((k_bsweep<OP, ORDER, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, L, nc);
+    hipLaunchKernelGGL((k_bsweep<OP, ORDER, PH, GRP, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st,
+                       L, nc);
     return hipGetLastError();
 }
 
-template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0>
+template <int OP, int TX, int TY, int TZ, int NT, int ORDER = 0, int PH = ORDER == 0 ? 4 : 8,
+          int GRP = 0>
 hipError_t go_one(hipStream_t st, const FsGrid &G, unsigned long long *nc)
 {
     const int blocks = G.tiles_x * G.tiles_y * G.tiles_z;
-    hipLaunchKernelGGL((k_bsweep1<OP, ORDER, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0, st, G, nc);
+    hipLaunchKernelGGL((k_bsweep1<OP, ORDER, PH, GRP, TX, TY, TZ, NT>), dim3(blocks), dim3(NT), 0,
+                       st, G, nc);
     return hipGetLastError();
 }
 
@@ -138,6 +147,10 @@ hipError_t list_op8(int cfg, hipStream_t st, const FsList *L, int blocks, unsign
         return go_list<OP, 8, 8, 8, 320, 1>(st, L, blocks, nc);
     case 2:
         return go_list<OP, 16, 8, 8, 512, 1>(st, L, blocks, nc);
+    case kGroupConfig8:
+        return go_list<OP, 32, 8, 8, 512, 1, 4, 0>(st, L, blocks, nc);
+    case kGroupConfig8 + 1:
+        return go_list<OP, 32, 8, 8, 512, 1, 4, 1>(st, L, blocks, nc);
     default:
         return hipErrorInvalidValue;
     }
@@ -153,6 +166,10 @@ hipError_t one_op8(int cfg, hipStream_t st, const FsGrid &G, unsigned long long 
         return go_one<OP, 8, 8, 8, 320, 1>(st, G, nc);
     case 2:
         return go_one<OP, 16, 8, 8, 512, 1>(st, G, nc);
+    case kGroupConfig8:
+        return go_one<OP, 32, 8, 8, 512, 1, 4, 0>(st, G, nc);
+    case kGroupConfig8 + 1:
+        return go_one<OP, 32, 8, 8, 512, 1, 4, 1>(st, G, nc);
     default:
         return hipErrorInvalidValue;
     }
@@ -249,7 +266,7 @@ int bsweep_num_configs() { return kNumCfg; }
 int bsweep_pick(int order, int n, long tiles8)
 {
     if (order == 1)
-        return n <= 32 && tiles8 < 256 ? 0 : n <= 64 ? 1 : 2;
+        return n >= kGroupN ? kGroupConfig8 : n <= 32 && tiles8 < 256 ? 0 : n <= 64 ? 1 : 2;
     if (n <= 16)
         return 2;
     if (n <= 32)
@@ -324,8 +341,11 @@ hipError_t launch_bsweep_one(hipStream_t st, int op, int order, int cfg, int n,
 {
     if (n < 2)
         return hipErrorInvalidValue;
-    if (cfg < 0 || cfg >= (order == 0 ? kNumCfg : kNumCfg8))
+    if (cfg < 0 || cfg >= (order == 0 ? kNumCfg : kNumCfg8)) {
         cfg = bsweep_pick(order, n, long((n - 1 + 7) / 8) * ((n - 1 + 7) / 8) * ((n - 1 + 7) / 8));
+        if (order == 1 && cfg == kGroupConfig8)   // half a sweep: only by name
+            cfg = kGroupConfig8 - 1;
+    }
     FsGrid G;
     bsweep_grid(order, cfg, n, u_in, u_out, F, op, 0, &G);
     if (order == 1)

@@ -311,6 +311,7 @@ class Engine {
 
   private:
     ma_status rebuild(Mode mode, const std::vector<char> &active);
+    bool grouped(int cfg) const { return order_ == 1 && cfg >= kGroupConfig8; }
     ma_status enqueue(Mode mode, bool cycle);
     ma_status enqueue_cycle(Mode mode, bool first, int d0, unsigned long long *count,
                             const NormRing *norm = nullptr);

@@ -2536,7 +2536,7 @@ bool Engine::block_level(int n, Mode mode) const
         return false;
     if ((smoother_ == MA_SMOOTHER_FUSED && n <= kBlockMaxN) || zs_level(n, mode))
         return true;
-    return n <= block_limit(order_, block_n_);
+    return n <= block_limit(order_, block_n_) || group_level(order_, block_n_, n);
 }
 
 // Automatic choice (zsweep_n = 0), from whole-solve timings on MI355X: the
@@ -2926,9 +2926,11 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                 out.assign(nsw, -1);
                 if (!blk)
                     return;
-                for (int k = 0; k + 1 < nsw; k += 2) {
+                // (8 colours, grouped: the two lists are one sweep)
+                const bool grp = grouped(cfg);
+                for (int k = 0; grp ? k < nsw : k + 1 < nsw; k += grp ? 1 : 2) {
                     bool same = true;
-                    for (int i = 0; i < S && same; ++i)
+                    for (int i = 0; i < S && same && !grp; ++i)
                         if (has(i))
                             same = (count(i) > k) == (count(i) > k + 1);
                     if (!same)
@@ -2968,7 +2970,7 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                         const size_t off = hbuf_.size();
                         fsoff_.push_back(off);
                         fsblocks_.push_back(int(bound));
-                        fscfg_.push_back(cfg);
+                        fscfg_.push_back(grp ? cfg + half : cfg);
                         fspro_.push_back(pro && half == 0 ? 1 : 0);
                         hbuf_.resize(off + fs_stride_, 0);
                         std::memcpy(hbuf_.data() + off, &L, fs_list_bytes(L.ngrids));
@@ -3087,10 +3089,10 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
         int launches = 0;
         auto count = [&](const std::vector<int> &lists, const std::vector<int> &pairs) {
             for (size_t k = 0; k < lists.size();) {
-                if (k + 1 < lists.size() && pairs[k] >= 0) {
+                if (pairs[k] >= 0) {
                     launches += (fsblocks_[pairs[k]] > 0 ? 1 : 0) +
                                 (fsblocks_[pairs[k] + 1] > 0 ? 1 : 0);
-                    k += 2;
+                    k += grouped(fscfg_[pairs[k]]) ? 1 : 2;
                 } else {
                     launches += lgrid_[lists[k]] > 0 ? colours : 0;
                     ++k;
@@ -3176,14 +3178,14 @@ ma_status Engine::enqueue_cycle(Mode mode, bool first, int d0, unsigned long lon
     // one launch per colour phase
     auto sweeps = [&](const std::vector<int> &lists, const std::vector<int> &pairs) -> ma_status {
         for (size_t k = 0; k < lists.size();) {
-            if (k + 1 < lists.size() && pairs[k] >= 0) {
+            if (pairs[k] >= 0) {
                 for (int h = 0; h < 2; ++h) {
                     const int f = pairs[k] + h;
                     if (fsblocks_[f] > 0)
                         E_HIP(launch_bsweep(stream_, op, order_, fscfg_[f], FL(f), fsblocks_[f], count,
                                             fspro_[f] != 0));
                 }
-                k += 2;
+                k += grouped(fscfg_[pairs[k]]) ? 1 : 2;
             } else {
                 for (int c = 0; c < colours; ++c)
                     MA_TRY(go(SW, lists[k], c));

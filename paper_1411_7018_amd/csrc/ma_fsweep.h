@@ -70,22 +70,28 @@ struct FsList {
 constexpr size_t fs_list_bytes(int ngrids) { return 16 + sizeof(FsGrid) * size_t(ngrids); }
 static_assert(offsetof(FsList, g) == 16, "list header is 16 bytes");
 
-// Growth of phase c's block along an axis (0: x, 1: y, 2: z).
-__host__ __device__ constexpr int fs_ext(int order, int c, int axis)
+// A launch runs PH consecutive phases of a sweep: all of them, or a group whose
+// other phases are launches of their own.
+//
+// Growth of phase c's block along an axis (0: x, 1: y, 2: z): what the later
+// phases of its launch read.
+__host__ __device__ constexpr int fs_ext(int order, int ph, int c, int axis)
 {
+    const int p = c % ph;
     if (order == 0)
-        return 3 - c;
-    constexpr int e[8][3] = {{5, 3, 1}, {4, 3, 1}, {3, 2, 1}, {2, 2, 1},
-                             {3, 1, 0}, {2, 1, 0}, {1, 0, 0}, {0, 0, 0}};
-    return e[c][axis];
+        return ph - 1 - p;
+    // colours 0-3 (4-7) lie in planes of one parity, and each two of them in
+    // columns beside one another
+    constexpr int e8[8][3] = {{5, 3, 1}, {4, 3, 1}, {3, 2, 1}, {2, 2, 1},
+                              {3, 1, 0}, {2, 1, 0}, {1, 0, 0}, {0, 0, 0}};
+    return e8[8 - ph + p][axis];
 }
 
-template <int ORDER, int TX, int TY, int TZ, int NT>
+template <int ORDER, int PH, int TX, int TY, int TZ, int NT>
 struct FsShape {
-    static constexpr int NC = ORDER == 0 ? 4 : 8;     // phases
     // halo loaded around the block: the first phase's growth and one node
-    static constexpr int HX = fs_ext(ORDER, 0, 0) + 1, HY = fs_ext(ORDER, 0, 1) + 1,
-                         HZ = fs_ext(ORDER, 0, 2) + 1;
+    static constexpr int HX = fs_ext(ORDER, PH, 0, 0) + 1, HY = fs_ext(ORDER, PH, 0, 1) + 1,
+                         HZ = fs_ext(ORDER, PH, 0, 2) + 1;
     static constexpr int LX = TX + 2 * HX;   // LDS row length
     static constexpr int LY = TY + 2 * HY;   // LDS rows per plane
     static constexpr int LZ = TZ + 2 * HZ;   // LDS planes
@@ -94,22 +100,23 @@ struct FsShape {
     // Doubles per plane.  The items of a wavefront lie in several rows and
     // planes whose starts would all be in one bank; with 4 colours this pad
     // brings the reads of 8-wide blocks from 2.9 cycles a pass to 1.8, and a
-    // sweep of n = 64 from 12.2 to 11.0 us (wider blocks and 8 colours, which
-    // walk rows of one parity, do not gain).
+    // sweep of n = 64 from 12.2 to 11.0 us (wider blocks and 8 colours do not
+    // gain).
     static constexpr int PL = PE + (ORDER == 0 && LX == 16 ? 3 : 0);
     static constexpr int NL = PL * LZ;       // doubles in LDS
     // phase c covers columns and planes of one parity and (4 colours) all
     // rows or (8 colours) those of one parity of its grown block
-    static constexpr int ncol(int c) { return TX / 2 + fs_ext(ORDER, c, 0); }
+    static constexpr int ncol(int c) { return TX / 2 + fs_ext(ORDER, PH, c, 0); }
     static constexpr int nrow(int c)
     {
-        return ORDER == 0 ? TY + 2 * fs_ext(ORDER, c, 1) : TY / 2 + fs_ext(ORDER, c, 1);
+        return ORDER == 0 ? TY + 2 * fs_ext(ORDER, PH, c, 1) : TY / 2 + fs_ext(ORDER, PH, c, 1);
     }
-    static constexpr int npl(int c) { return TZ / 2 + fs_ext(ORDER, c, 2); }
+    static constexpr int npl(int c) { return TZ / 2 + fs_ext(ORDER, PH, c, 2); }
     static constexpr int count(int c) { return ncol(c) * nrow(c) * npl(c); }
     // rounds of a workgroup over phase c, and those of the phases before it
     static constexpr int rounds(int c) { return (count(c) + NT - 1) / NT; }
-    static constexpr int before(int c) { return c == 0 ? 0 : before(c - 1) + rounds(c - 1); }
+    static constexpr int before(int c) { return c % PH == 0 ? 0 : before(c - 1) + rounds(c - 1); }
+    static constexpr int total = before(PH - 1) + rounds(PH - 1);
     static constexpr int SX = TX + 2, SY = TY + 2, SZ = TZ + 2;   // store bound
     static_assert(TX % 2 == 0 && TY % 2 == 0 && TZ % 2 == 0, "block sides must be even");
     static_assert(LX % 2 == 0, "LDS rows hold two parity halves");
@@ -172,13 +179,13 @@ struct GsStep {
 // Block `tile` of grid G by a workgroup of NT threads; su: LDS.  Global
 // offsets are 32-bit: grids up to n = 1289.  GS: a step of the Gauss-Seidel
 // iteration A, with sums over `blocks` blocks (waves: NT / 32 doubles of LDS).
-template <int OP, int ORDER, int TX, int TY, int TZ, int NT, bool GS>
+template <int OP, int ORDER, int PH, int GRP, int TX, int TY, int TZ, int NT, bool GS>
 __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *__restrict__ su,
                                             unsigned long long *__restrict__ ncount,
                                             const GsStep *A = nullptr, int blocks = 0,
                                             double *__restrict__ waves = nullptr)
 {
-    using S = FsShape<ORDER, TX, TY, TZ, NT>;
+    using S = FsShape<ORDER, PH, TX, TY, TZ, NT>;
     constexpr int LX = S::LX, HW = S::HW, PE = S::PE, PL = S::PL, NE = PE * S::LZ;
     constexpr int KL = (NE + NT - 1) / NT;
     constexpr int KS = (S::SX * S::SY * S::SZ + NT - 1) / NT;
@@ -203,7 +210,7 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
     // outside the grid interior.
     auto node = [&](auto cc, int item, int &i, int &j, int &k) -> bool {
         constexpr int c = decltype(cc)::value;
-        constexpr int ex = fs_ext(ORDER, c, 0), ey = fs_ext(ORDER, c, 1), ez = fs_ext(ORDER, c, 2);
+        constexpr int ex = fs_ext(ORDER, PH, c, 0), ey = fs_ext(ORDER, PH, c, 1), ez = fs_ext(ORDER, PH, c, 2);
         constexpr int nc = S::ncol(c);
         const int q = item % nc;
         const int r2 = item / nc;
@@ -245,8 +252,8 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
 
     // ---- right-hand sides of every item of this lane, in flight during
     // the block load (a lane without a node reads node 0 and discards it)
-    double f[S::before(S::NC)];
-    fs_phases<0, S::NC>([&](auto cc) {
+    double f[S::total];
+    fs_phases<GRP * PH, GRP * PH + PH>([&](auto cc) {
         constexpr int c = decltype(cc)::value;
 #pragma unroll
         for (int m = 0; m < S::rounds(c); ++m) {
@@ -342,7 +349,7 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
     }
 
     // ---- the phases
-    fs_phases<0, S::NC>([&](auto cc) {
+    fs_phases<GRP * PH, GRP * PH + PH>([&](auto cc) {
         constexpr int c = decltype(cc)::value;
 #pragma unroll
         for (int m = 0; m < S::rounds(c); ++m) {
@@ -376,11 +383,11 @@ __device__ __forceinline__ void bsweep_tile(const FsGrid &G, int tile, double *_
 // Blocks are dispatched round-robin over the 8 XCDs; tile_of_block gives
 // each XCD a contiguous range of tiles, so tiles that share halos share an
 // L2.  One tile per workgroup.
-template <int OP, int ORDER, int TX, int TY, int TZ, int NT>
+template <int OP, int ORDER, int PH, int GRP, int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_bsweep(const FsList *__restrict__ L,
                                                 unsigned long long *__restrict__ ncount)
 {
-    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
+    __shared__ double su[FsShape<ORDER, PH, TX, TY, TZ, NT>::NL];
     const int total = L->total;
     const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
     if (t >= total)
@@ -392,25 +399,26 @@ __global__ __launch_bounds__(NT) void k_bsweep(const FsList *__restrict__ L,
     const FsGrid G = L->g[g];   // the whole descriptor in one set of loads
     if ((L->stopped >> G.slot) & 1ull)
         return;
-    bsweep_tile<OP, ORDER, TX, TY, TZ, NT, false>(G, t - G.start, su, ncount);
+    bsweep_tile<OP, ORDER, PH, GRP, TX, TY, TZ, NT, false>(G, t - G.start, su, ncount);
 }
 
 // The same for one grid passed by value (gridDim.x = its tile count).
-template <int OP, int ORDER, int TX, int TY, int TZ, int NT>
+template <int OP, int ORDER, int PH, int GRP, int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_bsweep1(FsGrid G, unsigned long long *__restrict__ ncount)
 {
-    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
+    __shared__ double su[FsShape<ORDER, PH, TX, TY, TZ, NT>::NL];
     const int t = tile_of_block(int(blockIdx.x), int(gridDim.x));
-    bsweep_tile<OP, ORDER, TX, TY, TZ, NT, false>(G, t, su, ncount);
+    bsweep_tile<OP, ORDER, PH, GRP, TX, TY, TZ, NT, false>(G, t, su, ncount);
 }
 
 template <int ORDER, int TX, int TY, int TZ, int NT>
 __global__ __launch_bounds__(NT) void k_gs_step(FsGrid G, GsStep A)
 {
-    __shared__ double su[FsShape<ORDER, TX, TY, TZ, NT>::NL];
+    constexpr int PH = ORDER == 0 ? 4 : 8;
+    __shared__ double su[FsShape<ORDER, PH, TX, TY, TZ, NT>::NL];
     __shared__ double waves[NT / 32];
     const int blocks = int(gridDim.x);
-    bsweep_tile<OP_MA, ORDER, TX, TY, TZ, NT, true>(G, tile_of_block(int(blockIdx.x), blocks), su,
+    bsweep_tile<OP_MA, ORDER, PH, 0, TX, TY, TZ, NT, true>(G, tile_of_block(int(blockIdx.x), blocks), su,
                                                     A.count, &A, blocks, waves);
 }
 

@@ -32,6 +32,10 @@ hipError_t launch_sweep_color(hipStream_t st, int op, int order, int n, double *
 hipError_t launch_bsweep_one(hipStream_t st, int op, int order, int cfg, int n,
                              const double *u_in, double *u_out, const double *F,
                              unsigned long long *nonconvex);
+// The first of two 8-colour shapes that run half of a sweep's phases each, and
+// the least n that takes them where the whole sweep is no block sweep.
+constexpr int kGroupConfig8 = 3;
+constexpr int kGroupN = 136;
 int bsweep_num_configs();
 // Automatic block shape for grids of up to n intervals whose 8^3 tiles number
 // tiles8 in all.

@@ -65,6 +65,13 @@ inline int block_limit(int order, int block_n)
 {
     return block_n == 0 ? (order == MA_COLOR4 ? 64 : 88) : block_n < kBlockMaxN ? block_n : kBlockMaxN;
 }
+// 8-colour sweeps above that limit as two launches of four phases each, against
+// the colour launches, in us: n = 128: 41 / 40, 144: 61 / 66, 160: 72 / 85, 256:
+// 256 / 265, 384: 853 / 1133.
+inline bool group_level(int order, int block_n, int n)
+{
+    return order != MA_COLOR4 && block_n >= 0 && n >= mafas::kGroupN && n <= kBlockMaxN;
+}
 size_t mixed_bytes(const ma_params *p);
 // launches of the Gauss-Seidel iteration between looks at its sums
 constexpr int kGsBatch = 32;

@@ -579,8 +579,7 @@ bool ma_solver::sweep_shape(int n, int *cfg) const
     if (p.smoother == MA_SMOOTHER_COLOR)
         return false;
     if (p.smoother == MA_SMOOTHER_FUSED && n <= kBlockMaxN) {
-        if (p.order == MA_COLOR4)
-            *cfg = p.tile_config - 1;
+        *cfg = p.order == MA_COLOR4 ? p.tile_config - 1 : n >= kGroupN ? kGroupConfig8 : -1;
         return true;
     }
     const int zn = p.zsweep_n != 0 ? p.zsweep_n : kZsweepAuto;
@@ -590,7 +589,12 @@ bool ma_solver::sweep_shape(int n, int *cfg) const
     }
     if (p.order == MA_COLOR4 && p.tile_config > 0 && p.tile_config <= kZsFirstConfig)
         *cfg = p.tile_config - 1;
-    return n <= block_limit(p.order, p.block_n);
+    const bool block = n <= block_limit(p.order, p.block_n);
+    if (p.order != MA_COLOR4 && n >= kGroupN && (block || group_level(p.order, p.block_n, n))) {
+        *cfg = kGroupConfig8;
+        return true;
+    }
+    return block;
 }
 
 // count single-grid sweeps of op on level l; the result ends in u: one-launch
@@ -607,7 +611,10 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
     double *a = u, *b = lv[l].t;
     for (int k = 0; k < count; ++k) {
         MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg, n, a, b, F, dcount));
-        std::swap(a, b);
+        if (p.order != MA_COLOR4 && cfg == kGroupConfig8)
+            MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg + 1, n, b, a, F, dcount));
+        else
+            std::swap(a, b);
     }
     if (a != u)
         MA_HIP(this, launch_copy(stream, npts(n), a, u));

@@ -50,7 +50,8 @@ def close(got, want):
 
 
 @pytest.mark.parametrize("count", [1, 2])
-@pytest.mark.parametrize("n", [2, 3, 4, 5, 8, 9, 17, 32, 33, 34, 64, 65, 66, 127, 128])
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 8, 9, 17, 32, 33, 34, 64, 65, 66, 127, 128, 135, 136,
+                               137, 160, 161, 201])
 def test_8_colour_block_sweep_bitwise(n, count):
     note("8c block sweep", n, count)
     p = P.exp_cos(n, seed=n)
@@ -63,7 +64,7 @@ def test_8_colour_block_sweep_bitwise(n, count):
 
 
 @pytest.mark.parametrize("order", ["4c", "8c"])
-@pytest.mark.parametrize("n,coarse", [(40, 4), (72, 8), (144, 17)])
+@pytest.mark.parametrize("n,coarse", [(40, 4), (72, 8), (144, 17), (288, 17)])
 def test_8_colour_levels_bitwise(n, coarse, order):
     """Whole V-cycles, Poisson guess included, block levels against colour
     launches on every multi-block level."""
