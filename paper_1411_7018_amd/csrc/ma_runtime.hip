@@ -359,6 +359,14 @@ ma_status ma_restrict(ma_solver *s, const double *u, const double *f, double *w_
     if (s->lv.size() < 2)
         return s->fail(MA_ERR_ARG, "n must be even and >= 4 for a coarser level");
     const int n = s->p.n;
+    // One launch reads f and writes the coarse arrays, in no order between
+    // its blocks: outputs laid over f get it from a copy.
+    const double *f_end = f + npts(n);
+    auto over_f = [&](const double *o) { return o < f_end && f < o + npts(n / 2); };
+    if (over_f(w_c) || over_f(b_c)) {
+        MA_HIP(s, launch_copy(s->stream, npts(n), f, s->lv[0].r));
+        f = s->lv[0].r;
+    }
     MA_HIP(s, launch_restrict(s->stream, s->rmode(), n, u, f, w_c, s->lv[1].u, b_c));
     return MA_OK;
 }
