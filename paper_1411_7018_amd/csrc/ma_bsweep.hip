@@ -37,7 +37,7 @@ constexpr int kZsPureConfig = 11;
 // by 5, 3, 1 nodes) in one round.
 // Then the first and the last four phases of a sweep, a launch each (u -> t -> u):
 // the phases of a launch lie in planes of one parity, so its halo is one plane
-// and 4 x 2 nodes, a block recomputes 1.15 x its updates, and a sweep reads u
+// and 4 x 2 nodes, a block recomputes 1.24 x its updates, and a sweep reads u
 // twice where eight colour launches read it eight times.
 constexpr BCfg kCfg8[] = {{8, 8, 4, 256, 0},  {8, 8, 8, 320, 0}, {16, 8, 8, 512, 0},
                           {32, 8, 8, 512, 0}, {32, 8, 8, 512, 0}};
