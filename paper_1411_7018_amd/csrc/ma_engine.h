@@ -38,7 +38,7 @@ constexpr int kTailMixedFloats = 40832; // and of the mixed form (159.5 KiB), th
 
 // One grid of one solve inside a batched launch.  Every work item is one
 // wavefront handling 64 nodes of one x-row (bx, by, bz) of a gx x gy x gz
-// decomposition.  The items of a grid are ordered in y-strips of w rows
+// decomposition (a colour phase: of rows after each other, gx = 1).  The items of a grid are ordered in y-strips of w rows
 // walked along z: item - start = bx + gx*(jj + w*(bz + gz*strip)), by =
 // strip*w + jj (items with by >= gy are idle), so the rows a stencil
 // reads above, below and on both sides are fetched while they are still

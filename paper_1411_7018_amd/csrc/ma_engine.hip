@@ -425,23 +425,33 @@ __device__ __forceinline__ void pt_mrestrict(const GridItem &G, int I, int J, in
 // ---------------------------------------------------------------------------
 // Row kernel: work item (bx, by, bz) of grid G, lane t.
 // ---------------------------------------------------------------------------
-// Colour rows: (bx, by, bz) -> node (i, j, k) of lane t.
+// Colour items: (by, bz) -> node (i, j, k) of lane t.  Item by of plane bz is
+// 64 consecutive nodes of the colour, the plane's rows of n / 2 after each
+// other, so rows that do not fill wavefronts leave no lanes idle (a row of some
+// colours has one node less).  With segments of 64 nodes a row, before and now:
+// a V-cycle at n = 144: 535 / 453 us, 160: 589 / 519, 176: 675 / 606, 190: 850 /
+// 707, 128: 356 / 355; a mixed solve at n = 256: 26.0 / 25.3 ms.
 template <int ORDER>
-__device__ __forceinline__ void colour_row(int color, int bx, int by, int bz, int t, int &i,
-                                           int &j, int &k)
+__device__ __forceinline__ void colour_node(int color, int n, int by, int bz, int t, int &i,
+                                            int &j, int &k)
 {
+    const int m = n >> 1;
+    int row = int(64u * unsigned(by) / unsigned(m));
+    int x = 64 * by - row * m + t;
+    for (; x >= m; x -= m)
+        ++row;
     int i0;
     if (ORDER == 0) {
         const int c0 = color & 1, c1 = color >> 1;
-        j = 1 + by;
+        j = 1 + row;
         k = (((c0 + c1 + j) & 1) ? 1 : 2) + 2 * bz;
         i0 = ((c0 + j) & 1) ? 1 : 2;
     } else {
-        j = ((color >> 1) & 1 ? 1 : 2) + 2 * by;
+        j = ((color >> 1) & 1 ? 1 : 2) + 2 * row;
         k = ((color >> 2) & 1 ? 1 : 2) + 2 * bz;
         i0 = (color & 1) ? 1 : 2;
     }
-    i = i0 + 2 * (bx * 64 + t);
+    i = i0 + 2 * x;
 }
 
 template <int KIND, int OP, int ORDER, int RMODE>
@@ -453,13 +463,13 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
     const long sy = n + 1, sz = sy * sy;
     if (KIND == LK_SWEEP || KIND == LK_MSWEEP) {
         int i, j, k;
-        colour_row<ORDER>(color, bx, by, bz, t, i, j, k);
+        colour_node<ORDER>(color, n, by, bz, t, i, j, k);
         if (i <= n - 1 && j <= n - 1 && k <= n - 1) {
             const long p = i + sy * j + sz * k;
             if (KIND == LK_SWEEP && ORDER == 0 && G.p[2]) {
-                // colour-ordered F (ma_solver::fs): this row's values are
+                // colour-ordered F (ma_solver::fs): this item's values are
                 // contiguous, so the phase reads F of its own colour only
-                const long q = (long(bz) * G.gy + by) * G.gx + bx;
+                const long q = long(bz) * G.gy + by;
                 const double Fv = gptr<const double>(G.p[2])[long(color) * G.pbase + 64 * q + t];
                 sweep_node<OP>(gptr<double>(G.p[0]), Fv, p, sy, sz, G.s, G.hk, G.slot, ncount);
             } else if (KIND == LK_SWEEP) {
@@ -577,8 +587,9 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__r
             ++g;
         const GridItem G = L->g[g];   // the whole descriptor in one set of loads
         const int local = it - G.start;
-        const int bx = local % G.gx;
-        int rest = local / G.gx;
+        constexpr bool kColour = KIND == LK_SWEEP || KIND == LK_MSWEEP;   // gx = 1
+        const int bx = kColour ? 0 : local % G.gx;
+        int rest = kColour ? local : local / G.gx;
         const int jj = rest % G.w;
         rest /= G.w;
         const int bz = rest % G.gz;
@@ -590,21 +601,20 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__r
     }
 }
 
-// fs[c * cs + 64 q + t] = F at the node of lane t of 4-colour row q of
-// colour c (0 where the row runs past the grid): the right-hand side in the
-// order the finest-level colour sweep reads it.  Block b = row q.
+// fs[c * cs + 64 q + t] = F at the node of lane t of 4-colour item q of
+// colour c (0 where the item runs past the grid): the right-hand side in the
+// order the finest-level colour sweep reads it.  Block b = item q.
 __global__ __launch_bounds__(64) void k_fsplit(int n, const double *__restrict__ F,
-                                               double *__restrict__ fs, long cs, int gx, int gy)
+                                               double *__restrict__ fs, long cs, int gy)
 {
     const int q = int(blockIdx.x), t = int(threadIdx.x);
-    const int bx = q % gx, r = q / gx;
-    const int by = r % gy, bz = r / gy;
+    const int by = q % gy, bz = q / gy;
     const long sy = n + 1, sz = sy * sy;
     const auto Fg = to_global(F);
     const auto out = to_global(fs);
     for (int c = 0; c < 4; ++c) {
         int i, j, k;
-        colour_row<0>(c, bx, by, bz, t, i, j, k);
+        colour_node<0>(c, n, by, bz, t, i, j, k);
         const bool in = i <= n - 1 && j <= n - 1 && k <= n - 1;
         out[long(c) * cs + 64L * q + t] = in ? Fg[i + sy * j + sz * k] : 0.0;
     }
@@ -2086,8 +2096,8 @@ void item_dims(int kind, int order, int n, int *gx, int *gy, int *gz)
     switch (kind) {
     case LK_SWEEP:
     case LK_MSWEEP:
-        *gx = ((n + 1) / 2 + 63) / 64;
-        *gy = order == 0 ? n - 1 : n / 2;
+        *gx = 1;   // 64 nodes of a plane's rows after each other
+        *gy = colour_items(n, order == 0 ? n - 1 : n / 2);
         *gz = n / 2;
         break;
     case LK_RESTRICT:
@@ -2159,7 +2169,7 @@ hipError_t launch_fsplit(hipStream_t st, int n, const double *F, double *fs, lon
     item_dims(LK_SWEEP, 0, n, &gx, &gy, &gz);
     if (long(gx) * gy * gz * 64 != cs || n < 2)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fsplit, dim3(gx * gy * gz), dim3(64), 0, st, n, F, fs, cs, gx, gy);
+    hipLaunchKernelGGL(k_fsplit, dim3(gx * gy * gz), dim3(64), 0, st, n, F, fs, cs, gy);
     return hipGetLastError();
 }
 
@@ -2710,7 +2720,9 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             int gx, gy, gz;
             const int n = mixed ? solves_[i].s->mx[d].n : solves_[i].s->lv[d].n;
             item_dims(kind, order_, n, &gx, &gy, &gz);
-            const int w = strip_width(gy);
+            const int w = kind == LK_SWEEP || kind == LK_MSWEEP
+                              ? std::min(gy, colour_items(n, strip_width(n)))
+                              : strip_width(gy);
             const int items = padded_items(gx, gy, gz, w);
             bound += items;
             if (!active[i])

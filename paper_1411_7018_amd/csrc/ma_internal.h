@@ -11,6 +11,8 @@ namespace mafas {
 enum Op { OP_MA = 0, OP_LAP = 1 };
 
 inline size_t npts(int n) { return size_t(n + 1) * size_t(n + 1) * size_t(n + 1); }
+// Wavefronts of `rows` rows of one colour, packed (n / 2 nodes a row).
+inline int colour_items(int n, int rows) { return int((long(rows) * (n / 2) + 63) / 64); }
 inline double interior(int n) { return double(n - 1) * double(n - 1) * double(n - 1); }
 
 // Number of blocks (and partial sums) the residual-norm kernel produces for

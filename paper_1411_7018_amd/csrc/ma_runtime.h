@@ -51,8 +51,7 @@ size_t hierarchy_bytes(const ma_params *p);
 // (rows of the 4-colour sweep x 64 lanes).
 inline long fs_colour_count(int n)
 {
-    const long gx = ((n + 1) / 2 + 63) / 64, gy = n - 1, gz = n / 2;
-    return gx * gy * gz * 64;
+    return 64L * colour_items(n, n - 1) * (n / 2);
 }
 // largest n of a block sweep (its element offsets are 32-bit)
 constexpr int kBlockMaxN = 1289;
@@ -93,7 +92,7 @@ struct ma_solver {
     std::vector<mafas::Level> lv;
     double *R = nullptr;                  // Poisson right-hand side, finest level
     // The finest right-hand side in the order the 4-colour sweep visits it:
-    // colour c, work item (row) q, lane t at fs[c * fs_cs + 64 q + t]
+    // colour c, work item q, lane t at fs[c * fs_cs + 64 q + t]
     // (FP64 4-colour solvers; filled by the engine when stale).
     double *fs = nullptr;
     long fs_cs = 0;

@@ -33,3 +33,26 @@ def test_sweep_packed_rows(n, order):
         out.append((nc, t.cpu().numpy().view(np.int64)))
     assert out[0][0] == out[1][0]
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("n", [6, 34, 66, 96, 130, 160])
+@pytest.mark.parametrize("order,precision", [("4c", "fp64"), ("8c", "fp64"), ("4c", "mixed")])
+def test_cycles_packed_rows(n, order, precision):
+    """Levels of several row lengths in the engine, colour launches only
+    (block_n = -1, no coarse-level kernel) against the automatic choice."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1411_7018_amd import Solver, _lib as L
+    print("[case] packed rows cycles", n, order, precision, file=sys.stderr, flush=True)
+    p = P.exp_cos(n, seed=n)
+    f = torch.from_numpy(p.f.copy()).cuda()
+    out = []
+    for kw in ({"block_n": -1, "coarse_n": 0, "strip_rows": 5}, {}):
+        t = torch.from_numpy(P.initial_guess(p)).cuda()
+        try:
+            rep = Solver(n, order=order, precision=precision, max_cycles=3, **kw).solve(t, f)
+        except L.MAError as e:   # stops at the cycle limit
+            rep = e.report
+        out.append((rep["cycles"], rep["res"], t.cpu().numpy().view(np.int64)))
+    assert out[0][:2] == out[1][:2]
+    assert np.array_equal(out[0][2], out[1][2])
