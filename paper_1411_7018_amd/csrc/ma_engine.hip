@@ -2546,7 +2546,7 @@ bool Engine::block_level(int n, Mode mode) const
         return false;
     if ((smoother_ == MA_SMOOTHER_FUSED && n <= kBlockMaxN) || zs_level(n, mode))
         return true;
-    return n <= block_limit(order_, block_n_) || group_level(order_, block_n_, n);
+    return n <= block_limit(order_, block_n_) || group_level(order_, block_n_, n, kGroupN);
 }
 
 // Automatic choice (zsweep_n = 0), from whole-solve timings on MI355X: the

@@ -35,7 +35,8 @@ hipError_t launch_bsweep_one(hipStream_t st, int op, int order, int cfg, int n,
                              const double *u_in, double *u_out, const double *F,
                              unsigned long long *nonconvex);
 // The first of two 8-colour shapes that run half of a sweep's phases each, and
-// the least n that takes them where the whole sweep is no block sweep.
+// the least n of a block sweep that takes them (128: 62 us as whole sweeps; 144:
+// 64 as halves).
 constexpr int kGroupConfig8 = 3;
 constexpr int kGroupN = 136;
 int bsweep_num_configs();

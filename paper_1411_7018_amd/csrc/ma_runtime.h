@@ -64,12 +64,18 @@ inline int block_limit(int order, int block_n)
 {
     return block_n == 0 ? (order == MA_COLOR4 ? 64 : 88) : block_n < kBlockMaxN ? block_n : kBlockMaxN;
 }
-// 8-colour sweeps above that limit as two launches of four phases each, against
-// the colour launches, in us: n = 128: 41 / 40, 144: 61 / 66, 160: 72 / 85, 256:
-// 256 / 265, 384: 853 / 1133.
-inline bool group_level(int order, int block_n, int n)
+// 8-colour sweeps above that limit as two launches of four phases each, from n
+// = least on.  In the engine, whose colour phases go by strips, from kGroupN; a
+// V-cycle against colour launches in us: n = 136: 450 / 491, 160: 555 / 664,
+// 192: 823 / 915, 288: 2100 / 2700.  ma_sweep's colour launches are faster, so
+// there from kGroupSweepN; a sweep in us: n = 144: 64 / 51, 160: 73 / 73, 190:
+// 122 / 115, 256: 310 / 266, 304: 529 / 470, 320: 584 / 588 (u and F no longer
+// fit the last-level cache, and eight launches read u eight times), 384: 853 /
+// 1133.
+constexpr int kGroupSweepN = 320;
+inline bool group_level(int order, int block_n, int n, int least)
 {
-    return order != MA_COLOR4 && block_n >= 0 && n >= mafas::kGroupN && n <= kBlockMaxN;
+    return order != MA_COLOR4 && block_n >= 0 && n >= least && n <= kBlockMaxN;
 }
 size_t mixed_bytes(const ma_params *p);
 // launches of the Gauss-Seidel iteration between looks at its sums

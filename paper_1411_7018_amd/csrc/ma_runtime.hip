@@ -598,7 +598,7 @@ bool ma_solver::sweep_shape(int n, int *cfg) const
     if (p.order == MA_COLOR4 && p.tile_config > 0 && p.tile_config <= kZsFirstConfig)
         *cfg = p.tile_config - 1;
     const bool block = n <= block_limit(p.order, p.block_n);
-    if (p.order != MA_COLOR4 && n >= kGroupN && (block || group_level(p.order, p.block_n, n))) {
+    if (p.order != MA_COLOR4 && n >= kGroupN && (block || group_level(p.order, p.block_n, n, kGroupSweepN))) {
         *cfg = kGroupConfig8;
         return true;
     }
