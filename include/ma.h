@@ -322,7 +322,9 @@ ma_status ma_batch_add(ma_batch *b, ma_solver *s, double *u, const double *f, do
 /* One tick over all active slots; done_out[slot] (host, max_solves entries,
  * may be NULL) is set to 1 for slots that converged this tick and to 2 for
  * slots that stopped with an error (its status: ma_batch_report's fields and
- * ma_batch_last_error); 0 otherwise.  Synchronises the batch's stream. */
+ * ma_batch_last_error); 0 otherwise.  Synchronises the batch's stream.
+ * Between ticks the solvers of the batch may run other calls, on grids of
+ * their own; the resident solves' results do not change by it. */
 ma_status ma_batch_tick(ma_batch *b, int *done_out);
 
 /* Report of a slot (valid while it is in the batch). */

@@ -323,6 +323,7 @@ class Engine {
     ma_status flush_arms();
     ma_status upload();
     ma_status refresh_fs(Mode mode, const std::vector<char> &active);
+    ma_status restore_state(Mode mode, bool cycle, const std::vector<char> &active);
     void drop_graphs();
     const double *level_u(int i, int l, Mode mode) const;
     const double *level_F(int i, int l, Mode mode) const;
@@ -333,6 +334,8 @@ class Engine {
     std::vector<int> shape() const;
     ma_status prof_mark();
 
+    const unsigned long long id_ = new_id();   // of ma_solver::tick_state, never used again
+    static unsigned long long new_id();
     std::vector<SolveRef> solves_;
     hipStream_t user_ = nullptr, stream_ = nullptr;
     hipEvent_t ev_in_ = nullptr;

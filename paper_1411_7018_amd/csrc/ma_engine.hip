@@ -20,6 +20,7 @@
 #include "ma_walk.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -2297,6 +2298,12 @@ hipError_t launch_tail_lds(hipStream_t st, int mode, int order, int rmode, bool 
 // ---------------------------------------------------------------------------
 // Engine
 // ---------------------------------------------------------------------------
+unsigned long long Engine::new_id()
+{
+    static std::atomic<unsigned long long> last{0};
+    return ++last;
+}
+
 Engine::~Engine()
 {
     // ticks queued ahead may still run: drain the stream before freeing
@@ -3332,6 +3339,7 @@ ma_status Engine::launch(Mode mode, bool cycle, const std::vector<char> &active,
         E_HIP(hipStreamWaitEvent(stream_, ev_in_, 0));
         user_dirty_ = false;
     }
+    MA_TRY(restore_state(mode, cycle, active));
     if (cycle)
         MA_TRY(refresh_fs(mode, active));
     const int m = int(mode) + (profile_ ? 3 : 0) + (ticks == 2 ? 6 : 0);
@@ -3381,6 +3389,29 @@ ma_status Engine::launch(Mode mode, bool cycle, const std::vector<char> &active,
     p.nev = nev;
     p.ticks = ticks;
     fifo_.push_back(std::move(p));
+    for (size_t i = 0; i < active.size(); ++i)
+        if (active[i])
+            solves_[i].s->tick_state = id_;
+    return MA_OK;
+}
+
+// Ahead of a tick: form again what its solves carry from their last one, where
+// a call between the two has written over it.  A mixed correction's residual
+// launch leaves H, the FP32 residual and the zero start for the next one (the
+// same values for a solve that has them still).  Runs on the engine stream,
+// outside any captured graph.
+ma_status Engine::restore_state(Mode mode, bool cycle, const std::vector<char> &active)
+{
+    bool form = false;
+    for (size_t i = 0; i < active.size(); ++i)
+        if (active[i] && solves_[i].s->tick_state != id_) {
+            form |= mode == MODE_MIXED && cycle;
+            solves_[i].s->tick_state = 0;   // until the launch has been queued
+        }
+    if (form)
+        E_HIP(launch_batched(stream_, LK_RES32, OP_MA, order_, 0, rmode_,
+                             reinterpret_cast<const BatchList *>(dl_ + loff_[norm_]), lgrid_[norm_],
+                             dcount_, dfall_));
     return MA_OK;
 }
 

@@ -113,6 +113,11 @@ struct ma_solver {
     std::vector<mafas::MixedLevel> mx;
     std::string err;
     mafas::Engine *eng = nullptr;         // batch-of-one engine of ma_solve / ma_vcycle
+    // What the scratch arrays carry from one tick of a resident batch to the
+    // next is the state of engine tick_state's last tick; 0 once another call
+    // has written them (calls on a resident solve's solver may come between its
+    // ticks), and the engine forms that state again ahead of its next tick.
+    unsigned long long tick_state = 0;
 
     ~ma_solver();
     ma_status fail(ma_status st, const std::string &msg);
@@ -134,7 +139,9 @@ struct ma_solver {
     ma_status fmg(double *u, const double *f, long long *nonconvex, double *updates,
                   double *bytes);
     // H of a mixed solve's level l, two floats a node each (xx yy, zz xy, xz yz),
-    // in FP64 arrays that its inner cycles leave alone
+    // in FP64 arrays that its inner cycles leave alone.  Level 0's outlives the
+    // tick that forms it: a call that writes one of these arrays clears
+    // tick_state.
     void *mixed_h(int l, int q) const
     {
         return q == 0 ? lv[l].r : q == 1 ? lv[l].t : l == 0 ? R : lv[l].u;

@@ -364,6 +364,7 @@ ma_status ma_restrict(ma_solver *s, const double *u, const double *f, double *w_
     const double *f_end = f + npts(n);
     auto over_f = [&](const double *o) { return o < f_end && f < o + npts(n / 2); };
     if (over_f(w_c) || over_f(b_c)) {
+        s->tick_state = 0;
         MA_HIP(s, launch_copy(s->stream, npts(n), f, s->lv[0].r));
         f = s->lv[0].r;
     }
@@ -616,6 +617,7 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
             MA_HIP(this, launch_sweep_color(stream, op, p.order, n, u, F, dcount));
         return MA_OK;
     }
+    tick_state = 0;
     double *a = u, *b = lv[l].t;
     for (int k = 0; k < count; ++k) {
         MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg, n, a, b, F, dcount));
@@ -645,6 +647,7 @@ ma_status ma_solver::gs_steps(double *u, const double *F, int max_sweeps, double
     unsigned long long *counts = reinterpret_cast<unsigned long long *>(sums + R);
     int *stop = reinterpret_cast<int *>(sums + 2 * R);
     double *buf[2] = {u, lv[0].t};   // iterate q is in buf[q & 1]
+    tick_state = 0;
     MA_HIP(this, launch_fill(stream, 1, 0.0, sums + 2 * R));
     *nonconvex = 0;
     int launched = 0, tested = 0;   // sweeps launched, iterates tested
@@ -719,6 +722,7 @@ ma_status ma_solver::own_engine(Engine **out, double *u, const double *f)
 {
     if (!eng)
         eng = new Engine();
+    tick_state = 0;
     std::vector<SolveRef> refs(1);
     refs[0].s = this;
     refs[0].u = u;
