@@ -3390,24 +3390,32 @@ ma_status Engine::launch(Mode mode, bool cycle, const std::vector<char> &active,
     p.ticks = ticks;
     fifo_.push_back(std::move(p));
     for (size_t i = 0; i < active.size(); ++i)
-        if (active[i])
+        if (active[i]) {
             solves_[i].s->tick_state = id_;
+            solves_[i].s->tick_rows = multiblock_levels(int(i)) > 0;
+        }
     return MA_OK;
 }
 
 // Ahead of a tick: form again what its solves carry from their last one, where
-// a call between the two has written over it.  A mixed correction's residual
+// a call between the two has written over it, or where coarse_n has moved the
+// finest level to the other kernels since, which keep it otherwise.  A mixed correction's residual
 // launch leaves H, the FP32 residual and the zero start for the next one (the
 // same values for a solve that has them still).  Runs on the engine stream,
 // outside any captured graph.
 ma_status Engine::restore_state(Mode mode, bool cycle, const std::vector<char> &active)
 {
     bool form = false;
-    for (size_t i = 0; i < active.size(); ++i)
-        if (active[i] && solves_[i].s->tick_state != id_) {
+    for (size_t i = 0; i < active.size(); ++i) {
+        if (!active[i])
+            continue;
+        ma_solver *sv = solves_[i].s;
+        const bool rows = multiblock_levels(int(i)) > 0;
+        if (sv->tick_state != id_ || (mode == MODE_MIXED && sv->tick_rows != rows)) {
             form |= mode == MODE_MIXED && cycle;
-            solves_[i].s->tick_state = 0;   // until the launch has been queued
+            sv->tick_state = 0;   // until the launch has been queued
         }
+    }
     if (form)
         E_HIP(launch_batched(stream_, LK_RES32, OP_MA, order_, 0, rmode_,
                              reinterpret_cast<const BatchList *>(dl_ + loff_[norm_]), lgrid_[norm_],

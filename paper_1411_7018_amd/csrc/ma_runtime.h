@@ -118,6 +118,7 @@ struct ma_solver {
     // has written them (calls on a resident solve's solver may come between its
     // ticks), and the engine forms that state again ahead of its next tick.
     unsigned long long tick_state = 0;
+    bool tick_rows = false;   // mixed: the finest level had row kernels then (H formed, b in split rows)
 
     ~ma_solver();
     ma_status fail(ma_status st, const std::string &msg);

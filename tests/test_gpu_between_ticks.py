@@ -97,3 +97,31 @@ def test_component_calls_between_mixed_ticks(n, call):
         CALLS[call](s, u, f)
 
     same(run(n, between, precision="mixed"), run(n, precision="mixed"))
+
+
+@pytest.mark.parametrize("first,then", [(16, 32), (32, 16), (0, 32), (32, 8)])
+@pytest.mark.parametrize("n", [24, 32])
+def test_coarse_n_between_mixed_ticks(n, first, then):
+    """The levels move between the row kernels and the coarse-level kernel
+    while a solve is resident: the engine takes the new coarse_n over when
+    another solve joins or leaves."""
+    from paper_1411_7018_amd import Solver
+    print("[case] coarse_n between ticks", n, first, then, file=sys.stderr, flush=True)
+    q = P.example4(16)
+    other = []
+
+    def between(b, s, tick):
+        if tick == 1:
+            s.retune(coarse_n=then)
+            t = Solver(16, precision="mixed", inner_cycles=1, coarse_n=then)
+            slot = b.add(t, dev(P.initial_guess(q, q.u_exact * 1.01)), dev(q.f), tol=1e-12,
+                         init="none")
+            other.append((t, slot))
+        if tick == 3:
+            s.retune(coarse_n=first)
+            b.remove(other[0][1])
+
+    kw = dict(precision="mixed", inner_cycles=1, coarse_n=first)
+    got, want = run(n, between, **kw), run(n, **kw)
+    assert other and want[1] > 5
+    same(got, want)
