@@ -286,9 +286,6 @@ class Engine {
     // The device halt flag of solve i as last seen by the host.
     bool halted(int i) const { return halted_[i] != 0; }
     ma_status reset_counters(int slot);  // slot < 0: all
-    // The right-hand side behind solve i's finest level changed (its
-    // colour-ordered copy is rebuilt before the next tick that reads it).
-    void rhs_changed(int i);
     ma_status read_counters(std::vector<unsigned long long> &nonconvex,
                             std::vector<unsigned long long> &fallbacks);
     // Work of one tick of mode for solve i: point updates and algorithmic bytes.
@@ -300,7 +297,6 @@ class Engine {
     const std::string &error() const { return err_; }
     size_t size() const { return solves_.size(); }
     const SolveRef &ref(int i) const { return solves_[i]; }
-    hipStream_t user() const { return user_; }
     bool mixed() const { return mixed_; }
 
     ma_status fail(ma_status st, const std::string &m)

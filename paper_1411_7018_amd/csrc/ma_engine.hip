@@ -2470,12 +2470,6 @@ ma_status Engine::set(const std::vector<SolveRef> &solves, hipStream_t user, boo
     return MA_OK;
 }
 
-void Engine::rhs_changed(int i)
-{
-    if (i >= 0 && size_t(i) < fs_src_.size())
-        fs_src_[i] = nullptr;
-}
-
 // Rebuild the colour-ordered right-hand side of every active solve whose
 // finest-level colour sweeps read it and whose copy is not of the operand
 // this mode uses (f for FAS cycles, R for the Poisson start).  Runs on the
@@ -3397,12 +3391,14 @@ ma_status Engine::launch(Mode mode, bool cycle, const std::vector<char> &active,
     return MA_OK;
 }
 
-// Ahead of a tick: form again what its solves carry from their last one, where
-// a call between the two has written over it, or where coarse_n has moved the
-// finest level to the other kernels since, which keep it otherwise.  A mixed correction's residual
-// launch leaves H, the FP32 residual and the zero start for the next one (the
-// same values for a solve that has them still).  Runs on the engine stream,
-// outside any captured graph.
+// Ahead of a tick: form what its solves carry from tick to tick, for the first
+// one, where a call since the last has written over it, or where coarse_n has
+// moved the finest level to the other kernels, which keep it otherwise.  That is
+// the right-hand side of the Poisson guess; its or f's copy in colour order
+// (refresh_fs); and in the mixed form H, the FP32 residual and the zero start,
+// which the residual launch of a tick leaves for the next one (launched again,
+// it gives a solve that has them still the same values).  Runs on the engine
+// stream, outside any captured graph.
 ma_status Engine::restore_state(Mode mode, bool cycle, const std::vector<char> &active)
 {
     bool form = false;
@@ -3413,6 +3409,9 @@ ma_status Engine::restore_state(Mode mode, bool cycle, const std::vector<char> &
         const bool rows = multiblock_levels(int(i)) > 0;
         if (sv->tick_state != id_ || (mode == MODE_MIXED && sv->tick_rows != rows)) {
             form |= mode == MODE_MIXED && cycle;
+            if (mode == MODE_LAP)
+                E_HIP(launch_poisson_rhs(stream_, sv->p.n, solves_[i].f, sv->R));
+            fs_src_[i] = nullptr;
             sv->tick_state = 0;   // until the launch has been queued
         }
     }

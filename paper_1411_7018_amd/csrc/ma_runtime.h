@@ -116,7 +116,8 @@ struct ma_solver {
     // What the scratch arrays carry from one tick of a resident batch to the
     // next is the state of engine tick_state's last tick; 0 once another call
     // has written them (calls on a resident solve's solver may come between its
-    // ticks), and the engine forms that state again ahead of its next tick.
+    // ticks), and the engine forms that state again ahead of its next tick
+    // (Engine::restore_state).
     unsigned long long tick_state = 0;
     bool tick_rows = false;   // mixed: the finest level had row kernels then (H formed, b in split rows)
 

@@ -861,13 +861,8 @@ ma_status mafas::drive_step(Engine &eng, std::vector<SolveState *> &states, bool
     // 1. Poisson right-hand sides and the linear residuals of the start
     if (select(SolveState::INIT0)) {
         for (int i = 0; i < S; ++i)
-            if (act[i]) {
-                const SolveRef &r = eng.ref(i);
-                if (launch_poisson_rhs(eng.user(), r.s->p.n, r.f, r.s->R) != hipSuccess)
-                    return MA_ERR_DEVICE;
-                eng.mark_user();
-                eng.rhs_changed(i);
-            }
+            if (act[i])
+                eng.ref(i).s->tick_state = 0;   // R is formed ahead of the norm
         MA_TRY(eng.norms_only(Engine::MODE_LAP, act, nrm));
         for (int i = 0; i < S; ++i)
             if (act[i]) {

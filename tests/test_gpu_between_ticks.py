@@ -125,3 +125,17 @@ def test_coarse_n_between_mixed_ticks(n, first, then):
     got, want = run(n, between, **kw), run(n, **kw)
     assert other and want[1] > 5
     same(got, want)
+
+
+@pytest.mark.parametrize("call", ["vcycle", "poisson", "fmg", "solve"])
+@pytest.mark.parametrize("n,init", [(40, "none"), (40, "poisson"), (96, "poisson")])
+def test_whole_cycles_between_fp64_ticks(n, init, call):
+    """The right-hand side of the Poisson guess (n = 40) and the copy of the
+    right-hand side in colour order (n = 96: colour launches)."""
+    print("[case] fp64 between ticks", n, init, call, file=sys.stderr, flush=True)
+
+    def between(b, s, tick):
+        u, f = other_grid(n)
+        s.vcycle(u, f) if call == "vcycle" else CALLS[call](s, u, f)
+
+    same(run(n, between, init=init), run(n, init=init))
