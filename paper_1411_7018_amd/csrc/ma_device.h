@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "ma_internal.h"
+
 namespace mafas {
 
 // A pointer read from a device-side table is generic to the compiler, which
@@ -351,6 +353,49 @@ __device__ __forceinline__ int tile_of_block(int b, int nb)
     const int xcd = b & 7, idx = b >> 3;
     const int q = nb >> 3, rem = nb & 7;
     return xcd * q + min(xcd, rem) + idx;
+}
+
+// Node (i, j, k) of lane t of colour item (by, bz): 64 consecutive nodes of the
+// colour in plane bz, the plane's rows of m = n / 2 after each other (a row of
+// some colours has one node less).  md: colour_div(n), 2^31 / m rounded up.  The
+// item's first row is one division for the wavefront, the rows past it a 24-bit
+// one for each lane; both are exact (64 by (m - 1) < 2^31, and x (m - 1) < 2^21
+// for x < m + 64, up to n = 2048).  With an integer division and a loop over the
+// rows past, as the mixed form (LOOP) still has them, a V-cycle of colour
+// launches, us: 8 colours n = 40: 270, so 257, 104: 437 / 421; 4 colours n = 66:
+// 142 / 136.  The mixed kernel loses by it where it is bound by throughput (a
+// phase's average at n = 240: 15.5 us with the loop, 16.4 without; a solve at n =
+// 240 11.07 / 11.45 ms, at 40 1.36 / 1.31).
+template <int ORDER, bool LOOP = false>
+__device__ __forceinline__ void colour_node(int color, int n, unsigned md, int by, int bz, int t,
+                                            int &i, int &j, int &k)
+{
+    int row, x;
+    if (LOOP) {
+        const int m = n >> 1;
+        row = int(64u * unsigned(by) / unsigned(m));
+        x = 64 * by - row * m + t;
+        for (; x >= m; x -= m)
+            ++row;
+    } else {
+        const unsigned m = unsigned(n) >> 1, q = 64u * unsigned(by);
+        const unsigned row0 = __umulhi(2u * q, md), x0 = q - row0 * m + unsigned(t);
+        const unsigned past = __umul24(x0, (md + 1023u) >> 10) >> 21;
+        row = int(row0 + past);
+        x = int(x0 - __umul24(past, m));
+    }
+    int i0;
+    if (ORDER == 0) {
+        const int c0 = color & 1, c1 = color >> 1;
+        j = 1 + row;
+        k = (((c0 + c1 + j) & 1) ? 1 : 2) + 2 * bz;
+        i0 = ((c0 + j) & 1) ? 1 : 2;
+    } else {
+        j = ((color >> 1) & 1 ? 1 : 2) + 2 * row;
+        k = ((color >> 2) & 1 ? 1 : 2) + 2 * bz;
+        i0 = (color & 1) ? 1 : 2;
+    }
+    i = i0 + 2 * x;
 }
 
 // New centre value of one linear Gauss-Seidel update for Lap_h u = F;

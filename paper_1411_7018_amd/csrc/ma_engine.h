@@ -50,6 +50,7 @@ struct GridItem {
     int w;         // rows per y-strip
     int slot;      // solve index: norm and counter slot
     int pbase;     // first partial-sum slot (norm lists): gx*gy*gz slots
+    unsigned md;   // colour_div(n)
     double s;      // 1/h^2 of this grid
     double hk;     // h^2/2 (nonlinear update) or 1/(6s) (linear update)
     void *p[8];    // operands, meaning set by the list kind

@@ -426,35 +426,6 @@ __device__ __forceinline__ void pt_mrestrict(const GridItem &G, int I, int J, in
 // ---------------------------------------------------------------------------
 // Row kernel: work item (bx, by, bz) of grid G, lane t.
 // ---------------------------------------------------------------------------
-// Colour items: (by, bz) -> node (i, j, k) of lane t.  Item by of plane bz is
-// 64 consecutive nodes of the colour, the plane's rows of n / 2 after each
-// other, so rows that do not fill wavefronts leave no lanes idle (a row of some
-// colours has one node less).  With segments of 64 nodes a row, before and now:
-// a V-cycle at n = 144: 535 / 453 us, 160: 589 / 519, 176: 675 / 606, 190: 850 /
-// 707, 128: 356 / 355; a mixed solve at n = 256: 26.0 / 25.3 ms.
-template <int ORDER>
-__device__ __forceinline__ void colour_node(int color, int n, int by, int bz, int t, int &i,
-                                            int &j, int &k)
-{
-    const int m = n >> 1;
-    int row = int(64u * unsigned(by) / unsigned(m));
-    int x = 64 * by - row * m + t;
-    for (; x >= m; x -= m)
-        ++row;
-    int i0;
-    if (ORDER == 0) {
-        const int c0 = color & 1, c1 = color >> 1;
-        j = 1 + row;
-        k = (((c0 + c1 + j) & 1) ? 1 : 2) + 2 * bz;
-        i0 = ((c0 + j) & 1) ? 1 : 2;
-    } else {
-        j = ((color >> 1) & 1 ? 1 : 2) + 2 * row;
-        k = ((color >> 2) & 1 ? 1 : 2) + 2 * bz;
-        i0 = (color & 1) ? 1 : 2;
-    }
-    i = i0 + 2 * x;
-}
-
 template <int KIND, int OP, int ORDER, int RMODE>
 __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int bz, int color,
                                          int t, unsigned long long *__restrict__ ncount,
@@ -464,7 +435,7 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
     const long sy = n + 1, sz = sy * sy;
     if (KIND == LK_SWEEP || KIND == LK_MSWEEP) {
         int i, j, k;
-        colour_node<ORDER>(color, n, by, bz, t, i, j, k);
+        colour_node<ORDER, KIND == LK_MSWEEP>(color, n, G.md, by, bz, t, i, j, k);
         if (i <= n - 1 && j <= n - 1 && k <= n - 1) {
             const long p = i + sy * j + sz * k;
             if (KIND == LK_SWEEP && ORDER == 0 && G.p[2]) {
@@ -553,19 +524,16 @@ __device__ __forceinline__ void run_item(const GridItem &G, int bx, int by, int 
     }
 }
 
-// Wavefronts per block, each on items of its own: four times fewer blocks to
-// dispatch than with one (an 8-colour phase at n = 160: 12.2 -> 11.3 us).
-constexpr int kRowWaves = 4;
 // gridDim.x is a multiple of 8: gridDim.x / 8 blocks per XCD chunk.
 template <int KIND, int OP, int ORDER, int RMODE>
-__global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__restrict__ L, int color,
+__global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__restrict__ L, int color, int waves,
                                                 unsigned long long *__restrict__ ncount,
                                                 unsigned long long *__restrict__ nfall)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), t = int(threadIdx.x & 63);
-    const int bpx = int(gridDim.x >> 3) * kRowWaves;
+    const int bpx = int(gridDim.x >> 3) * waves;
     const int total = L->total;
-    const int xcd = blockIdx.x & 7, lb = int(blockIdx.x >> 3) * kRowWaves + wave;
+    const int xcd = blockIdx.x & 7, lb = int(blockIdx.x >> 3) * waves + wave;
     const int per = (total + 7) >> 3;
     const int lo = xcd * per;
     const int hi = min(total, lo + per);
@@ -606,7 +574,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_batched(const BatchList *__r
 // colour c (0 where the item runs past the grid): the right-hand side in the
 // order the finest-level colour sweep reads it.  Block b = item q.
 __global__ __launch_bounds__(64) void k_fsplit(int n, const double *__restrict__ F,
-                                               double *__restrict__ fs, long cs, int gy)
+                                               double *__restrict__ fs, long cs, int gy,
+                                               unsigned md)
 {
     const int q = int(blockIdx.x), t = int(threadIdx.x);
     const int by = q % gy, bz = q / gy;
@@ -615,7 +584,7 @@ __global__ __launch_bounds__(64) void k_fsplit(int n, const double *__restrict__
     const auto out = to_global(fs);
     for (int c = 0; c < 4; ++c) {
         int i, j, k;
-        colour_node<0>(c, n, by, bz, t, i, j, k);
+        colour_node<0>(c, n, md, by, bz, t, i, j, k);
         const bool in = i <= n - 1 && j <= n - 1 && k <= n - 1;
         out[long(c) * cs + 64L * q + t] = in ? Fg[i + sy * j + sz * k] : 0.0;
     }
@@ -2041,17 +2010,18 @@ hipError_t launch_k(hipStream_t st, int order, int color, int rmode, const Batch
                     int blocks, unsigned long long *nc, unsigned long long *nf)
 {
     // blocks is in wavefronts
-    const dim3 grid((blocks / kRowWaves + 7) / 8 * 8), block(64 * kRowWaves);
+    const int w = row_waves(blocks);
+    const dim3 grid((blocks / w + 7) / 8 * 8), block(64 * w);
     if (order == 0) {
         if (rmode == 0)
-            hipLaunchKernelGGL((k_batched<KIND, OP, 0, 0>), grid, block, 0, st, L, color, nc, nf);
+            hipLaunchKernelGGL((k_batched<KIND, OP, 0, 0>), grid, block, 0, st, L, color, w, nc, nf);
         else
-            hipLaunchKernelGGL((k_batched<KIND, OP, 0, 1>), grid, block, 0, st, L, color, nc, nf);
+            hipLaunchKernelGGL((k_batched<KIND, OP, 0, 1>), grid, block, 0, st, L, color, w, nc, nf);
     } else {
         if (rmode == 0)
-            hipLaunchKernelGGL((k_batched<KIND, OP, 1, 0>), grid, block, 0, st, L, color, nc, nf);
+            hipLaunchKernelGGL((k_batched<KIND, OP, 1, 0>), grid, block, 0, st, L, color, w, nc, nf);
         else
-            hipLaunchKernelGGL((k_batched<KIND, OP, 1, 1>), grid, block, 0, st, L, color, nc, nf);
+            hipLaunchKernelGGL((k_batched<KIND, OP, 1, 1>), grid, block, 0, st, L, color, w, nc, nf);
     }
     return hipGetLastError();
 }
@@ -2170,7 +2140,8 @@ hipError_t launch_fsplit(hipStream_t st, int n, const double *F, double *fs, lon
     item_dims(LK_SWEEP, 0, n, &gx, &gy, &gz);
     if (long(gx) * gy * gz * 64 != cs || n < 2)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_fsplit, dim3(gx * gy * gz), dim3(64), 0, st, n, F, fs, cs, gy);
+    hipLaunchKernelGGL(k_fsplit, dim3(gx * gy * gz), dim3(64), 0, st, n, F, fs, cs, gy,
+                       colour_div(n));
     return hipGetLastError();
 }
 
@@ -2737,6 +2708,7 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             G.gy = gy;
             G.gz = gz;
             G.w = w;
+            G.md = colour_div(n);
             G.start = start;
             if (partial) {
                 G.pbase = pnext;

@@ -13,6 +13,17 @@ enum Op { OP_MA = 0, OP_LAP = 1 };
 inline size_t npts(int n) { return size_t(n + 1) * size_t(n + 1) * size_t(n + 1); }
 // Wavefronts of `rows` rows of one colour, packed (n / 2 nodes a row).
 inline int colour_items(int n, int rows) { return int((long(rows) * (n / 2) + 63) / 64); }
+// Factor of colour_node's divisions by n / 2.
+inline unsigned colour_div(int n) { return unsigned(((1ull << 31) + n / 2 - 1) / (n / 2)); }
+// Wavefronts per block of a launch of row items, each on items of its own.  A
+// large launch takes four a block, four times fewer blocks to dispatch (4 colours
+// n = 160, two sweeps, us: 114 with one, 110 with four; 8 colours n = 272: 636 /
+// 620).  A small one takes one: its few blocks spread over more compute units (8
+// colours n = 104: 63 with one, 68 with four; 4 colours n = 104: 46.5 / 48.7).
+// (The number is a kernel argument: reading it as blockDim.x costs each
+// wavefront a load before its first item, 3-5% of those times.)
+constexpr int kRowWaves = 4, kManyWaves = 6144;
+inline int row_waves(int waves) { return waves > kManyWaves ? kRowWaves : 1; }
 inline double interior(int n) { return double(n - 1) * double(n - 1) * double(n - 1); }
 
 // Number of blocks (and partial sums) the residual-norm kernel produces for

@@ -46,42 +46,22 @@ __device__ __forceinline__ double block_sum(double v)
 // of a phase do not interact.
 // ---------------------------------------------------------------------------
 template <int OP, int ORDER>
-__global__ __launch_bounds__(256) void k_sweep_color(double *__restrict__ u,
-                                                     const double *__restrict__ F, int n,
-                                                     int color, int gy, int gz, int nb, double s,
-                                                     double s4, double hk,
-                                                     unsigned long long *__restrict__ ncount)
+__global__ __launch_bounds__(64 * kRowWaves) void k_sweep_color(
+    double *__restrict__ u, const double *__restrict__ F, int n, unsigned md, int waves, int color,
+    int gy, int gz, int nb, double s, double s4, double hk, unsigned long long *__restrict__ ncount)
 {
-    // One wavefront = 64 consecutive nodes of the colour, rows of m after each
-    // other; blocks in XCD-contiguous order.  With a row in segments of 64 a
-    // row of 65-95 nodes left its second wavefront mostly idle; us a sweep of
-    // four phases, before and now: n = 96: 20.8 / 20.7, 128: 30.4 / 30.5, 130:
-    // 48.4 / 33.0, 149: 63.5 / 45.5, 176: 84.2 / 66.2.
-    const int m = n >> 1, lane = threadIdx.x & 63;
-    const unsigned wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned q = 64u * (4u * tile_of_block(blockIdx.x, nb) + wave);
-    const unsigned row = q / unsigned(m);
-    int x = int(q - row * unsigned(m)) + lane, by = int(row % unsigned(gy)),
-        bz = int(row / unsigned(gy));
-    for (; x >= m; x -= m)
-        if (++by == gy) {
-            by = 0;
-            ++bz;
-        }
+    // One wavefront per colour item (rows packed: with a row in segments of 64 a
+    // row of 65-95 nodes left its second wavefront mostly idle; two sweeps, us,
+    // segments / packed: 4 colours n = 66: 31.7 / 28.4, 96: 43.4 / 40.0, 128:
+    // 62.3 / 62.3, 130: 97.7 / 67.0, 160: 145 / 108, 240: 320 / 305; 8 colours n =
+    // 104: 62.4 / 59.4, 127: 76.5 / 77.8); blocks in XCD-contiguous order.
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int q = tile_of_block(blockIdx.x, nb) * waves + wave;
+    const int bz = q / gy, by = q - bz * gy;
     if (bz >= gz)
         return;
-    int i0, j, k;
-    if (ORDER == 0) {
-        const int c0 = color & 1, c1 = color >> 1;
-        j = 1 + by;
-        k = (((c0 + c1 + j) & 1) ? 1 : 2) + 2 * bz;
-        i0 = ((c0 + j) & 1) ? 1 : 2;
-    } else {
-        j = ((color >> 1) & 1 ? 1 : 2) + 2 * by;
-        k = ((color >> 2) & 1 ? 1 : 2) + 2 * bz;
-        i0 = (color & 1) ? 1 : 2;
-    }
-    const int i = i0 + 2 * x;
+    int i, j, k;
+    colour_node<ORDER>(color, n, md, by, bz, int(threadIdx.x & 63), i, j, k);
     if (i > n - 1 || j > n - 1 || k > n - 1)
         return;
     const long sy = n + 1, sz = sy * sy;
@@ -347,12 +327,13 @@ hipError_t launch_sweep_color(hipStream_t st, int op, int order, int n, double *
     const double s = double(n) * double(n), s4 = 0.25 * s;
     const double hk = op == OP_MA ? 0.5 / s : 1.0 / (6.0 * s);
     const int ncol = order == 1 ? 8 : 4;
-    const int gy = order == 0 ? n - 1 : n / 2, gz = n / 2;
-    const int nb = int((size_t(n / 2) * gy * gz + 255) / 256);
+    const int gy = colour_items(n, order == 0 ? n - 1 : n / 2), gz = n / 2;
+    const int w = row_waves(gy * gz), nb = (gy * gz + w - 1) / w;
+    const unsigned md = colour_div(n);
     for (int c = 0; c < ncol; ++c) {
 #define MA_COLOR_LAUNCH(OPV, ORD)                                                                \
-    hipLaunchKernelGGL((k_sweep_color<OPV, ORD>), dim3(nb), dim3(256), 0, st, u, F, n, c, gy, gz, \
-                       nb, s, s4, hk, nonconvex)
+    hipLaunchKernelGGL((k_sweep_color<OPV, ORD>), dim3(nb), dim3(64 * w), 0, st, u, F, n, md, w, \
+                       c, gy, gz, nb, s, s4, hk, nonconvex)
         if (op == OP_MA) {
             if (order == 0)
                 MA_COLOR_LAUNCH(OP_MA, 0);
