@@ -80,13 +80,17 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_sweep_color(
 // ---------------------------------------------------------------------------
 // Residual r = F - S(u) (0 on the boundary; r may be null) and per-block sums
 // of r^2 over interior nodes.  A wavefront takes 64 columns of one row and
-// walks kResPlanes planes along z (ma_walk.h).  Bound by HBM; 298^3 with r: 375
+// walks a chunk of planes along z (ma_walk.h).  Bound by HBM; 298^3 with r: 375
 // us as a gather and a separate clear of r, 250 us with nine loads a node and a
-// plane in flight, 204 us so.
+// plane in flight, 204 us so.  On small grids a launch lasts as long as one
+// wavefront's walk, so their chunks are two planes; residual and norm, us, a
+// gather / chunks of eight / of two: n = 32: 19.3 / 21.5 / 19.3, 64: 20.6 / 23.1 /
+// 22.0, 72: 24.0 / 23.1 / 22.8.
 // ---------------------------------------------------------------------------
-constexpr int kResPlanes = 8;
+constexpr int kResPlanes = 8, kResPlanesSmall = 2;
+int residual_planes(int n) { return n <= 65 ? kResPlanesSmall : kResPlanes; }
 
-template <int OP>
+template <int OP, int PLANES>
 __global__ __launch_bounds__(RES_BX *RES_BY) void k_residual(const double *__restrict__ u,
                                                              const double *__restrict__ F,
                                                              double *__restrict__ r,
@@ -95,12 +99,12 @@ __global__ __launch_bounds__(RES_BX *RES_BY) void k_residual(const double *__res
 {
     const int i = blockIdx.x * RES_BX + threadIdx.x;
     const int j = blockIdx.y * RES_BY + threadIdx.y;
-    const int k0 = blockIdx.z * kResPlanes, k1 = min(k0 + kResPlanes, n + 1);
+    const int k0 = blockIdx.z * PLANES, k1 = min(k0 + PLANES, n + 1);
     const bool col = i >= 1 && i <= n - 1 && j >= 1 && j <= n - 1;
     const int sy = n + 1;
     const long sz = long(sy) * sy;
     double acc = 0.0;
-    walk_planes<kResPlanes>(u, F, n, i, min(max(j, 1), n - 1), k0, k1, int(threadIdx.x),
+    walk_planes<PLANES>(u, F, n, i, min(max(j, 1), n - 1), k0, k1, int(threadIdx.x),
                             [&](int k, const PlaneTerms &C, const PlaneTerms &D,
                                 const PlaneTerms &U, double f) {
         double rv;
@@ -311,7 +315,8 @@ inline dim3 res_grid(int cnt_x, int cnt_y, int cnt_z)
 namespace {
 dim3 residual_grid(int n)
 {
-    return dim3((n + RES_BX) / RES_BX, (n + RES_BY) / RES_BY, (n + kResPlanes) / kResPlanes);
+    return dim3((n + RES_BX) / RES_BX, (n + RES_BY) / RES_BY,
+                (n + residual_planes(n)) / residual_planes(n));
 }
 } // namespace
 
@@ -358,10 +363,21 @@ hipError_t launch_residual(hipStream_t st, int op, int n, const double *u, const
 {
     const double s = double(n) * double(n), s4 = 0.25 * s;
     const dim3 grid = residual_grid(n), block(RES_BX, RES_BY);
-    if (op == OP_MA)
-        hipLaunchKernelGGL((k_residual<OP_MA>), grid, block, 0, st, u, F, r, partials, n, s, s4);
-    else
-        hipLaunchKernelGGL((k_residual<OP_LAP>), grid, block, 0, st, u, F, r, partials, n, s, s4);
+    const bool small = residual_planes(n) == kResPlanesSmall;
+#define MA_RESIDUAL_LAUNCH(OPV, PL)                                                              \
+    hipLaunchKernelGGL((k_residual<OPV, PL>), grid, block, 0, st, u, F, r, partials, n, s, s4)
+    if (op == OP_MA) {
+        if (small)
+            MA_RESIDUAL_LAUNCH(OP_MA, kResPlanesSmall);
+        else
+            MA_RESIDUAL_LAUNCH(OP_MA, kResPlanes);
+    } else {
+        if (small)
+            MA_RESIDUAL_LAUNCH(OP_LAP, kResPlanesSmall);
+        else
+            MA_RESIDUAL_LAUNCH(OP_LAP, kResPlanes);
+    }
+#undef MA_RESIDUAL_LAUNCH
     return hipGetLastError();
 }
 

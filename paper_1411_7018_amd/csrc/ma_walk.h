@@ -85,7 +85,7 @@ template <int PLANES, typename PU, typename PF, typename N>
 __device__ __forceinline__ void walk_planes(PU u, PF F, int n, int i, int j, int k0, int k1,
                                             int lane, N node)
 {
-    constexpr int kAhead = 3;
+    constexpr int kAhead = PLANES < 3 ? PLANES : 3;
     const long sy = n + 1, sz = sy * sy;
     const bool outer = lane == 0 || lane == 63;
     const long at = min(max(i, 0), n) + sy * j;
