@@ -285,6 +285,12 @@ int bsweep_zs_pick(int n)
     return zs_model_cost100(n, kZsPureConfig) <= zs_model_cost100(n, 7) ? kZsPureConfig : 7;
 }
 
+bool bsweep_zs_alone(int n)
+{
+    const double step = 0.0142, cost = std::min(zs_model_cost100(n, kZsPureConfig), zs_model_cost100(n, 7));
+    return n > 256 || step * cost <= 8.5e-6 * n * n * n;
+}
+
 void bsweep_grid(int order, int cfg, int n, const double *uin, double *uout, const double *F,
                  int op, int slot, FsGrid *G)
 {

@@ -60,6 +60,12 @@ int gs_blocks(int order, int n);
 hipError_t launch_gs_step(hipStream_t st, int order, int n, const double *u_in, double *u_out,
                           const double *F, const double *part_in, double *part_out, double *sum,
                           unsigned long long *count, int *stop, int q, double thr);
+// Whether one z-stream sweep of an n grid and the copy back to u take less than
+// its colour launches.  The sweep by the chunk model, its steps 1.42 us / 100;
+// the copy 3.0 ns a node and the launches 11.5, until u and F no longer fit the
+// last-level cache.  us, sweep and copy / launches: n = 192: 90 / 86, 208: 112 /
+// 108, 224: 125 / 131, 240: 168 / 161, 256: 200 / 203, 272: 266 / 300.
+bool bsweep_zs_alone(int n);
 // automatic z-stream shape (config index) of an n grid
 int bsweep_zs_pick(int n);
 

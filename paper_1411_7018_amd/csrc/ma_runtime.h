@@ -126,6 +126,7 @@ struct ma_solver {
     ma_status alloc(double **q, size_t count);
     ma_status allocate();
     bool sweep_shape(int n, int *cfg) const;
+    bool alone_pays(int n, int cfg) const;
     int rmode() const;
     // single-grid kernels behind the component entry points
     ma_status smooth(int l, double *u, const double *F, int count, int op);

@@ -606,20 +606,29 @@ bool ma_solver::sweep_shape(int n, int *cfg) const
     return block;
 }
 
+// Whether a lone one-launch sweep of shape cfg, which ends in t and is copied
+// back to u, takes less than its colour launches (8-colour halves go u -> t ->
+// u).  us, 4 colours n = 48: 13.0 / 14.9, 56 (more blocks of 8^3 than compute
+// units): 16.2 / 15.5, 64: 17.5 / 16.5; 8 colours n = 80: 25 / 27, 88: 34 / 29.
+bool ma_solver::alone_pays(int n, int cfg) const
+{
+    if (p.order != MA_COLOR4)
+        return cfg == kGroupConfig8 || n <= 80;
+    return bsweep_is_zstream(0, cfg) ? bsweep_zs_alone(n) : n <= 49;
+}
+
 // count single-grid sweeps of op on level l; the result ends in u: one-launch
-// sweeps go u -> t -> u, and an odd last one is copied back.
+// sweeps go u -> t -> u, and an odd last one is copied back or runs per colour.
 ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op)
 {
     const int n = lv[l].n;
-    int cfg;
-    if (!sweep_shape(n, &cfg)) {
-        for (int k = 0; k < count; ++k)
-            MA_HIP(this, launch_sweep_color(stream, op, p.order, n, u, F, dcount));
-        return MA_OK;
-    }
-    tick_state = 0;
+    int cfg, whole = 0;   // sweeps in one launch
+    if (sweep_shape(n, &cfg))
+        whole = alone_pays(n, cfg) ? count : count / 2 * 2;
+    if (whole > 0)
+        tick_state = 0;
     double *a = u, *b = lv[l].t;
-    for (int k = 0; k < count; ++k) {
+    for (int k = 0; k < whole; ++k) {
         MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg, n, a, b, F, dcount));
         if (p.order != MA_COLOR4 && cfg == kGroupConfig8)
             MA_HIP(this, launch_bsweep_one(stream, op, p.order, cfg + 1, n, b, a, F, dcount));
@@ -628,6 +637,8 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
     }
     if (a != u)
         MA_HIP(this, launch_copy(stream, npts(n), a, u));
+    for (int k = whole; k < count; ++k)
+        MA_HIP(this, launch_sweep_color(stream, op, p.order, n, u, F, dcount));
     return MA_OK;
 }
 
