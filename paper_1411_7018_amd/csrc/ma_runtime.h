@@ -78,8 +78,8 @@ inline bool group_level(int order, int block_n, int n, int least)
     return order != MA_COLOR4 && block_n >= 0 && n >= least && n <= kBlockMaxN;
 }
 size_t mixed_bytes(const ma_params *p);
-// launches of the Gauss-Seidel iteration between looks at its sums
-constexpr int kGsBatch = 32;
+// most launches of the Gauss-Seidel iteration between looks at its sums
+constexpr int kGsBatch = 64;
 
 hipError_t launch_fill(hipStream_t st, size_t count, double v, double *dst);
 hipError_t launch_fill_u64(hipStream_t st, size_t count, unsigned long long v,

@@ -102,7 +102,7 @@ size_t gs_doubles(const ma_params *p)
 {
     if (p->n > (p->order == MA_COLOR4 ? 96 : 80) || p->smoother == MA_SMOOTHER_COLOR)
         return 0;
-    return 2 * size_t(gs_blocks(p->order, p->n)) + 4 * kGsBatch + 1;
+    return 2 * size_t(gs_blocks(p->order, p->n)) + 2 * kGsBatch + 3;
 }
 
 } // namespace
@@ -563,8 +563,8 @@ ma_status ma_solver::allocate()
             return fail(MA_ERR_OOM, std::string("hipMalloc: ") + hipGetErrorString(e));
         owned.push_back(reinterpret_cast<double *>(dcount));
     }
-    if (hipHostMalloc(reinterpret_cast<void **>(&hpin), 2 * kGsBatch * sizeof(double)) != hipSuccess ||
-        hipHostMalloc(reinterpret_cast<void **>(&hpin_u64), 2 * kGsBatch * sizeof(unsigned long long)) !=
+    if (hipHostMalloc(reinterpret_cast<void **>(&hpin), (2 * kGsBatch + 2) * sizeof(double)) != hipSuccess ||
+        hipHostMalloc(reinterpret_cast<void **>(&hpin_u64), 4 * sizeof(unsigned long long)) !=
             hipSuccess)
         return fail(MA_ERR_OOM, "hipHostMalloc failed");
     if (p.precision == MA_MIXED)
@@ -643,72 +643,72 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
 }
 
 // The standalone Gauss-Seidel iteration on u by launches of k_gs_step (one
-// sweep each, GsStep in ma_fsweep.h), kGsBatch of them between looks at the
-// sums.  Launch q sweeps iterate q - 1 (in u when q is odd, else in t) into
-// iterate q and tests iterate q - 2.  test(q, residual) is the host's test of
-// iterate q, the same on the same sum (thr: sum_threshold), so both stop at
-// the same iterate; *nonconvex counts the sweeps up to it.
+// sweep each, GsStep in ma_fsweep.h), m of them between looks at the sums.
+// Launch b of a batch that starts from iterate q0, in x[0], sweeps iterate q0 + b
+// into the next (iterate q0 + b is in x[b & 1]) and tests iterate q0 + b - 1
+// where that is one of the batch; the last two iterates' sums are taken after
+// the launches.  test(q, residual) is the host's test of iterate q, the same on
+// the same sum (thr: sum_threshold), so both stop at the same iterate;
+// *nonconvex counts the sweeps up to it.
+//
+// A solve may stop anywhere in a batch, and what is queued behind that still
+// loads its blocks, so a batch is at most half (from n = 41 on, a quarter) of
+// the sweeps before it, and the first sweeps are looked at one by one: on larger
+// grids as colour launches, since k_gs_step takes a residual that a lone sweep
+// has no use for (4 colours n = 96, 3 sweeps 263 us with it, 235 without; n = 64,
+// where the launches count, 5 sweeps 249 / 280).  us a solve, every sweep looked
+// at / batches of 32 from the start / so: 4 colours n = 32, 1 sweep 83 / 179 / 62,
+// 6 sweeps 243 / 209 / 192; n = 96, 3 sweeps 257 / 577 / 235, 40 sweeps 1990 /
+// 1297 / 1598; 8 colours n = 80, 3 sweeps 246 / 668 / 230.
 ma_status ma_solver::gs_steps(double *u, const double *F, int max_sweeps, double thr,
                               const std::function<bool(int, double)> &test, long long *nonconvex)
 {
-    constexpr int B = kGsBatch, R = 2 * kGsBatch;   // ring of sums and counts
     const int n = p.n, blocks = gs_blocks(p.order, n);
+    const int part_of = n <= 40 ? 2 : 4;
+    const bool colours = n > (p.order == MA_COLOR4 ? 84 : 72);   // a lone sweep's launches
     const double h = 1.0 / double(n);
-    double *part[2] = {gs_work, gs_work + blocks}, *sums = gs_work + 2 * blocks;
-    unsigned long long *counts = reinterpret_cast<unsigned long long *>(sums + R);
-    int *stop = reinterpret_cast<int *>(sums + 2 * R);
-    double *buf[2] = {u, lv[0].t};   // iterate q is in buf[q & 1]
+    // block sums of two iterates; a batch's counts and, behind them, its sums
+    double *part[2] = {gs_work, gs_work + blocks}, *res = gs_work + 2 * blocks;
+    unsigned long long *counts = reinterpret_cast<unsigned long long *>(res);
+    int *stop = reinterpret_cast<int *>(res + 2 * kGsBatch + 2);
+    double *x[2] = {u, lv[0].t};
     tick_state = 0;
-    MA_HIP(this, launch_fill(stream, 1, 0.0, sums + 2 * R));
+    MA_HIP(this, launch_fill(stream, 1, 0.0, res + 2 * kGsBatch + 2));
     *nonconvex = 0;
-    int launched = 0, tested = 0;   // sweeps launched, iterates tested
+    int q0 = 0;   // sweeps tested; iterate q0 is in x[0]
     bool stopped = false;
-    std::vector<double> hs(R);
-    std::vector<unsigned long long> hc(R);
-    auto read = [&]() -> ma_status {
-        MA_HIP(this, hipMemcpyAsync(hpin, sums, R * sizeof(double), hipMemcpyDeviceToHost, stream));
-        MA_HIP(this, hipMemcpyAsync(hpin_u64, counts, R * sizeof(unsigned long long),
-                                    hipMemcpyDeviceToHost, stream));
+    while (!stopped && q0 < max_sweeps) {
+        const int m = std::min({std::max(q0 / part_of, 1), kGsBatch, max_sweeps - q0});
+        double *sums = res + m;
+        MA_HIP(this, launch_fill_u64(stream, m, 0ull, counts));
+        const bool here = m == 1 && colours;   // the sweep stays in x[0]
+        if (here)
+            MA_HIP(this, launch_sweep_color(stream, OP_MA, p.order, n, x[0], F, counts));
+        for (int b = 0; b < m && !here; ++b)
+            MA_HIP(this, launch_gs_step(stream, p.order, n, x[b & 1], x[1 - (b & 1)], F,
+                                        b >= 2 ? part[1 - (b & 1)] : nullptr, part[b & 1],
+                                        sums + b, counts + b, stop, q0 + b + 1, thr));
+        if (m >= 2)   // the block sums of iterate q0 + m - 1 are there
+            MA_HIP(this, launch_reduce(stream, part[1 - (m & 1)], blocks, sums + m));
+        MA_HIP(this, launch_residual(stream, OP_MA, n, x[here ? 0 : m & 1], F, nullptr,
+                                     partials));
+        MA_HIP(this, launch_reduce(stream, partials, residual_partials(n), sums + m + 1));
+        MA_HIP(this, hipMemcpyAsync(hpin, res, (2 * m + 2) * sizeof(double), hipMemcpyDeviceToHost,
+                                    stream));
         MA_HIP(this, hipStreamSynchronize(stream));
-        std::copy(hpin, hpin + R, hs.begin());
-        std::copy(hpin_u64, hpin_u64 + R, hc.begin());
-        return MA_OK;
-    };
-    while (!stopped && launched < max_sweeps) {
-        const int m = std::min(B, max_sweeps - launched);
-        MA_HIP(this, launch_fill_u64(stream, B, 0ull, counts + launched % R));
-        for (int q = launched + 1; q <= launched + m; ++q) {
-            // iterate 0 is not tested: at least one sweep is done
-            const double *in = q >= 3 ? part[q & 1] : nullptr;
-            MA_HIP(this, launch_gs_step(stream, p.order, n, buf[(q - 1) & 1], buf[q & 1], F, in,
-                                        part[1 - (q & 1)], sums + (q - 1) % R, counts + (q - 1) % R,
-                                        stop, q, thr));
+        int b = 0;   // iterate q0 + b was tested last
+        while (!stopped && b < m) {
+            unsigned long long c;
+            std::memcpy(&c, hpin + b++, sizeof(c));
+            *nonconvex += (long long)c;
+            stopped = test(q0 + b, std::sqrt(hpin[m + b + 1] * h * h * h));
         }
-        launched += m;
-        MA_TRY(read());
-        while (!stopped && tested < launched - 2) {
-            ++tested;
-            *nonconvex += (long long)hc[(tested - 1) % R];
-            stopped = test(tested, std::sqrt(hs[(tested + 1) % R] * h * h * h));
-        }
+        q0 += b;
+        if (!here && (b & 1))
+            std::swap(x[0], x[1]);
     }
-    // at max_sweeps, the last two iterates: the block sums of one are there,
-    // not added up; the other's residual is still to be taken
-    while (!stopped && tested < launched) {
-        ++tested;
-        double res;
-        if (tested < launched) {
-            MA_HIP(this, launch_reduce(stream, part[tested & 1], blocks, dsum));
-            MA_TRY(read_norm(n, &res));
-        } else {
-            MA_HIP(this, launch_residual(stream, OP_MA, n, buf[tested & 1], F, nullptr, partials));
-            MA_TRY(finish_norm(n, &res));
-        }
-        *nonconvex += (long long)hc[(tested - 1) % R];
-        stopped = test(tested, res);
-    }
-    if (buf[tested & 1] != u)
-        MA_HIP(this, launch_copy(stream, npts(n), buf[tested & 1], u));
+    if (x[0] != u)
+        MA_HIP(this, launch_copy(stream, npts(n), x[0], u));
     return MA_OK;
 }
 

@@ -1,5 +1,6 @@
 """An odd number of sweeps, whose last one runs in one launch with a copy back
-or per colour by the size: the bits of the colour launches on both sides of each size."""
+or per colour by the size, and the Gauss-Seidel solver's first sweeps, looked at
+one by one: the bits of the colour launches on both sides of each size."""
 import sys
 
 import numpy as np
@@ -35,3 +36,20 @@ def test_odd_sweeps_bitwise(order, n, count):
         out.append((nc, t.cpu().numpy().view(np.int64)))
     for o in out[1:]:
         assert o[0] == out[0][0] and np.array_equal(o[1], out[0][1])
+
+
+@pytest.mark.parametrize("sweeps", [1, 2, 5, 9, 10, 18])
+@pytest.mark.parametrize("order,n", [("4c", 48), ("4c", 90), ("8c", 76)])
+def test_gs_first_sweeps_bitwise(order, n, sweeps):
+    print("[case] gs first sweeps", order, n, sweeps, file=sys.stderr, flush=True)
+    from paper_1411_7018_amd import Solver, _lib as L
+    u, f = start(n)
+    out = []
+    for smoother in ("color", "auto"):
+        t = u.clone()
+        with pytest.raises(L.MAError) as ei:
+            Solver(n, order=order, smoother=smoother).gs_solve(t, f, tol=1e-14, max_sweeps=sweeps)
+        out.append((ei.value.report["cycles"], ei.value.report["nonconvex"],
+                    t.cpu().numpy().view(np.int64), np.array(ei.value.report["history"])))
+    assert out[0][:2] == out[1][:2] and np.array_equal(out[0][2], out[1][2])
+    assert np.abs(out[0][3] - out[1][3]).max() <= 1e-12 * out[0][3].max()
