@@ -2238,7 +2238,7 @@ hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc, 
     std::memset(&G, 0, sizeof(G));
     G.n = nf;
     item_dims(LK_PROLONG, 0, nf, &G.gx, &G.gy, &G.gz);
-    G.w = std::min(32, G.gy);
+    G.w = even_strips(G.gy, std::min(32, G.gy));
     G.p[0] = uf;
     G.p[1] = const_cast<double *>(uc);
     G.p[2] = const_cast<double *>(wc);
@@ -2693,8 +2693,8 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
             const int n = mixed ? solves_[i].s->mx[d].n : solves_[i].s->lv[d].n;
             item_dims(kind, order_, n, &gx, &gy, &gz);
             const int w = kind == LK_SWEEP || kind == LK_MSWEEP
-                              ? std::min(gy, colour_items(n, strip_width(n)))
-                              : strip_width(gy);
+                              ? even_strips(gy, std::min(gy, colour_items(n, strip_width(n))))
+                              : even_strips(gy, strip_width(gy));
             const int items = padded_items(gx, gy, gz, w);
             bound += items;
             if (!active[i])
