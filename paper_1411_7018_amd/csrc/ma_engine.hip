@@ -2889,6 +2889,9 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
                 const long t = (n - 1 + 7) / 8;
                 tiles8 += t * t * t;
             }
+            if (order_ != MA_COLOR4 && smoother_ == MA_SMOOTHER_AUTO && block_n_ == 0 &&
+                nmax <= 64 && tiles8 > kBlockTiles8)
+                blk = false;
             // z-stream levels take a z-stream shape (tile_config 8..12, else
             // the automatic pick), the others a block shape (tile_config
             // 1..7, else the automatic pick)

@@ -64,6 +64,13 @@ inline int block_limit(int order, int block_n)
 {
     return block_n == 0 ? (order == MA_COLOR4 ? 64 : 88) : block_n < kBlockMaxN ? block_n : kBlockMaxN;
 }
+// With 8 colours the grids of a depth of up to 64 intervals take colour launches
+// when they have more 8^3 tiles together: many small grids fill the chip as one
+// large one does, and their 8-wide blocks recompute most.  Six cycles of a batch,
+// colour launches / blocks, ms: 2 grids of n = 64 (1024 tiles) 2.48 / 2.11, 3: 2.22
+// / 2.46, 16: 4.8 / 7.5; 64 of n = 24 2.7 / 3.6; wider blocks pay: 2 of n = 80
+// (2000) 2.58 / 2.18, 2 of n = 88 2.67 / 2.50.
+constexpr long kBlockTiles8 = 1200;
 // 8-colour sweeps above that limit as two launches of four phases each, from n
 // = least on.  In the engine, whose colour phases go by strips, from kGroupN; a
 // V-cycle against colour launches in us: n = 136: 450 / 491, 160: 555 / 664,
