@@ -942,6 +942,33 @@ __global__ __launch_bounds__(BX *BY) void k2_zero_interior(double *__restrict__ 
     u[i + long(n + 1) * j] = 0.0;
 }
 
+// A phase of a lone sweep as a launch of its own.  4 colours: in place.
+// Red-black: the colour's new values into t (out = t), then back (commit).
+template <int ORDER>
+__global__ __launch_bounds__(BX *BY) void k2_phase(double *u, const double *__restrict__ F,
+                                                   double *out, int n, int color,
+                                                   unsigned long long *cnt, bool commit)
+{
+    const int y = int(blockIdx.y * BY + threadIdx.y);
+    const int j = ORDER == MA2D_COLOR4 ? ((color & 2) ? 1 : 2) + 2 * y : 1 + y;
+    const bool odd = ORDER == MA2D_COLOR4 ? (color & 1) != 0 : ((color + j) & 1) != 0;
+    const int i = (odd ? 1 : 2) + 2 * int(blockIdx.x * BX + threadIdx.x);
+    const bool in = i <= n - 1 && j <= n - 1;
+    int bad = 0;
+    if (in) {
+        const long sy = n + 1, p = i + sy * j;
+        if (commit) {
+            u[p] = out[p];
+        } else {
+            const double s = double(n) * double(n);
+            const Nine v{u[p - 1],      u[p + 1],      u[p - sy],     u[p + sy],
+                         u[p - sy - 1], u[p - sy + 1], u[p + sy - 1], u[p + sy + 1]};
+            out[p] = update1(u[p], v, F[p], s, 0.5 / s, true, bad);
+        }
+    }
+    count_nonconvex(bad, cnt);
+}
+
 inline dim3 grid2(int cx, int cy) { return dim3((cx + BX - 1) / BX, (cy + BY - 1) / BY); }
 
 double now_s()
@@ -1172,11 +1199,41 @@ ma_status run_legs(ma2d_solver *s, int l, const std::vector<Leg> &v, const doubl
     return MA_OK;
 }
 
+// Whether a lone sweep in place takes less as a launch per phase than as a leg,
+// which needs a copy beside it.  In between, u and F are in the L2 caches and
+// the copy takes half the time; above, the phases read them again from farther
+// away, and below, the launches count.  us, phases / leg: 4 colours n = 640: 15.5
+// / 14.6, 768: 16.4 / 18.7, 1024: 19.1 / 23.4, 1536: 29.8 / 34.9, 1700: 38.9 / 38.4;
+// red-black n = 900: 21.2 / 20.1, 1024: 22.4 / 24.5, 1100: 26.0 / 24.6.
+bool lone_phases(int order, int n)
+{
+    return order == MA2D_COLOR4 ? n >= 704 && n <= 1664 : n >= 992 && n <= 1056;
+}
+
+ma_status sweep_phases(ma2d_solver *s, int l, double *u, const double *F)
+{
+    const int n = s->ns[l];
+    for (int c = 0; c < (s->p.order == MA2D_COLOR4 ? 4 : 2); ++c) {
+        if (s->p.order == MA2D_COLOR4) {
+            hipLaunchKernelGGL((k2_phase<MA2D_COLOR4>), grid2(n / 2, n / 2), dim3(BX, BY), 0, s->st,
+                               u, F, u, n, c, s->cnt, false);
+        } else {
+            for (int commit = 0; commit < 2; ++commit)
+                hipLaunchKernelGGL((k2_phase<MA2D_RED_BLACK>), grid2(n / 2, n - 1), dim3(BX, BY),
+                                   0, s->st, u, F, s->t[l], n, c, s->cnt, commit != 0);
+        }
+        H2_HIP(s, hipGetLastError());
+    }
+    return MA_OK;
+}
+
 // count sweeps of level l from x to u (x may be u)
 ma_status sweep2(ma2d_solver *s, int l, const double *x, double *u, const double *F, int count)
 {
     if (count <= 0 && x == u)
         return MA_OK;
+    if (count == 1 && x == u && lone_phases(s->p.order, s->ns[l]))
+        return sweep_phases(s, l, u, F);
     const std::vector<Leg> v = legs_of(count);
     if (x == u && v.size() % 2) {
         H2_HIP(s, mafas::launch_copy(s->st, pts2(s->ns[l]), u, s->t[l]));

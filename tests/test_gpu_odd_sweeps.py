@@ -1,5 +1,5 @@
 """An odd number of sweeps, whose last one runs in one launch with a copy back
-or per colour by the size, and the Gauss-Seidel solver's first sweeps, looked at
+or per colour by the size (in two dimensions too), and the Gauss-Seidel solver's first sweeps, looked at
 one by one: the bits of the colour launches on both sides of each size."""
 import sys
 
@@ -53,3 +53,28 @@ def test_gs_first_sweeps_bitwise(order, n, sweeps):
                     t.cpu().numpy().view(np.int64), np.array(ei.value.report["history"])))
     assert out[0][:2] == out[1][:2] and np.array_equal(out[0][2], out[1][2])
     assert np.abs(out[0][3] - out[1][3]).max() <= 1e-12 * out[0][3].max()
+
+
+@pytest.mark.parametrize("order,n", [("4c", 702), ("4c", 704), ("4c", 1025), ("rb", 990),
+                                     ("rb", 992), ("rb", 1025)])
+def test_lone_2d_sweep_bitwise(order, n):
+    """A lone sweep as a launch per phase, against the first of three sweeps (no
+    phase launches): the second and third, run apart, end in the same bits."""
+    from paper_1411_7018_amd.solver2d import Solver2D
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    print("[case] lone 2D sweep", order, n, file=sys.stderr, flush=True)
+    x = torch.arange(n + 1, dtype=torch.float64, device="cuda") / n
+    r = x[None, :] ** 2 + x[:, None] ** 2
+    g = torch.Generator(device="cuda").manual_seed(n)
+    u = torch.exp(r / 2)
+    u[1:-1, 1:-1] *= 1.0 + 1e-6 * torch.randn((n - 1, n - 1), generator=g, dtype=torch.float64,
+                                              device="cuda")
+    f = ((1.0 + r) * torch.exp(r)).contiguous()
+    a, b = u.clone(), u.clone()
+    s = Solver2D(n, order=order)
+    na = s.sweep(a, f, 3)
+    nb = s.sweep(b, f, 1) + s.sweep(b, f, 2)
+    torch.cuda.synchronize()
+    assert na == nb and not torch.equal(a, u)
+    assert torch.equal(a.view(torch.int64), b.view(torch.int64))
