@@ -2,11 +2,11 @@
 
 The engine's arithmetic is fixed; what changes its speed is how the work is
 cut into launches:
-  * ``max_blocks`` -- the cap on the blocks of one row-kernel launch.  Few
-    blocks walk many rows each inside one XCD's window (good L2 reuse of the
-    stencil halos on big grids); many blocks put more waves in flight (good
-    latency hiding).  The largest caps give the 385^3 finest level one row
-    per block.
+  * ``max_blocks`` -- the cap on the wavefronts of one row-kernel launch.  Few
+    walk many rows each inside one XCD's window (good L2 reuse of the stencil
+    halos on big grids); many keep more loads in flight (good latency
+    hiding).  The largest caps give the 385^3 finest level one row per
+    wavefront.
   * ``coarse_n``   -- levels with n <= coarse_n run inside the
     single-workgroup coarse-level kernel instead of one launch per phase.
   * ``strip_rows`` -- the width of the y-strips in which a launch walks its

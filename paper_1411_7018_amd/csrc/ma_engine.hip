@@ -2724,7 +2724,10 @@ ma_status Engine::rebuild(Mode mode, const std::vector<char> &active)
         loff_.push_back(off);
         lng_.push_back(L.ngrids);
         const long b8 = ((bound + 7) / 8) * 8;
-        lgrid_.push_back(bound == 0 ? 0 : int(std::min<long>(b8, max_blocks_)));
+        // a cap of many wavefronts is kept by whole blocks on every XCD
+        const int cap = row_waves(max_blocks_) == 1 ? max_blocks_
+                                                    : max_blocks_ / (8 * kRowWaves) * (8 * kRowWaves);
+        lgrid_.push_back(bound == 0 ? 0 : int(std::min<long>(b8, cap)));
         hbuf_.resize(off + stride_, 0);
         std::memcpy(hbuf_.data() + off, &L, list_bytes(L.ngrids));
         return int(loff_.size()) - 1;

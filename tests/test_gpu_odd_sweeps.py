@@ -1,6 +1,7 @@
 """An odd number of sweeps, whose last one runs in one launch with a copy back
-or per colour by the size (in two dimensions too), and the Gauss-Seidel solver's first sweeps, looked at
-one by one: the bits of the colour launches on both sides of each size."""
+or per colour by the size (in two dimensions too), and the Gauss-Seidel solver's
+first sweeps, looked at one by one: the bits of the colour launches on both sides
+of each size."""
 import sys
 
 import numpy as np
