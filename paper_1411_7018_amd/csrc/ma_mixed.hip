@@ -19,7 +19,9 @@ __global__ void k_zero32(float *__restrict__ dst, size_t count)
 }
 } // namespace
 
-// FP32 d, b, w, r per level and an FP64 injected copy of u on coarse levels.
+// FP32 d, b, w per level, r where the coarse-level kernel may run in global memory
+// (elsewhere the residual stays in LDS), and an FP64 injected copy of u on coarse
+// levels.
 size_t mafas::mixed_bytes(const ma_params *p)
 {
     int ns[32];
@@ -27,7 +29,7 @@ size_t mafas::mixed_bytes(const ma_params *p)
     size_t b = 0;
     for (int l = 0; l < L; ++l) {
         const size_t c = npts(ns[l]);
-        b += 4 * c * sizeof(float);
+        b += (ns[l] <= kCoarseMax ? 4 : 3) * c * sizeof(float);
         if (l > 0)
             b += c * sizeof(double);
     }
@@ -58,7 +60,8 @@ ma_status ma_solver::mixed_allocate()
         MA_TRY(falloc(&m.d, c));
         MA_TRY(falloc(&m.b, c));
         MA_TRY(falloc(&m.w, c));
-        MA_TRY(falloc(&m.r, c));
+        if (m.n <= kCoarseMax)
+            MA_TRY(falloc(&m.r, c));
         if (l > 0)
             MA_TRY(alloc(&m.U, c));
     }

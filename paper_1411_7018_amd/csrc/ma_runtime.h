@@ -27,6 +27,8 @@ namespace mafas {
 
 class Engine;
 
+constexpr int kCoarseMax = 32;   // largest coarse_n
+
 struct Level {
     int n = 0;
     double *u = nullptr;   // iterate (coarse levels; level 0 is the caller's array)
@@ -42,7 +44,7 @@ struct MixedLevel {
     float *d = nullptr;    // correction delta
     float *b = nullptr;    // right-hand side of T(delta) = b
     float *w = nullptr;    // injected delta
-    float *r = nullptr;    // residual of the inner problem
+    float *r = nullptr;    // residual of the inner problem (n <= kCoarseMax: k_tail)
     double *U = nullptr;   // injected FP64 approximation (coarse levels)
 };
 

@@ -63,7 +63,7 @@ bool valid_params(const ma_params *p, std::string &why)
         why = "cycle counts must be >= 0 and 1 <= inner_cycles <= 16";
         return false;
     }
-    if (p->coarse_n < 0 || p->coarse_n > 32) {
+    if (p->coarse_n < 0 || p->coarse_n > kCoarseMax) {
         why = "coarse_n must be in 0..32";
         return false;
     }

@@ -53,6 +53,20 @@ def test_levels_match_oracle():
         assert L.ma_levels(n) == oracle.levels(n)
 
 
+def test_mixed_footprint_counts_what_is_read():
+    """The mixed form adds FP32 d, b, w per level, r on the levels that coarse_n
+    can give to the coarse-level kernel (n <= 32) and an FP64 U below the finest."""
+    from paper_1411_7018_amd import _lib as L
+    for n in (16, 48, 256):
+        p = L.ma_params_default(n)
+        p.order = 1   # no colour-ordered right-hand side in either form
+        plain = L.ma_footprint_bytes(p)
+        p.precision = 1
+        want = sum((m + 1) ** 3 * (4 * (4 if m <= 32 else 3) + (8 if k else 0))
+                   for k, m in enumerate(L.ma_levels(n)))
+        assert L.ma_footprint_bytes(p) - plain == want, n
+
+
 def test_footprint_grows_with_n_and_rejects_invalid():
     from paper_1411_7018_amd import _lib as L
     a = L.ma_footprint_bytes(L.ma_params_default(64))
