@@ -90,8 +90,6 @@ hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc,
 hipError_t launch_poisson_rhs(hipStream_t st, int n, const double *f, double *R);
 // dst = src (count doubles).
 hipError_t launch_copy(hipStream_t st, size_t count, const double *src, double *dst);
-// Copy the Dirichlet layer of src into dst.
-hipError_t launch_copy_boundary(hipStream_t st, int n, const double *src, double *dst);
 // u0 and f0 of an n0 grid injected onto levels n0 / 2, n0 / 4, ... (levels of
 // them; block is set by the launch).
 struct InjectLevels {

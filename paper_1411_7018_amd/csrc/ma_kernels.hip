@@ -162,19 +162,6 @@ __global__ void k_copy(const double *__restrict__ src, double *__restrict__ dst,
         dst[q] = src[q];
 }
 
-__global__ void k_copy_boundary(const double *__restrict__ src, double *__restrict__ dst, int n)
-{
-    const int i = blockIdx.x * RES_BX + threadIdx.x;
-    const int j = blockIdx.y * RES_BY + threadIdx.y;
-    const int k = blockIdx.z;
-    if (i > n || j > n)
-        return;
-    if (i == 0 || i == n || j == 0 || j == n || k == 0 || k == n) {
-        const long q = i + long(n + 1) * (j + long(n + 1) * k);
-        dst[q] = src[q];
-    }
-}
-
 // Injection of u and f onto every coarser level at once: each coarse node,
 // boundary included, takes the finest value at the same point.
 __global__ __launch_bounds__(256) void k_inject_levels(InjectLevels A)
@@ -430,13 +417,6 @@ hipError_t launch_zero_interior(hipStream_t st, int n, double *u)
         return hipSuccess;
     hipLaunchKernelGGL(k_zero_interior, res_grid(n - 1, n - 1, n - 1), dim3(RES_BX, RES_BY), 0, st,
                        u, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_copy_boundary(hipStream_t st, int n, const double *src, double *dst)
-{
-    const dim3 grid = res_grid(n + 1, n + 1, n + 1), block(RES_BX, RES_BY);
-    hipLaunchKernelGGL(k_copy_boundary, grid, block, 0, st, src, dst, n);
     return hipGetLastError();
 }
 
