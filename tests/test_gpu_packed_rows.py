@@ -39,7 +39,10 @@ def test_sweep_packed_rows(n, order):
 @pytest.mark.parametrize("order,precision", [("4c", "fp64"), ("8c", "fp64"), ("4c", "mixed")])
 def test_cycles_packed_rows(n, order, precision):
     """Levels of several row lengths in the engine, colour launches only
-    (block_n = -1, no coarse-level kernel) against the automatic choice."""
+    (block_n = -1, no coarse-level kernel) against the automatic choice.  (In
+    the mixed form the levels from n = 34 on are the same launches on both sides
+    but for their strips: what is compared is their work order and the smaller
+    levels; test_gpu_mixed_wide_tiles.py has the rest.)"""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_1411_7018_amd import Solver, _lib as L
