@@ -56,13 +56,15 @@ typedef enum { MA_COLOR4 = 0, MA_COLOR8 = 1 } ma_order;
  * weighting (27 points, tensor product of 1/4, 1/2, 1/4) is the default. */
 typedef enum { MA_RESTRICT_FULL = 0, MA_RESTRICT_HALF = 1 } ma_restriction;
 
-/* Smoother kernel selection.  Every choice computes bitwise the same sweep
- * (the same pointwise update on the same neighbour values); they differ in
- * data movement.  The block sweep runs the four colour phases of one sweep
- * in one launch: each workgroup updates a block of the grid with a halo in
- * LDS, recomputing the halo's updates, out of place into a second array
- * (pairs of sweeps go u -> t -> u; an odd last sweep runs per colour).  It
- * applies to the 4-colour ordering in MA_FP64 only. */
+/* Smoother kernel selection (MA_FP64; the mixed form has colour launches).
+ * Every choice computes bitwise the same sweep (the same pointwise update on
+ * the same neighbour values); they differ in data movement.  The block sweep
+ * runs the colour phases of one sweep in one launch: each workgroup updates a
+ * block of the grid with a halo in LDS, recomputing the halo's updates, out of
+ * place into a second array.  In a cycle pairs of sweeps go u -> t -> u and an
+ * odd last sweep runs per colour; with 8 colours from n = 136 on the pair is one
+ * sweep, four phases a launch.  ma_sweep copies an odd last block sweep back to
+ * u, or runs it per colour, whichever is faster at its size. */
 typedef enum {
     MA_SMOOTHER_AUTO = 0,      /* block sweeps on levels with n <= block_n,
                                   z-stream sweeps from zsweep_n on (4 colours)
@@ -113,7 +115,8 @@ typedef struct {
     int coarse_n;          /* levels with n <= coarse_n (0..32) run inside one
                               single-workgroup kernel per solve; 0: off         */
     int max_blocks;        /* cap on the wavefronts of one batched launch
-                              (multiple of 8, 0 automatic = 16384)               */
+                              (multiple of 8, 0 automatic = 16384; above 6144
+                              rounded down to a multiple of 32)                  */
     int strip_rows;        /* x-rows per y-strip in the work order of a batched
                               launch (strips are walked along z; 0 automatic)    */
     int zsweep_n;          /* MA_SMOOTHER_AUTO, 4-colour FP64: z-stream sweeps

@@ -3,7 +3,8 @@
 // launches per level (k2_leg: the sweeps of one leg with the transfer beside
 // them) driven from the host, and one for all the levels n <= 64 (k2_tail): a
 // 2D grid of the sizes this variant targets (up to 8193^2) fills the chip on
-// its own, so no batching is needed.
+// its own, so no batching is needed.  A lone sweep of a middle grid is a launch
+// per phase (k2_phase).
 #include "ma2d.h"
 #include "ma_device.h"
 #include "ma_fsweep.h"
@@ -188,8 +189,9 @@ __device__ __forceinline__ double fmg_value(U uc, int nc, int i, int j)
 // instructions (55 of them 64-bit) of an update on 1.9 x the nodes keep the
 // vector units busy 60% of it, its memory traffic alone would take 0.4 ms, and
 // a tile's load and phases overlap only with other tiles', so the wavefronts
-// count: within 64 registers (launch bound) 6-8% faster than with 70.  From 512^2 down it takes
-// 7-11 us, mostly the latency of its load, phases and store.
+// count: within 64 registers (launch bound) 6-8% faster than with 70 (the 32 x 32
+// 4-colour legs, which no large grid takes, stay at 70).  From 512^2 down a leg
+// takes 7-11 us, mostly the latency of its load, phases and store.
 //   IN   LEG_U    the values of uin
 //        LEG_PRO  uin plus the bilinear interpolation of uc - wc (the
 //                 coarse-grid correction; interior nodes)

@@ -4,8 +4,9 @@
 // residual, FAS restriction with the tau-corrected coarse right-hand side,
 // prolongation, and their FP32 mixed-precision counterparts) is written once
 // below as pt_* functions.  Two kernels drive them:
-//   k_batched  single-wave blocks walk the work items of a BatchList, one
-//              x-row segment of 64 nodes per item.  The items are split into
+//   k_batched  wavefronts (one or four a block) walk the work items of a
+//              BatchList: an x-row segment of 64 nodes, or 64 nodes of a
+//              colour, the rows of a plane after each other.  The items are split into
 //              8 contiguous chunks, one per XCD (blocks are dispatched
 //              round-robin over XCDs), so rows that read each other as
 //              stencil halos are processed on one XCD and share its L2.
@@ -1524,8 +1525,8 @@ __device__ __forceinline__ int div18(int q, unsigned m) { return int((unsigned(q
 //     alone, down and up again, without barriers;
 //   - the Dirichlet data of every level is injected once, at entry.
 // The expressions of a node are those of k_tail, so results are bitwise the
-// same.  A V-cycle from n = 16 takes 41-47 us (55-59 before), a linear one 24 us
-// (32).
+// same.  In kernel traces a V-cycle from n = 16 takes 51 us (56 with the norm; 59
+// as k_tail_lds), a linear one 26-29 us (33).
 __host__ __device__ constexpr int tail_pitch(int n) { return n < 9 ? n + 1 : n + 1 + (36 - (n + 1)) % 16; }
 
 // One level in LDS (u and w rows of tail_pitch(n), b and r rows of n + 1).

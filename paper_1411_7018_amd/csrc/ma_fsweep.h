@@ -159,8 +159,8 @@ __device__ __forceinline__ void fs_phases(F f)
 // block, in part_out; launch q + 1, which would overwrite u_{q-1}, first adds
 // them up -- every block the same sum in the same order -- and when the sum
 // meets the test (<= thr, or not finite) sets *stop to its number q and
-// stores nothing, like every launch after it (q > *stop).  So a sweep is one launch, and the host looks at the
-// sums once per batch of launches.  Bound by the latency of one block's chain
+// stores nothing, like every launch after it (q > *stop).  So a sweep is one
+// launch, and the host looks at the sums once per batch of launches.  Bound by the latency of one block's chain
 // (launch, loads, residual, phases): the sums are loaded with the block and
 // added up with its residual, and the test is taken just before the phases.
 // n = 32, a sweep and its test: 29 us as colour launches, a residual, a

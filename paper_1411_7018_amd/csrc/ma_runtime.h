@@ -59,9 +59,10 @@ inline long fs_colour_count(int n)
 constexpr int kBlockMaxN = 1289;
 // Largest n whose sweeps MA_SMOOTHER_AUTO runs as block sweeps (-1: none).
 // A sweep of Monge-Ampere, one launch against the colour launches, in us: 4
-// colours, n = 64: 13 / 14, 96: 26 / 22, 128: 47 / 33; 8 colours (a block
+// colours, n = 64: 11 / 14, 96: 26 / 20, 128: 47 / 31; 8 colours (a block
 // recomputes 2.2-2.7 x its updates, with 4 colours 2.9 x, and replaces eight
-// launches), n = 32: 9 / 20, 64: 15 / 23, 80: 17 / 26, 96: 33 / 30, 128: 60 / 41.
+// launches), n = 32: 9 / 24, 64: 13 / 24, 80: 16 / 27, 88: 22 / 28, 96: 33 / 28, 128:
+// 60 / 39.
 inline int block_limit(int order, int block_n)
 {
     return block_n == 0 ? (order == MA_COLOR4 ? 64 : 88) : block_n < kBlockMaxN ? block_n : kBlockMaxN;
@@ -74,13 +75,13 @@ inline int block_limit(int order, int block_n)
 // (2000) 2.58 / 2.18, 2 of n = 88 2.67 / 2.50.
 constexpr long kBlockTiles8 = 1200;
 // 8-colour sweeps above that limit as two launches of four phases each, from n
-// = least on.  In the engine, whose colour phases go by strips, from kGroupN; a
-// V-cycle against colour launches in us: n = 136: 450 / 491, 160: 555 / 664,
-// 192: 823 / 915, 288: 2100 / 2700.  ma_sweep's colour launches are faster, so
-// there from kGroupSweepN; a sweep in us: n = 144: 64 / 51, 160: 73 / 73, 190:
-// 122 / 115, 256: 310 / 266, 304: 529 / 470, 320: 584 / 588 (u and F no longer
-// fit the last-level cache, and eight launches read u eight times), 384: 853 /
-// 1133.
+// = least on.  In the engine from kGroupN; a V-cycle with them against colour
+// launches on those levels, in us: n = 136: 426 / 438, 144: 487 / 493, 160: 552 /
+// 602, 192: 804 / 893, 256: 1606 / 1831.  Repeated on one grid, as ma_sweep runs
+// them, colour launches find u in the last-level cache and are faster, so there
+// from kGroupSweepN; a sweep in us: n = 144: 64 / 51, 160: 73 / 73, 190: 122 / 113,
+// 256: 310 / 267, 304: 529 / 470, 320: 584 / 588 (u and F no longer fit that cache,
+// and eight launches read u eight times), 384: 853 / 1133.
 constexpr int kGroupSweepN = 320;
 inline bool group_level(int order, int block_n, int n, int least)
 {

@@ -79,8 +79,9 @@ __device__ __forceinline__ double laplacian_planes(const PlaneTerms &D, const Pl
 
 // Walk columns i (any; loads are clamped into the grid) of row j (1 <= j <=
 // n - 1) over planes k0 .. k0 + PLANES - 1 below k1 (k1 uniform, k0 >= 0):
-// node(k, D, C, U, f) takes each plane's terms and F there (f is F's value at
-// the nearest interior node of lanes and planes outside the interior).
+// node(k, C, D, U, f) takes the terms of plane k and of those below and above it
+// and F there (f is F's value at the nearest interior node of lanes and planes
+// outside the interior).
 template <int PLANES, typename PU, typename PF, typename N>
 __device__ __forceinline__ void walk_planes(PU u, PF F, int n, int i, int j, int k0, int k1,
                                             int lane, N node)
