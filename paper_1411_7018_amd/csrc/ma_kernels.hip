@@ -85,19 +85,25 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_sweep_color(
 // plane in flight, 204 us so.  On small grids a launch lasts as long as one
 // wavefront's walk, so their chunks are two planes; residual and norm, us, a
 // gather / chunks of eight / of two: n = 32: 19.3 / 21.5 / 19.3, 64: 20.6 / 23.1 /
-// 22.0, 72: 24.0 / 23.1 / 22.8.
+// 20.9, 72: 24.0 / 23.1 / 22.8.
 // ---------------------------------------------------------------------------
 constexpr int kResPlanes = 8, kResPlanesSmall = 2;
 int residual_planes(int n) { return n <= 65 ? kResPlanesSmall : kResPlanes; }
+// First column of a row's wavefronts: 1 where that saves the row a wavefront of
+// one or two columns (its end columns then write the boundary ones beside them),
+// else 0, without the end columns' stores.  Us, from 0 / 1: residual and norm, 64:
+// 22.0 / 20.9, 129: 33.2 / 30.4; residual, 96: 11.6 / 12.4, 130: 19.5 / 20.7.
+int residual_column(int n) { return n >= 64 && n % RES_BX <= 1 ? 1 : 0; }
 
 template <int OP, int PLANES>
 __global__ __launch_bounds__(RES_BX *RES_BY) void k_residual(const double *__restrict__ u,
                                                              const double *__restrict__ F,
                                                              double *__restrict__ r,
                                                              double *__restrict__ partials,
-                                                             int n, double s, double s4)
+                                                             int n, int x0, double s,
+                                                             double s4)
 {
-    const int i = blockIdx.x * RES_BX + threadIdx.x;
+    const int i = x0 + blockIdx.x * RES_BX + threadIdx.x;
     const int j = blockIdx.y * RES_BY + threadIdx.y;
     const int k0 = blockIdx.z * PLANES, k1 = min(k0 + PLANES, n + 1);
     const bool col = i >= 1 && i <= n - 1 && j >= 1 && j <= n - 1;
@@ -115,8 +121,14 @@ __global__ __launch_bounds__(RES_BX *RES_BY) void k_residual(const double *__res
         if (!col || k < 1 || k > n - 1)
             rv = 0.0;
         acc = fma(rv, rv, acc);
-        if (r && i <= n && j <= n)
-            r[i + long(sy) * j + sz * k] = rv;
+        if (r && i <= n && j <= n) {
+            double *p = r + (i + long(sy) * j + sz * k);
+            *p = rv;
+            if (x0 == 1 && i == 1)
+                p[-1] = 0.0;
+            if (x0 == 1 && i == n - 1)
+                p[1] = 0.0;
+        }
     });
     const double t = block_sum<RES_BX * RES_BY / 64>(acc);
     if (threadIdx.x == 0 && threadIdx.y == 0)
@@ -302,7 +314,7 @@ inline dim3 res_grid(int cnt_x, int cnt_y, int cnt_z)
 namespace {
 dim3 residual_grid(int n)
 {
-    return dim3((n + RES_BX) / RES_BX, (n + RES_BY) / RES_BY,
+    return dim3((n - 2 * residual_column(n) + RES_BX) / RES_BX, (n + RES_BY) / RES_BY,
                 (n + residual_planes(n)) / residual_planes(n));
 }
 } // namespace
@@ -352,7 +364,8 @@ hipError_t launch_residual(hipStream_t st, int op, int n, const double *u, const
     const dim3 grid = residual_grid(n), block(RES_BX, RES_BY);
     const bool small = residual_planes(n) == kResPlanesSmall;
 #define MA_RESIDUAL_LAUNCH(OPV, PL)                                                              \
-    hipLaunchKernelGGL((k_residual<OPV, PL>), grid, block, 0, st, u, F, r, partials, n, s, s4)
+    hipLaunchKernelGGL((k_residual<OPV, PL>), grid, block, 0, st, u, F, r, partials, n,       \
+                       residual_column(n), s, s4)
     if (op == OP_MA) {
         if (small)
             MA_RESIDUAL_LAUNCH(OP_MA, kResPlanesSmall);
