@@ -90,6 +90,8 @@ hipError_t launch_prolong(hipStream_t st, int nf, double *uf, const double *uc,
 hipError_t launch_poisson_rhs(hipStream_t st, int n, const double *f, double *R);
 // dst = src (count doubles).
 hipError_t launch_copy(hipStream_t st, size_t count, const double *src, double *dst);
+// src copied to dst (pinned host memory) and cleared
+hipError_t launch_take(hipStream_t st, size_t count, double *src, double *dst);
 // u0 and f0 of an n0 grid injected onto levels n0 / 2, n0 / 4, ... (levels of
 // them; block is set by the launch).
 struct InjectLevels {

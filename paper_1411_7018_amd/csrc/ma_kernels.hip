@@ -174,6 +174,16 @@ __global__ void k_copy(const double *__restrict__ src, double *__restrict__ dst,
         dst[q] = src[q];
 }
 
+// A look at device scalars: copied out (dst: pinned host memory) and cleared.
+__global__ void k_take(double *__restrict__ src, double *__restrict__ dst, size_t count)
+{
+    const size_t q = blockIdx.x * size_t(blockDim.x) + threadIdx.x;
+    if (q < count) {
+        dst[q] = src[q];
+        src[q] = 0.0;
+    }
+}
+
 // Injection of u and f onto every coarser level at once: each coarse node,
 // boundary included, takes the finest value at the same point.
 __global__ __launch_bounds__(256) void k_inject_levels(InjectLevels A)
@@ -399,6 +409,12 @@ hipError_t launch_copy(hipStream_t st, size_t count, const double *src, double *
     if (count == 0)
         return hipSuccess;
     hipLaunchKernelGGL(k_copy, dim3((count + 255) / 256), dim3(256), 0, st, src, dst, count);
+    return hipGetLastError();
+}
+
+hipError_t launch_take(hipStream_t st, size_t count, double *src, double *dst)
+{
+    hipLaunchKernelGGL(k_take, dim3((count + 255) / 256), dim3(256), 0, st, src, dst, count);
     return hipGetLastError();
 }
 

@@ -89,7 +89,7 @@ inline bool group_level(int order, int block_n, int n, int least)
 }
 size_t mixed_bytes(const ma_params *p);
 // most launches of the Gauss-Seidel iteration between looks at its sums
-constexpr int kGsBatch = 64;
+constexpr int kGsBatch = 32;
 
 hipError_t launch_fill(hipStream_t st, size_t count, double v, double *dst);
 hipError_t launch_fill_u64(hipStream_t st, size_t count, unsigned long long v,
@@ -117,6 +117,7 @@ struct ma_solver {
     double *gs_work = nullptr;            // sums and counts of gs_steps (small grids)
     unsigned long long *dcount = nullptr; // counter of the single-grid kernels
     double *hpin = nullptr;               // pinned host scalars
+    double *hpin_dev = nullptr;           // the same as kernels see them
     unsigned long long *hpin_u64 = nullptr;
     std::vector<double *> owned;
     std::vector<void *> mixed_owned;

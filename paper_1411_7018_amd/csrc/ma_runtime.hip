@@ -565,7 +565,8 @@ ma_status ma_solver::allocate()
     }
     if (hipHostMalloc(reinterpret_cast<void **>(&hpin), (2 * kGsBatch + 2) * sizeof(double)) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&hpin_u64), 4 * sizeof(unsigned long long)) !=
-            hipSuccess)
+            hipSuccess ||
+        hipHostGetDevicePointer(reinterpret_cast<void **>(&hpin_dev), hpin, 0) != hipSuccess)
         return fail(MA_ERR_OOM, "hipHostMalloc failed");
     if (p.precision == MA_MIXED)
         MA_TRY(mixed_allocate());
@@ -643,29 +644,30 @@ ma_status ma_solver::smooth(int l, double *u, const double *F, int count, int op
 }
 
 // The standalone Gauss-Seidel iteration on u by launches of k_gs_step (one
-// sweep each, GsStep in ma_fsweep.h), m of them between looks at the sums.
-// Launch b of a batch that starts from iterate q0, in x[0], sweeps iterate q0 + b
-// into the next (iterate q0 + b is in x[b & 1]) and tests iterate q0 + b - 1
-// where that is one of the batch; the last two iterates' sums are taken after
-// the launches.  test(q, residual) is the host's test of iterate q, the same on
-// the same sum (thr: sum_threshold), so both stop at the same iterate;
-// *nonconvex counts the sweeps up to it.
+// sweep each, GsStep in ma_fsweep.h), in batches with a look at the sums behind
+// each.  Launches chain from iterate base, in x[0]: launch e takes iterate base + e,
+// in x[e & 1], to the next and tests iterate base + e - 1, so a look knows all but
+// the chain's last two iterates.  A batch that closes the chain takes their sums
+// too, and a new one starts from its last iterate.  test(q, residual) is the host's
+// test of iterate q, the same on the same sum (thr: sum_threshold), so both stop at
+// the same iterate; *nonconvex counts the sweeps up to it.
 //
-// A solve may stop anywhere in a batch, and what is queued behind that still
-// loads its blocks, so a batch is at most half (from n = 41 on, a quarter) of
-// the sweeps before it, and the first sweeps are looked at one by one: on larger
-// grids as colour launches, since k_gs_step takes a residual that a lone sweep
-// has no use for (4 colours n = 96, 3 sweeps 263 us with it, 235 without; n = 64,
-// where the launches count, 5 sweeps 249 / 280).  us a solve, every sweep looked
-// at / batches of 32 from the start / so: 4 colours n = 32, 1 sweep 83 / 179 / 62,
-// 6 sweeps 243 / 209 / 192; n = 96, 3 sweeps 257 / 577 / 235, 40 sweeps 1990 /
-// 1297 / 1598; 8 colours n = 80, 3 sweeps 246 / 668 / 230.
+// Where the batches end: a look costs 20 to 25 us, a launch queued behind the
+// iterate a solve stops at still loads its block (3.5 us at n = 32, 11 at 96), and
+// a sweep looked at by itself 30 to 50.  So the first batch is what costs about
+// as much as one such look (from n = 77, 8 colours 73, on eight lone sweeps, as colour
+// launches: k_gs_step takes a residual that a lone sweep has no use for), the next
+// ones double, and from 32 sweeps on the waste is bounded by a batch of 32.  us a
+// solve, every sweep looked at / batches of 32 throughout / so: 4 colours n = 32, 1
+// sweep 87 / 183 / 97, 5: 208 / 203 / 185, 20: 661 / 271 / 302, 888: 26130 / 7990 /
+// 7855; n = 64, 2: 116 / 251 / 130, 8: 328 / 317 / 287, 60: 2090 / 1016 / 1067; n =
+// 84 (lone sweeps by k_gs_step in batches of 1, 2, 5 ..: 3: 263, 8: 499), 3: 195 /
+// 495 / 161, 8: 430 / 586 / 364; n = 96, 3: 215 / 567 / 182, 40: 2081 / 1788 / 1840.
 ma_status ma_solver::gs_steps(double *u, const double *F, int max_sweeps, double thr,
                               const std::function<bool(int, double)> &test, long long *nonconvex)
 {
     const int n = p.n, blocks = gs_blocks(p.order, n);
-    const int part_of = n <= 40 ? 2 : 4;
-    const bool colours = n > (p.order == MA_COLOR4 ? 84 : 72);   // a lone sweep's launches
+    const bool colours = n > (p.order == MA_COLOR4 ? 76 : 72);
     const double h = 1.0 / double(n);
     // block sums of two iterates; a batch's counts and, behind them, its sums
     double *part[2] = {gs_work, gs_work + blocks}, *res = gs_work + 2 * blocks;
@@ -673,39 +675,65 @@ ma_status ma_solver::gs_steps(double *u, const double *F, int max_sweeps, double
     int *stop = reinterpret_cast<int *>(res + 2 * kGsBatch + 2);
     double *x[2] = {u, lv[0].t};
     tick_state = 0;
-    MA_HIP(this, launch_fill(stream, 1, 0.0, res + 2 * kGsBatch + 2));
+    MA_HIP(this, launch_fill(stream, 2 * kGsBatch + 3, 0.0, res));
     *nonconvex = 0;
-    int q0 = 0;   // sweeps tested; iterate q0 is in x[0]
+    static constexpr int kEnds[4][5] = {{4, 16, 32}, {2, 8, 16, 32}, {1, 3, 8, 16, 32}, {8, 12, 20, 32}};
+    const auto &ends = kEnds[colours ? 3 : n > 56 ? 2 : n > 40 ? 1 : 0];
+    auto batch_end = [&](int q) {   // of the batch that starts after q sweeps
+        if (colours && q < 8)
+            return q + 1;
+        for (int e : ends)
+            if (e > q)
+                return e;
+        return q + kGsBatch;
+    };
+    int base = 0, done = 0, tested = 0;   // launches since base; iterates tested
+    std::vector<unsigned long long> pending;   // counts of the sweeps not tested
     bool stopped = false;
-    while (!stopped && q0 < max_sweeps) {
-        const int m = std::min({std::max(q0 / part_of, 1), kGsBatch, max_sweeps - q0});
+    while (!stopped && base + done < max_sweeps) {
+        const int q0 = base + done;
+        const int m = std::min(batch_end(q0), max_sweeps) - q0;
+        const bool close = q0 == 0 || m < 3 || q0 + m == max_sweeps;
+        const bool here = m == 1 && done == 0 && colours;   // a lone sweep, in x[0]
         double *sums = res + m;
-        MA_HIP(this, launch_fill_u64(stream, m, 0ull, counts));
-        const bool here = m == 1 && colours;   // the sweep stays in x[0]
         if (here)
             MA_HIP(this, launch_sweep_color(stream, OP_MA, p.order, n, x[0], F, counts));
-        for (int b = 0; b < m && !here; ++b)
-            MA_HIP(this, launch_gs_step(stream, p.order, n, x[b & 1], x[1 - (b & 1)], F,
-                                        b >= 2 ? part[1 - (b & 1)] : nullptr, part[b & 1],
-                                        sums + b, counts + b, stop, q0 + b + 1, thr));
-        if (m >= 2)   // the block sums of iterate q0 + m - 1 are there
-            MA_HIP(this, launch_reduce(stream, part[1 - (m & 1)], blocks, sums + m));
-        MA_HIP(this, launch_residual(stream, OP_MA, n, x[here ? 0 : m & 1], F, nullptr,
-                                     partials));
-        MA_HIP(this, launch_reduce(stream, partials, residual_partials(n), sums + m + 1));
-        MA_HIP(this, hipMemcpyAsync(hpin, res, (2 * m + 2) * sizeof(double), hipMemcpyDeviceToHost,
-                                    stream));
-        MA_HIP(this, hipStreamSynchronize(stream));
-        int b = 0;   // iterate q0 + b was tested last
-        while (!stopped && b < m) {
-            unsigned long long c;
-            std::memcpy(&c, hpin + b++, sizeof(c));
-            *nonconvex += (long long)c;
-            stopped = test(q0 + b, std::sqrt(hpin[m + b + 1] * h * h * h));
+        for (int b = 0; b < m && !here; ++b) {
+            const int e = done + b;
+            MA_HIP(this, launch_gs_step(stream, p.order, n, x[e & 1], x[1 - (e & 1)], F,
+                                        e >= 2 ? part[1 - (e & 1)] : nullptr, part[e & 1],
+                                        sums + b, counts + b, stop, base + e + 1, thr));
         }
-        q0 += b;
-        if (!here && (b & 1))
-            std::swap(x[0], x[1]);
+        const int before = done;
+        done += m;
+        if (close) {
+            if (done >= 2)   // the block sums of iterate base + done - 1 are there
+                MA_HIP(this, launch_reduce(stream, part[1 - (done & 1)], blocks, sums + m));
+            MA_HIP(this, launch_residual(stream, OP_MA, n, x[here ? 0 : done & 1], F, nullptr,
+                                         partials));
+            MA_HIP(this, launch_reduce(stream, partials, residual_partials(n), sums + m + 1));
+        }
+        MA_HIP(this, launch_take(stream, 2 * m + 2, res, hpin_dev));
+        MA_HIP(this, hipStreamSynchronize(stream));
+        for (int b = 0; b < m; ++b) {
+            unsigned long long c;
+            std::memcpy(&c, hpin + b, sizeof(c));
+            pending.push_back(c);
+        }
+        const int last = base + (close ? done : done - 2);   // iterates whose sums are there
+        size_t k = 0;
+        while (!stopped && tested < last) {
+            ++tested;
+            *nonconvex += (long long)pending[k++];
+            stopped = test(tested, std::sqrt(hpin[m + tested - base + 1 - before] * h * h * h));
+        }
+        pending.erase(pending.begin(), pending.begin() + k);
+        if (close || stopped) {
+            if (!here && ((tested - base) & 1))
+                std::swap(x[0], x[1]);
+            base = tested;
+            done = 0;
+        }
     }
     if (x[0] != u)
         MA_HIP(this, launch_copy(stream, npts(n), x[0], u));

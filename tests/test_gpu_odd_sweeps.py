@@ -56,6 +56,36 @@ def test_gs_first_sweeps_bitwise(order, n, sweeps):
     assert np.abs(out[0][3] - out[1][3]).max() <= 1e-12 * out[0][3].max()
 
 
+@pytest.mark.parametrize("order,n", [("4c", 12), ("4c", 40), ("4c", 41), ("4c", 57), ("4c", 76),
+                                     ("4c", 77), ("8c", 12), ("8c", 41), ("8c", 64), ("8c", 73)])
+def test_gs_stops_bitwise(order, n):
+    """A tolerance met at every place of the batches: the iterate, the counts and
+    the history of the sweeps looked at one by one."""
+    print("[case] gs stops", order, n, file=sys.stderr, flush=True)
+    from paper_1411_7018_amd import Solver, _lib as L
+    p = P.exp_cos(n, seed=n)
+    t = np.sin(3.0 * np.arange(n + 1) / n)
+    bump = 1.0 + 0.02 * t[:, None, None] * t[None, :, None] * t[None, None, :]
+    u = torch.from_numpy(P.initial_guess(p, p.u_exact * bump)).cuda()
+    f = torch.from_numpy(p.f.copy()).cuda()
+    one, auto = Solver(n, order=order, smoother="color"), Solver(n, order=order)
+    with pytest.raises(L.MAError) as ei:
+        one.gs_solve(u.clone(), f, tol=1e-14, max_sweeps=64)
+    h = np.array(ei.value.report["history"][:64])
+    # sweeps whose residual is below all before it by more than the sums' round-off
+    ks = [k for k in (*range(1, 21), 31, 32, 33, 34, 35, 63, 64)
+          if h[k - 1] < (1.0 - 1e-6) * min([ei.value.report["res0"], *h[:k - 1]])]
+    assert len(ks) >= 10
+    for k in ks:
+        out = []
+        for s in (one, auto):
+            v = u.clone()
+            rep = s.gs_solve(v, f, tol=(1.0 + 1e-7) * h[k - 1] / ei.value.report["res0"])
+            out.append((rep["cycles"], rep["nonconvex"], v.cpu().numpy().view(np.int64)))
+        assert out[0][0] == out[1][0] == k and out[0][1] == out[1][1]
+        assert np.array_equal(out[0][2], out[1][2])
+
+
 @pytest.mark.parametrize("order,n", [("4c", 702), ("4c", 704), ("4c", 1025), ("rb", 990),
                                      ("rb", 992), ("rb", 1025)])
 def test_lone_2d_sweep_bitwise(order, n):
